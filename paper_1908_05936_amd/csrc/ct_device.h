@@ -184,6 +184,12 @@ struct Seq {
   uint64_t step;
 };
 
+// floor(mix * n / 2^64) for n < 2^32: two 32-bit multiplies instead of a full 128-bit product.
+__device__ __forceinline__ uint64_t scale32(uint64_t mix, uint64_t n) {
+  const uint64_t lo = (mix & 0xFFFFFFFFull) * (uint32_t)n;
+  return ((mix >> 32) * (uint32_t)n + (lo >> 32)) >> 32;
+}
+
 __device__ __forceinline__ Seq probe_seq(const TableView& t, uint64_t key) {
   const uint64_t mix = fmix64(key);
   Seq r;
@@ -191,11 +197,11 @@ __device__ __forceinline__ Seq probe_seq(const TableView& t, uint64_t key) {
     const uint64_t h = voxel21(key);
     r.home = t.nb_pow2 ? (h & (t.nb - 1)) : (h % t.nb);
   } else {
-    r.home = __umul64hi(mix, t.nb);
+    r.home = scale32(mix, t.nb);
   }
   const uint64_t rot = (mix << 32) | (mix >> 32);
   if (t.step_mode == 1) r.step = (rot | 1ull) & (t.nb - 1);
-  else if (t.step_mode == 2) r.step = 1 + __umul64hi(rot, t.nb - 1);
+  else if (t.step_mode == 2) r.step = 1 + scale32(rot, t.nb - 1);
   else r.step = 1;
   if (t.nb == 1) r.step = 0;
   return r;

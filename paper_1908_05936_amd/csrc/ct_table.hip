@@ -31,6 +31,7 @@
 #include "ct.h"
 #include "ct_device.h"
 #include "ct_dev_api.h"
+#include "ct_probe.h"
 
 using namespace ct;
 
@@ -1903,35 +1904,37 @@ __global__ __launch_bounds__(kBlock) void k_fix(TableView t, uint8_t* __restrict
   fix_range(t, status, vout, (int64_t)blockIdx.x * blockDim.x, (int64_t)gridDim.x * blockDim.x);
 }
 
-// find / contains, 8 keys per group and one per lane for loading and storing (coalesced).  The
-// group probes its keys together in rounds: every pending bucket load of a round is issued before
-// the first ballot, so a lane has up to 8 independent 16-byte loads in flight.
+// find / contains: a wave takes 64 consecutive keys, one per lane (coalesced loads and stores), and
+// probes them in rounds until every lane has its answer.
 template <int VK>
-__device__ __forceinline__ void find_range(const TableView& t, const uint64_t* __restrict__ keys,
-                                           void* __restrict__ out, uint8_t* __restrict__ found_out,
-                                           int64_t lo, int64_t hi, int64_t step) {
-  const int sub = threadIdx.x & 7;
-  for (int64_t g0 = lo + (int64_t)(threadIdx.x >> 3) * kSlots; g0 < hi; g0 += step) {
-    const int64_t i = g0 + sub;
+__device__ __forceinline__ void find_range(const TableView& t, WaveLds* w,
+                                           const uint64_t* __restrict__ keys, void* __restrict__ out,
+                                           uint8_t* __restrict__ found_out, int64_t lo, int64_t hi,
+                                           int64_t step) {
+  for (int64_t w0 = lo + (int64_t)(threadIdx.x & ~63u); w0 < hi; w0 += step) {
+    const int64_t i = w0 + wave_lane();
     const bool valid = i < hi;
-    const uint64_t key = valid ? keys[i] : kEmpty;
+    const uint64_t key = keys[min(i, hi - 1)];
+    bool look = valid && key < kTomb;
     bool hit = false;
     uint64_t v = 0;
-    if (valid && key >= kTomb) {
+    if (valid && !look) {
       hit = t.hdr->spec_live[key - kTomb] != 0;
       v = t.hdr->spec_val[key - kTomb];
     }
-    const uint32_t A = group_bits(__ballot(valid && key < kTomb));
-    if (A) {
-      uint32_t found, hadE, freeb;
-      uint64_t mypos = kNoPos, myval = 0, myfb = 0, myexp = 0;
-      int myc = 0;
-      uint64_t mystep = 0;
-      group_probe<false>(t, key, A, sub, &found, &hadE, &freeb, &mypos, &myval, &myfb, &myc, &myexp,
-                         &mystep);
-      if ((A >> sub) & 1) {
-        hit = (found >> sub) & 1;
-        v = myval;
+    const Seq q = probe_seq(t, key);
+    uint32_t b = (uint32_t)q.home;
+    uint32_t left = (uint32_t)t.nb;
+    for (uint64_t mask = __ballot(look); mask; mask = __ballot(look)) {
+      uint64_t val = 0;
+      const uint32_t x = probe_round<false, VK != 0>(t, w, mask, look, key, b, &val);
+      if (look) {
+        if (x & kBitsMatch) {
+          hit = true;
+          v = val;
+        }
+        look = x == 0 && --left != 0;
+        b = next_bucket32(t, b, (uint32_t)q.step);
       }
     }
     if (valid) {
@@ -1941,11 +1944,16 @@ __device__ __forceinline__ void find_range(const TableView& t, const uint64_t* _
   }
 }
 
+// Held to 7 waves per SIMD (72 VGPRs, no spills): 2^27 Zipf lookups in the 2^26-key table took
+// 2.27 ms at 7 waves, 2.37 at 6, 2.60 at 5 (the compiler's choice) and 2.66 at 8, which spills;
+// probing eight keys per 8-lane group with a ballot per key and no packing took 3.51 ms.  Uniform
+// lookups (2^26 keys): 2.04 ms at 6 and 7, 2.33 ms before; 2^24 in a 2^20-key table 0.31, 0.40 before.
 template <int VK>
-__global__ __launch_bounds__(kBlock) void k_find(TableView t, const uint64_t* __restrict__ keys,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) void k_find(TableView t, const uint64_t* __restrict__ keys,
                                                  int64_t n, void* __restrict__ out,
                                                  uint8_t* __restrict__ found_out) {
-  find_range<VK>(t, keys, out, found_out, (int64_t)blockIdx.x * kBlock, n,
+  __shared__ WaveLds w[kBlock / 64];
+  find_range<VK>(t, &w[threadIdx.x >> 6], keys, out, found_out, (int64_t)blockIdx.x * kBlock, n,
                  (int64_t)gridDim.x * kBlock);
 }
 
@@ -2738,9 +2746,11 @@ __device__ __forceinline__ void g_find_body(const GStep* __restrict__ st, const 
   const GStep& g = st[L.step];
   const TableView t = g.v;
   const int64_t lo = (int64_t)L.lb * BS, step = (int64_t)L.nblk * BS;
-  if (g.vk == 1) find_range<1>(t, g.keys, g.vout, g.flags, lo, g.q, step);
-  else if (g.vk == 2) find_range<2>(t, g.keys, g.vout, g.flags, lo, g.q, step);
-  else find_range<0>(t, g.keys, nullptr, g.flags, lo, g.q, step);
+  __shared__ WaveLds wl[BS / 64];
+  WaveLds* w = &wl[threadIdx.x >> 6];
+  if (g.vk == 1) find_range<1>(t, w, g.keys, g.vout, g.flags, lo, g.q, step);
+  else if (g.vk == 2) find_range<2>(t, w, g.keys, g.vout, g.flags, lo, g.q, step);
+  else find_range<0>(t, w, g.keys, nullptr, g.flags, lo, g.q, step);
 }
 
 // The count change into the live count and the feedback words; for a speculative step also the
