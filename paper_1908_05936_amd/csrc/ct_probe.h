@@ -56,13 +56,14 @@ __device__ __forceinline__ uint32_t transpose8(uint32_t x, int sub) {
 template <bool FREE, bool VAL, int NJ>
 __device__ __forceinline__ uint32_t probe_lines(const Bucket* bk, WaveLds* w, uint32_t n, uint32_t g,
                                                 int sub) {
-  u64x2 sl[NJ];
+  u64x2 sl[NJ];  // .y is loaded only with VAL
   const char* base = reinterpret_cast<const char*>(bk) + sub * (int)sizeof(Slot);
   uint32_t r[NJ];
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
     r[j] = NJ == 8 ? (uint32_t)j * 8u + g : min((uint32_t)j * 8u + g, n - 1u);
-    sl[j] = *reinterpret_cast<const u64x2*>(base + w->off[r[j]]);
+    if (VAL) sl[j] = *reinterpret_cast<const u64x2*>(base + w->off[r[j]]);
+    else sl[j].x = *reinterpret_cast<const uint64_t*>(base + w->off[r[j]]);
   }
   // the keys are read back here rather than held across the loads: sixteen registers fewer
   asm volatile("" ::: "memory");
@@ -119,6 +120,104 @@ __device__ __forceinline__ uint32_t next_bucket32(const TableView& t, uint32_t b
   const uint32_t nb = (uint32_t)t.nb;
   const uint32_t nx = b + step;
   return nx >= nb ? nx - nb : nx;
+}
+
+// The WaveLds of this thread's wave in a block of BS threads (one array per kernel).
+template <int BS>
+__device__ __forceinline__ WaveLds* wave_lds() {
+  __shared__ WaveLds w[BS / 64];
+  return &w[threadIdx.x >> 6];
+}
+
+// Where a wave's keys are, or where they go.  Every lane with `look` set walks its key's probe path
+// to the key, or to the first bucket that holds an empty slot; with CLAIM an absent key then takes
+// the first free slot on the path (one CAS per lane, all lanes of the wave at once).
+//
+// Inside a bucket the order of the free slots is fixed per key: tombstones first (an empty slot
+// keeps the bucket open for lookups), and from a slot that depends on the key, so that keys of one
+// bucket that claim at the same time mostly ask for different slots.  With the lowest slot first,
+// 2^14 keys filling 2^14 buckets lost every third claim and retried one key at a time.
+//
+// A claim that loses to another key excludes that slot (the loads may show it free for ever: they
+// are cached) and goes on from the same bucket, looking for the key as well.  Slots only change
+// from free to a key while a kernel inserts, and all copies of a key ask for free slots in the
+// same order, so a copy either claims, sees the key, or loses its CAS to the key: a key is stored
+// once.  Every lost claim excludes one more slot and every step moves one bucket on, at most nb of
+// them, so each lane ends.
+struct Place {
+  bool found;      // the key is there (with CLAIM: or another copy of it got the slot)
+  bool had_empty;  // its bucket holds an empty slot
+  uint64_t pos;    // slot of the key or of the claim; kNoPos: none (!found)
+  uint64_t val;    // value beside the key found (VAL)
+};
+
+template <bool CLAIM, bool VAL>
+__device__ __forceinline__ Place place_keys(const TableView& t, WaveLds* w, bool look, uint64_t key,
+                                            bool claim, uint32_t inject, uint64_t id) {
+  Place r = {false, false, kNoPos, 0};
+  const Seq q = probe_seq(t, key);
+  const uint32_t step = (uint32_t)q.step;
+  uint32_t b = (uint32_t)q.home, left = (uint32_t)t.nb;
+  uint32_t fb = kNone, fc = 0, fleft = 0;   // first free slot on the path (kNone: none yet)
+  bool ftomb = false;
+  uint32_t xb = kNone, xmask = 0;           // slots of one bucket that were lost to other keys
+  bool forced = CLAIM && inject && id % inject == 0;  // test hook: the first claim counts as lost
+  for (uint64_t mask = __ballot(look); mask; mask = __ballot(look)) {
+    uint64_t val = 0;
+    const uint32_t x = probe_round<CLAIM, VAL>(t, w, mask, look, key, b, &val);
+    if (!look) continue;
+    if (x & kBitsMatch) {
+      r.found = true;
+      r.had_empty = ((x >> kEmptyShift) & 0xFFu) != 0;
+      r.pos = (uint64_t)b * kSlots + (uint64_t)__builtin_ctz(x & kBitsMatch);
+      if (VAL) r.val = val;
+      look = false;
+      continue;
+    }
+    uint32_t e = (x >> kEmptyShift) & 0xFFu;
+    if constexpr (CLAIM) {
+      uint32_t tb = (x >> kTombShift) & 0xFFu;
+      if (b == xb) {
+        e &= ~xmask;
+        tb &= ~xmask;
+      }
+      if (fb == kNone && (e | tb)) {
+        fb = b;
+        fleft = left;
+        ftomb = tb != 0;
+        const uint32_t f = (ftomb ? tb : e) * 0x101u;
+        const uint32_t rot = (step >> 1) & 7u;
+        fc = ((uint32_t)__builtin_ctz(f >> rot) + rot) & 7u;
+      }
+    }
+    if (!e && --left != 0) {
+      b = next_bucket32(t, b, step);
+      continue;
+    }
+    look = false;
+    if constexpr (CLAIM) {
+      if (!claim || fb == kNone) continue;
+      uint64_t expected = ftomb ? kTomb : kEmpty;
+      uint64_t* kw = &t.bk[fb].s[fc].key;
+      if (!forced && cas64(kw, expected, key)) {
+        r.pos = (uint64_t)fb * kSlots + fc;
+      } else if (!forced && expected == key) {
+        r.found = true;
+      } else {   // taken by another key: on from the same bucket
+        if (xb != fb) {
+          xb = fb;
+          xmask = 0;
+        }
+        if (!forced) xmask |= 1u << fc;
+        forced = false;
+        b = fb;
+        left = fleft;
+        fb = kNone;
+        look = true;
+      }
+    }
+  }
+  return r;
 }
 
 }  // namespace ct

@@ -725,133 +725,27 @@ __device__ __forceinline__ uint32_t first_copy(const TableView& t, const uint64_
   return (uint32_t)i;
 }
 
-// Group probe of up to 8 keys at once.  Key u of the group (held by lane u, broadcast here) is
-// probed when bit u of `A` is set.  All bucket loads of a round are issued before any is
-// resolved.  Results: bit u of *found / *hadE / *freeb, and on lane u for its own key: the slot
-// and value when found; with WANT_FREE, the first free slot on the probe path (bucket *myfb, slot
-// *myc) and the key word seen there (*myexp, the expected value of a claim).
-template <bool WANT_FREE>
-__device__ __forceinline__ void group_probe(const TableView& t, uint64_t key, uint32_t A, int sub,
-                                            uint32_t* found, uint32_t* hadE, uint32_t* freeb,
-                                            uint64_t* mypos, uint64_t* myval, uint64_t* myfb,
-                                            int* myc, uint64_t* myexp, uint64_t* mystep) {
-  const int gb = group_base();
-  // bucket indices and strides fit 32 bits (fewer than 2^31 buckets): half the registers and
-  // shuffles of 64-bit copies
-  uint64_t kk[kSlots];
-  uint32_t b[kSlots], st[kSlots];
-  Slot sl[kSlots];
-  Seq mine = {0, 0};
-  if ((A >> sub) & 1) mine = probe_seq(t, key);  // each lane hashes its own key once
-  const uint32_t nb32 = (uint32_t)t.nb;
-#pragma unroll
-  for (int u = 0; u < kSlots; ++u) {
-    kk[u] = __shfl(key, gb + u, 64);
-    b[u] = (uint32_t)__shfl((uint32_t)mine.home, gb + u, 64);
-    st[u] = (uint32_t)__shfl((uint32_t)mine.step, gb + u, 64);
-  }
-  uint32_t live = A, fnd = 0, he = 0, frb = 0;
-  for (uint64_t round = 0; live && round < t.nb; ++round) {
-    // unconditional: a branch around each load would make the compiler drain the load queue
-    // before the next one; a finished key re-reads its last bucket (an L1 hit)
-#pragma unroll
-    for (int u = 0; u < kSlots; ++u) sl[u] = t.bk[b[u]].s[sub];
-#pragma unroll
-    for (int u = 0; u < kSlots; ++u) {
-      if (!((live >> u) & 1)) continue;
-      const uint32_t m = group_bits(__ballot(sl[u].key == kk[u]));
-      const uint32_t e = group_bits(__ballot(sl[u].key == kEmpty));
-      if (m) {
-        const int c = lowest(m);
-        const uint64_t v = __shfl(sl[u].val, gb + c, 64);
-        if (sub == u) {
-          *mypos = (uint64_t)b[u] * kSlots + (uint64_t)c;
-          *myval = v;
-        }
-        fnd |= 1u << u;
-        if (e) he |= 1u << u;
-        live &= ~(1u << u);
-        continue;
-      }
-      if (WANT_FREE && !((frb >> u) & 1)) {
-        const uint32_t f = e | group_bits(__ballot(sl[u].key == kTomb));
-        if (f) {
-          const int c = lowest(f);
-          const uint64_t seen = __shfl(sl[u].key, gb + c, 64);
-          frb |= 1u << u;
-          if (sub == u) {
-            *myfb = b[u];
-            *myc = c;
-            *myexp = seen;
-          }
-        }
-      }
-      if (e) {
-        live &= ~(1u << u);
-      } else {
-        const uint32_t nx = b[u] + st[u];   // < 2^32: both terms are below 2^31
-        b[u] = nx >= nb32 ? nx - nb32 : nx;
-      }
-    }
-  }
-  *found = fnd;
-  *hadE = he;
-  *freeb = frb;
-  *mystep = mine.step;
-}
-
-// Claims for the keys of the lanes in `want` (bit u: lane u's key is new and its probe saw a free
-// slot first at bucket myfb, slot myc, holding myexp): every lane claims for its own key, one CAS
-// instruction for the whole group; a key that lost its slot to another key scans on, one key at a
-// time.  Returns this lane's claimed slot (meaningful on `want` lanes), kNoPos when none is left.
-__device__ __forceinline__ uint64_t claim_group(const TableView& t, uint64_t key, uint32_t want,
-                                                int sub, uint64_t myfb, int myc, uint64_t myexp,
-                                                uint64_t mystep, uint32_t inject, uint64_t id) {
-  uint64_t mypos = kNoPos;
-  int won = 0;
-  if ((want >> sub) & 1) {
-    uint64_t expected = myexp;
-    if (!inject || id % inject != 0) won = cas64(&t.bk[myfb].s[myc].key, expected, key) ? 1 : 0;
-  }
-  if (won) mypos = myfb * kSlots + (uint64_t)myc;
-  const uint32_t retry = want & ~group_bits(__ballot(won));
-  if (retry) {
-    const int gb = group_base();
-#pragma unroll
-    for (int u = 0; u < kSlots; ++u) {
-      if (!((retry >> u) & 1)) continue;
-      const uint64_t ku = __shfl(key, gb + u, 64);
-      const uint64_t fbu = __shfl(myfb, gb + u, 64);
-      const uint64_t stu = __shfl(mystep, gb + u, 64);
-      const uint64_t pos = claim(t, ku, fbu, stu, sub);
-      if (sub == u) mypos = pos;
-    }
-  }
-  return mypos;
-}
-
-// Insert actors, 8 elements per group and one per lane.  fast: claim directly with one CAS per
-// new key (all CASes of the group in flight together; a lost race retries one key at a time).
-// Otherwise (or with a pool) flag new keys for the ranked completion.
-// Elements [lo, hi) of a chunk, 8 per group, the block's groups striding by `step` elements.
+// Insert actors, one element per lane.  fast: claim directly with one CAS per new key (all CASes of
+// the wave in flight together).  Otherwise (or with a pool) flag new keys for the ranked
+// completion.  Elements [lo, hi) of a chunk, 64 per wave, the block's waves striding by `step`.
 // `skip` (nullable): elements with a nonzero byte there take no part and keep their outputs.
 // Returns this thread's count of stored keys.
 template <int VK, bool ALLOC>
-__device__ __forceinline__ int64_t insert_range(const TableView& t, const uint64_t* __restrict__ keys,
+__device__ __forceinline__ int64_t insert_range(const TableView& t, WaveLds* w,
+                                                const uint64_t* __restrict__ keys,
                                                 const uint8_t* __restrict__ skip,
                                                 const void* __restrict__ vals, uint32_t dmask,
                                                 uint8_t* __restrict__ status,
                                                 int32_t* __restrict__ vout, int64_t lo, int64_t hi,
                                                 int64_t step) {
-  const int sub = threadIdx.x & 7;
   const bool fast = t.hdr->fast != 0;
   const uint32_t inject = t.hdr->inject;
   const bool flags = ALLOC || !fast;
   int64_t ins = 0;
-  for (int64_t g0 = lo + (int64_t)(threadIdx.x >> 3) * kSlots; g0 < hi; g0 += step) {
-    const int64_t i = g0 + sub;
+  for (int64_t w0 = lo + (int64_t)(threadIdx.x & ~63u); w0 < hi; w0 += step) {
+    const int64_t i = w0 + wave_lane();
     const bool valid = i < hi;
-    const uint64_t key = valid ? keys[i] : kEmpty;
+    const uint64_t key = keys[min(i, hi - 1)];
     // the value is loaded with the key (coalesced) so that its latency hides behind the probe
     const uint64_t val = (!ALLOC && valid) ? load_val<VK>(vals, i) : 0;
     const uint32_t mark = t.dmark[min(i, hi - 1)];
@@ -884,56 +778,24 @@ __device__ __forceinline__ int64_t insert_range(const TableView& t, const uint64
         ++ins;
       }
     }
-    const uint32_t A = group_bits(__ballot(actor && key < kTomb));
-    if (A) {
-      uint32_t found, hadE, freeb;
-      uint64_t mypos = kNoPos, myval = 0, myfb = 0, myexp = 0;
-      int myc = 0;
-      uint64_t mystep = 0;
-      group_probe<true>(t, key, A, sub, &found, &hadE, &freeb, &mypos, &myval, &myfb, &myc, &myexp,
-                        &mystep);
-      const uint32_t want = fast ? (A & ~found & freeb) : 0u;
-      if (want) {
-        // every lane claims for its own key: one CAS instruction for the whole group
-        int won = 0;
-        if ((want >> sub) & 1) {
-          uint64_t expected = myexp;
-          // (test hook: an injected loss leaves the slot free, so the retry below claims it)
-          if (!inject || (uint64_t)i % inject != 0)
-            won = cas64(&t.bk[myfb].s[myc].key, expected, key) ? 1 : 0;
-        }
-        if (won) mypos = myfb * kSlots + (uint64_t)myc;
-        const uint32_t retry = want & ~group_bits(__ballot(won));
-        if (retry) {  // lost a race for the slot to another key: scan on, one key at a time
-          const int gb = group_base();
-#pragma unroll
-          for (int u = 0; u < kSlots; ++u) {
-            if (!((retry >> u) & 1)) continue;
-            const uint64_t ku = __shfl(key, gb + u, 64);
-            const uint64_t fbu = __shfl(myfb, gb + u, 64);
-            const uint64_t stu = __shfl(mystep, gb + u, 64);
-            const uint64_t pos = claim(t, ku, fbu, stu, sub);
-            if (sub == u) mypos = pos;
-          }
-        }
-      }
-      if ((A >> sub) & 1) {
-        if ((found >> sub) & 1) {
-          st = kPresent;
-          if (ALLOC && vout) vout[i] = (int32_t)(uint32_t)myval;
-        } else if (!fast) {
-          newf = 1;
-        } else if (!((want >> sub) & 1) || mypos == kNoPos) {
-          st = kFull;  // no free slot anywhere: cannot happen while size + chunk <= capacity
-          aor32(&t.hdr->err, kErrFull);
-        } else if (ALLOC) {
-          ref = mypos;
-          newf = 1;
-        } else {
-          t.bk[mypos >> 3].s[mypos & 7].val = val;
-          st = kInserted;
-          ++ins;
-        }
+    const bool look = actor && key < kTomb;
+    const Place p = place_keys<true, ALLOC>(t, w, look, key, fast, inject, (uint64_t)i);
+    if (look) {
+      if (p.found) {
+        st = kPresent;
+        if (ALLOC && vout) vout[i] = (int32_t)(uint32_t)p.val;
+      } else if (!fast) {
+        newf = 1;
+      } else if (p.pos == kNoPos) {
+        st = kFull;  // no free slot anywhere: cannot happen while size + chunk <= capacity
+        aor32(&t.hdr->err, kErrFull);
+      } else if (ALLOC) {
+        ref = p.pos;
+        newf = 1;
+      } else {
+        if (VK) t.bk[p.pos >> 3].s[p.pos & 7].val = val;
+        st = kInserted;
+        ++ins;
       }
     }
     if (valid) {
@@ -945,16 +807,18 @@ __device__ __forceinline__ int64_t insert_range(const TableView& t, const uint64
   return ins;
 }
 
-// Map inserts are held to 96 VGPRs (5 waves per SIMD); the set and allocating variants need more
-// and keep the compiler's choice.
+// Held to 5 waves per SIMD (96 VGPRs, no spills), as are the speculative kernels below; the compiler
+// takes 98 to 109 VGPRs, 4 waves.  Of the large-table churn (2^24 keys erased and inserted again,
+// load 0.8) one round took 2.75 ms at 5 waves, 2.83 at 4, 2.78 at 6 and 2.98 at 7, which spill; with
+// eight keys per 8-lane group and claims retried one key at a time it took 2.89 ms.
 template <int VK, bool ALLOC>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu((ALLOC || VK == 0) ? 1 : 5))) void k_insert(TableView t, const uint64_t* __restrict__ keys,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_insert(TableView t, const uint64_t* __restrict__ keys,
                                                    const void* __restrict__ vals, int64_t q,
                                                    uint32_t dmask, uint8_t* __restrict__ status,
                                                    int32_t* __restrict__ vout,
                                                    const uint8_t* __restrict__ skip,
                                                    int count_tiles) {
-  const int64_t ins = insert_range<VK, ALLOC>(t, keys, skip, vals, dmask, status, vout,
+  const int64_t ins = insert_range<VK, ALLOC>(t, wave_lds<kBlock>(), keys, skip, vals, dmask, status, vout,
                                               (int64_t)blockIdx.x * kBlock, q,
                                               (int64_t)gridDim.x * kBlock);
   // one partial per block, summed by k_apply_count: no same-address atomics across the grid
@@ -974,41 +838,27 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu((ALLOC |
 }
 
 // Host-side resizing (a table's capacity is fixed when it is created, Section 4; it grows by a
-// copy into a larger table): every live pair of src is inserted into dst.  One 8-lane group per
-// src bucket, its 8 slots as the group's keys.  The keys of src are distinct and the host has
-// checked that dst has room for all of them, so a new key claims a slot directly; a key dst
-// already holds stays unchanged.  Counts per block, summed by k_apply_count.
+// copy into a larger table): every live pair of src is inserted into dst.  A wave takes 64 slots of
+// src (8 buckets).  The keys of src are distinct and the host has checked that dst has room for
+// all of them, so a new key claims a slot directly; a key dst already holds stays unchanged.
+// Counts per block, summed by k_apply_count.
 __global__ __launch_bounds__(kBlock) void k_rehash(TableView src, TableView dst) {
-  const int sub = threadIdx.x & 7;
-  const int64_t nbk = (int64_t)src.nb;
-  const int64_t gpb = kBlock / 8;
-  const int64_t ngroups = (int64_t)gridDim.x * gpb;
-  const int64_t span = ((nbk + ngroups - 1) / ngroups) * ngroups;  // equal trips for all lanes
+  const int64_t nslots = (int64_t)src.nb * kSlots;
   const uint32_t inject = dst.hdr->inject;
   int64_t ins = 0;
-  for (int64_t g = (int64_t)blockIdx.x * gpb + (threadIdx.x >> 3); g < span; g += ngroups) {
+  for (int64_t w0 = (int64_t)blockIdx.x * kBlock + (threadIdx.x & ~63u); w0 < nslots;
+       w0 += (int64_t)gridDim.x * kBlock) {
+    const int64_t j = w0 + wave_lane();
     Slot sl;
     sl.key = kEmpty;
     sl.val = 0;
-    if (g < nbk) sl = src.bk[g].s[sub];
-    const bool live = sl.key != kEmpty && sl.key != kTomb;
-    const uint64_t key = live ? sl.key : kEmpty;
-    const uint32_t A = group_bits(__ballot(live));
-    if (!A) continue;
-    uint32_t found, hadE, freeb;
-    uint64_t mypos = kNoPos, myval = 0, myfb = 0, myexp = 0;
-    int myc = 0;
-    uint64_t mystep = 0;
-    group_probe<true>(dst, key, A, sub, &found, &hadE, &freeb, &mypos, &myval, &myfb, &myc, &myexp,
-                      &mystep);
-    const uint32_t want = A & ~found & freeb;
-    uint64_t pos = kNoPos;
-    if (want)
-      pos = claim_group(dst, key, want, sub, myfb, myc, myexp, mystep, inject,
-                        (uint64_t)g * kSlots + (uint64_t)sub);
-    if (live && !((found >> sub) & 1)) {
-      if (((want >> sub) & 1) && pos != kNoPos) {
-        dst.bk[pos >> 3].s[pos & 7].val = sl.val;
+    if (j < nslots) sl = src.bk[j >> 3].s[j & 7];
+    const bool live = sl.key < kTomb;
+    const Place p = place_keys<true, false>(dst, wave_lds<kBlock>(), live, sl.key, true, inject,
+                                            (uint64_t)j);
+    if (live && !p.found) {
+      if (p.pos != kNoPos) {
+        dst.bk[p.pos >> 3].s[p.pos & 7].val = sl.val;
         ++ins;
       } else {
         aor32(&dst.hdr->err, kErrFull);  // not reached while dst has the room the host checked
@@ -1028,17 +878,17 @@ __global__ __launch_bounds__(kBlock) void k_rehash(TableView src, TableView dst)
   if (threadIdx.x == 0) dst.bcnt[blockIdx.x] = tot;
 }
 
-// Erase actors, 8 elements per group.  RELEASE: the removed value is kept for the ordered push.
+// Erase actors, one element per lane.  RELEASE: the removed value is kept for the ordered push.
 template <bool RELEASE>
-__device__ __forceinline__ int64_t erase_range(const TableView& t, const uint64_t* __restrict__ keys,
-                                               uint32_t dmask, uint8_t* __restrict__ erased,
-                                               int64_t lo, int64_t hi, int64_t step) {
-  const int sub = threadIdx.x & 7;
+__device__ __forceinline__ int64_t erase_range(const TableView& t, WaveLds* w,
+                                               const uint64_t* __restrict__ keys, uint32_t dmask,
+                                               uint8_t* __restrict__ erased, int64_t lo, int64_t hi,
+                                               int64_t step) {
   int64_t del = 0;
-  for (int64_t g0 = lo + (int64_t)(threadIdx.x >> 3) * kSlots; g0 < hi; g0 += step) {
-    const int64_t i = g0 + sub;
+  for (int64_t w0 = lo + (int64_t)(threadIdx.x & ~63u); w0 < hi; w0 += step) {
+    const int64_t i = w0 + wave_lane();
     const bool valid = i < hi;
-    const uint64_t key = valid ? keys[i] : kEmpty;
+    const uint64_t key = keys[min(i, hi - 1)];
     const uint32_t mark = t.dmark[min(i, hi - 1)];
     asm volatile("" ::"v"(mark));  // keep the load here, issued with the key's
     const bool actor = valid && first_copy(t, keys, key, i, dmask, mark) == (uint32_t)i;
@@ -1052,20 +902,12 @@ __device__ __forceinline__ int64_t erase_range(const TableView& t, const uint64_
         hit = 1;
       }
     }
-    const uint32_t A = group_bits(__ballot(actor && key < kTomb));
-    if (A) {
-      uint32_t found, hadE, freeb;
-      uint64_t mypos = kNoPos, myval = 0, myfb = 0, myexp = 0;
-      int myc = 0;
-      uint64_t mystep = 0;
-      group_probe<false>(t, key, A, sub, &found, &hadE, &freeb, &mypos, &myval, &myfb, &myc, &myexp,
-                         &mystep);
-      if ((found >> sub) & 1) {
-        // kEmpty only where the bucket already holds one: no probe sequence runs through it
-        t.bk[mypos >> 3].s[mypos & 7].key = ((hadE >> sub) & 1) ? kEmpty : kTomb;
-        val = myval;
-        hit = 1;
-      }
+    const Place p = place_keys<false, RELEASE>(t, w, actor && key < kTomb, key, false, 0, 0);
+    if (p.found) {
+      // kEmpty only where the bucket already holds one: no probe sequence runs through it
+      t.bk[p.pos >> 3].s[p.pos & 7].key = p.had_empty ? kEmpty : kTomb;
+      val = p.val;
+      hit = 1;
     }
     if (valid) {
       if (erased) erased[i] = hit;
@@ -1083,7 +925,7 @@ template <bool RELEASE>
 __global__ __launch_bounds__(kBlock) void k_erase(TableView t, const uint64_t* __restrict__ keys,
                                                   int64_t q, uint32_t dmask,
                                                   uint8_t* __restrict__ erased) {
-  const int64_t del = erase_range<RELEASE>(t, keys, dmask, erased, (int64_t)blockIdx.x * kBlock, q,
+  const int64_t del = erase_range<RELEASE>(t, wave_lds<kBlock>(), keys, dmask, erased, (int64_t)blockIdx.x * kBlock, q,
                                            (int64_t)gridDim.x * kBlock);
   const int64_t tot = block_sum(del);
   if (threadIdx.x == 0) t.bcnt[blockIdx.x] = -tot;
@@ -1166,107 +1008,36 @@ __device__ __forceinline__ uint32_t listed_total(const TableView& t) {
   return n;
 }
 
-// Claim for an absent key from bucket b on (the retry after a lost CAS), watching for the key
-// itself: *seen is set when a copy of the key holds a slot on the way.  Returns the claimed slot,
-// or kNoPos (also when seen).
-__device__ __forceinline__ uint64_t claim_watch(const TableView& t, uint64_t key, uint64_t b,
-                                                uint64_t stride, int sub, bool* seen) {
-  for (uint64_t step = 0; step < t.nb; ++step) {
-    const uint64_t cur = t.bk[b].s[sub].key;
-    if (group_bits(__ballot(cur == key))) {
-      *seen = true;
-      return kNoPos;
-    }
-    uint32_t f = group_bits(__ballot(cur == kEmpty || cur == kTomb));
-    while (f) {
-      const int c = lowest(f);
-      int won = 0, same = 0;
-      if (sub == c) {
-        uint64_t expected = cur;
-        won = cas64(&t.bk[b].s[c].key, expected, key) ? 1 : 0;
-        same = !won && expected == key;
-      }
-      if (group_bits(__ballot(won))) return b * kSlots + (uint64_t)c;
-      if (group_bits(__ballot(same))) {
-        *seen = true;
-        return kNoPos;
-      }
-      f &= f - 1;
-    }
-    b = next_bucket(t, b, stride);
-  }
-  return kNoPos;
-}
-
-// Elements [lo, hi) of a chunk, 8 per group.  Returns this thread's (stored, listed) counts.
+// Elements [lo, hi) of a chunk, 64 per wave.  Returns this thread's (stored, listed) counts.
 template <int VK>
-__device__ __forceinline__ uint2 insert_spec_range(const TableView& t,
+__device__ __forceinline__ uint2 insert_spec_range(const TableView& t, WaveLds* w,
                                                    const uint64_t* __restrict__ keys,
                                                    const void* __restrict__ vals,
                                                    uint8_t* __restrict__ status, int64_t lo,
                                                    int64_t hi, int64_t step) {
-  const int sub = threadIdx.x & 7;
   const uint32_t inject = t.hdr->inject;
   uint32_t ins = 0, listed = 0;
-  for (int64_t g0 = lo + (int64_t)(threadIdx.x >> 3) * kSlots; g0 < hi; g0 += step) {
-    const int64_t i = g0 + sub;
+  for (int64_t w0 = lo + (int64_t)(threadIdx.x & ~63u); w0 < hi; w0 += step) {
+    const int64_t i = w0 + wave_lane();
     const bool valid = i < hi;
-    const uint64_t key = valid ? keys[i] : kEmpty;
+    const uint64_t key = keys[min(i, hi - 1)];
     const uint64_t val = valid ? load_val<VK>(vals, i) : 0;
     bool amb = valid && key >= kTomb;  // out-of-band keys: resolved after the kernel
     uint8_t st = kPresent;
     uint8_t claimed = 0;
-    const uint32_t A = group_bits(__ballot(valid && key < kTomb));
-    if (A) {
-      uint32_t found, hadE, freeb;
-      uint64_t mypos = kNoPos, myval = 0, myfb = 0, myexp = 0;
-      int myc = 0;
-      uint64_t mystep = 0;
-      group_probe<true>(t, key, A, sub, &found, &hadE, &freeb, &mypos, &myval, &myfb, &myc, &myexp,
-                        &mystep);
-      const uint32_t want = A & ~found & freeb;
-      bool seen = false;
-      if (want) {
-        int won = 0;
-        if ((want >> sub) & 1) {
-          uint64_t expected = myexp;
-          // (test hook: an injected loss leaves the slot free, so the retry below claims it)
-          if (!inject || (uint64_t)i % inject != 0) {
-            won = cas64(&t.bk[myfb].s[myc].key, expected, key) ? 1 : 0;
-            seen = !won && expected == key;
-          }
-        }
-        if (won) mypos = myfb * kSlots + (uint64_t)myc;
-        const uint32_t retry = want & ~group_bits(__ballot(won || seen));
-        if (retry) {  // lost the slot to another key: scan on, one key at a time
-          const int gb = group_base();
-#pragma unroll
-          for (int u = 0; u < kSlots; ++u) {
-            if (!((retry >> u) & 1)) continue;
-            const uint64_t ku = __shfl(key, gb + u, 64);
-            const uint64_t fbu = __shfl(myfb, gb + u, 64);
-            const uint64_t stu = __shfl(mystep, gb + u, 64);
-            bool su = false;
-            const uint64_t pos = claim_watch(t, ku, fbu, stu, sub, &su);
-            if (sub == u) {
-              mypos = pos;
-              seen = su;
-            }
-          }
-        }
-      }
-      if ((A >> sub) & 1) {
-        if (((found >> sub) & 1) || seen) {
-          amb = true;
-        } else if (!((want >> sub) & 1) || mypos == kNoPos) {
-          st = kFull;  // no free slot anywhere: cannot happen while size + chunk <= capacity
-          aor32(&t.hdr->err, kErrFull);
-        } else {
-          if (VK) t.bk[mypos >> 3].s[mypos & 7].val = val;
-          st = kInserted;
-          claimed = 1;
-          ++ins;
-        }
+    const bool look = valid && key < kTomb;
+    const Place p = place_keys<true, false>(t, w, look, key, true, inject, (uint64_t)i);
+    if (look) {
+      if (p.found) {
+        amb = true;
+      } else if (p.pos == kNoPos) {
+        st = kFull;  // no free slot anywhere: cannot happen while size + chunk <= capacity
+        aor32(&t.hdr->err, kErrFull);
+      } else {
+        if (VK) t.bk[p.pos >> 3].s[p.pos & 7].val = val;
+        st = kInserted;
+        claimed = 1;
+        ++ins;
       }
     }
     if (valid) {
@@ -1279,10 +1050,10 @@ __device__ __forceinline__ uint2 insert_spec_range(const TableView& t,
 }
 
 template <int VK>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(VK == 0 ? 1 : 5))) void k_insert_spec(TableView t, const uint64_t* __restrict__ keys,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_insert_spec(TableView t, const uint64_t* __restrict__ keys,
                                                         const void* __restrict__ vals, int64_t q,
                                                         uint8_t* __restrict__ status) {
-  const uint2 c = insert_spec_range<VK>(t, keys, vals, status, (int64_t)blockIdx.x * kBlock, q,
+  const uint2 c = insert_spec_range<VK>(t, wave_lds<kBlock>(), keys, vals, status, (int64_t)blockIdx.x * kBlock, q,
                                         (int64_t)gridDim.x * kBlock);
   // both counts in one reduction: stored in the low half, listed in the high half
   const int64_t tot = block_sum((int64_t)c.x + ((int64_t)c.y << 32));
@@ -1300,49 +1071,34 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(VK == 0 
 // afterwards the lowest listed copy takes the removal over from a higher remover.  A copy cannot
 // miss a key that is still there: an erase writes kEmpty only into buckets that already hold one,
 // so no probe sequence is cut short.  Out-of-band keys are always listed.
-__device__ __forceinline__ uint2 erase_spec_range(const TableView& t, const uint64_t* __restrict__ keys,
+__device__ __forceinline__ uint2 erase_spec_range(const TableView& t, WaveLds* w,
+                                                  const uint64_t* __restrict__ keys,
                                                   uint8_t* __restrict__ erased, int64_t lo,
                                                   int64_t hi, int64_t step) {
-  const int sub = threadIdx.x & 7;
   uint32_t del = 0, listed = 0;
-  for (int64_t g0 = lo + (int64_t)(threadIdx.x >> 3) * kSlots; g0 < hi; g0 += step) {
-    const int64_t i = g0 + sub;
+  for (int64_t w0 = lo + (int64_t)(threadIdx.x & ~63u); w0 < hi; w0 += step) {
+    const int64_t i = w0 + wave_lane();
     const bool valid = i < hi;
-    const uint64_t key = valid ? keys[i] : kEmpty;
-    bool amb = valid && key >= kTomb;
+    const uint64_t key = keys[min(i, hi - 1)];
+    const Place p = place_keys<false, false>(t, w, valid && key < kTomb, key, false, 0, 0);
     uint8_t hit = 0;
-    const uint32_t A = group_bits(__ballot(valid && key < kTomb));
-    if (A) {
-      uint32_t found, hadE, freeb;
-      uint64_t mypos = kNoPos, myval = 0, myfb = 0, myexp = 0;
-      int myc = 0;
-      uint64_t mystep = 0;
-      group_probe<false>(t, key, A, sub, &found, &hadE, &freeb, &mypos, &myval, &myfb, &myc, &myexp,
-                         &mystep);
-      if ((A >> sub) & 1) {
-        if ((found >> sub) & 1) {
-          uint64_t expected = key;
-          const uint64_t gone = ((hadE >> sub) & 1) ? kEmpty : kTomb;
-          if (cas64(&t.bk[mypos >> 3].s[mypos & 7].key, expected, gone)) hit = 1;
-          else amb = true;
-        } else {
-          amb = true;
-        }
-      }
+    if (p.found) {
+      uint64_t expected = key;
+      hit = cas64(&t.bk[p.pos >> 3].s[p.pos & 7].key, expected, p.had_empty ? kEmpty : kTomb) ? 1 : 0;
     }
     if (valid) {
-      t.flag[i] = hit ? kFlagClaimed : (amb ? kFlagListed : kFlagNone);
+      t.flag[i] = hit ? kFlagClaimed : kFlagListed;
       if (erased) erased[i] = hit;
       del += hit;
-      listed += amb ? 1u : 0u;
+      listed += hit ^ 1u;
     }
   }
   return make_uint2(del, listed);
 }
 
-__global__ __launch_bounds__(kBlock) void k_erase_spec(TableView t, const uint64_t* __restrict__ keys,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_erase_spec(TableView t, const uint64_t* __restrict__ keys,
                                                        int64_t q, uint8_t* __restrict__ erased) {
-  const uint2 c = erase_spec_range(t, keys, erased, (int64_t)blockIdx.x * kBlock, q,
+  const uint2 c = erase_spec_range(t, wave_lds<kBlock>(), keys, erased, (int64_t)blockIdx.x * kBlock, q,
                                    (int64_t)gridDim.x * kBlock);
   const int64_t tot = block_sum((int64_t)c.x + ((int64_t)c.y << 32));
   if (threadIdx.x == 0) {
@@ -1952,8 +1708,7 @@ template <int VK>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) void k_find(TableView t, const uint64_t* __restrict__ keys,
                                                  int64_t n, void* __restrict__ out,
                                                  uint8_t* __restrict__ found_out) {
-  __shared__ WaveLds w[kBlock / 64];
-  find_range<VK>(t, &w[threadIdx.x >> 6], keys, out, found_out, (int64_t)blockIdx.x * kBlock, n,
+  find_range<VK>(t, wave_lds<kBlock>(), keys, out, found_out, (int64_t)blockIdx.x * kBlock, n,
                  (int64_t)gridDim.x * kBlock);
 }
 
@@ -2706,21 +2461,22 @@ __device__ __forceinline__ void g_insert_body(const GStep* __restrict__ st, cons
   const GStep& g = st[L.step];
   const TableView t = g.v;
   const int64_t lo = (int64_t)L.lb * BS, step = (int64_t)L.nblk * BS;
+  WaveLds* w = wave_lds<BS>();
   if (t.hdr->spec) {
     uint2 c;
-    if (g.vk == 1) c = insert_spec_range<1>(t, g.keys, g.vals, g.flags, lo, g.q, step);
-    else if (g.vk == 2) c = insert_spec_range<2>(t, g.keys, g.vals, g.flags, lo, g.q, step);
-    else c = insert_spec_range<0>(t, g.keys, nullptr, g.flags, lo, g.q, step);
+    if (g.vk == 1) c = insert_spec_range<1>(t, w, g.keys, g.vals, g.flags, lo, g.q, step);
+    else if (g.vk == 2) c = insert_spec_range<2>(t, w, g.keys, g.vals, g.flags, lo, g.q, step);
+    else c = insert_spec_range<0>(t, w, g.keys, nullptr, g.flags, lo, g.q, step);
     g_spec_counts<BS>(t, c, L.lb, false);
     return;
   }
   int64_t ins;
   if (g.vk == 1)
-    ins = insert_range<1, false>(t, g.keys, nullptr, g.vals, g.db - 1, g.flags, nullptr, lo, g.q, step);
+    ins = insert_range<1, false>(t, w, g.keys, nullptr, g.vals, g.db - 1, g.flags, nullptr, lo, g.q, step);
   else if (g.vk == 2)
-    ins = insert_range<2, false>(t, g.keys, nullptr, g.vals, g.db - 1, g.flags, nullptr, lo, g.q, step);
+    ins = insert_range<2, false>(t, w, g.keys, nullptr, g.vals, g.db - 1, g.flags, nullptr, lo, g.q, step);
   else
-    ins = insert_range<0, false>(t, g.keys, nullptr, nullptr, g.db - 1, g.flags, nullptr, lo, g.q, step);
+    ins = insert_range<0, false>(t, w, g.keys, nullptr, nullptr, g.db - 1, g.flags, nullptr, lo, g.q, step);
   const int64_t tot = block_sum<BS>(ins);
   if (threadIdx.x == 0) t.bcnt[L.lb] = tot;
 }
@@ -2730,12 +2486,12 @@ __device__ __forceinline__ void g_erase_body(const GStep* __restrict__ st, const
   const GStep& g = st[L.step];
   const TableView t = g.v;
   if (t.hdr->spec) {
-    const uint2 c = erase_spec_range(t, g.keys, g.flags, (int64_t)L.lb * BS, g.q,
+    const uint2 c = erase_spec_range(t, wave_lds<BS>(), g.keys, g.flags, (int64_t)L.lb * BS, g.q,
                                      (int64_t)L.nblk * BS);
     g_spec_counts<BS>(t, c, L.lb, true);
     return;
   }
-  const int64_t del = erase_range<false>(t, g.keys, g.db - 1, g.flags, (int64_t)L.lb * BS,
+  const int64_t del = erase_range<false>(t, wave_lds<BS>(), g.keys, g.db - 1, g.flags, (int64_t)L.lb * BS,
                                          g.q, (int64_t)L.nblk * BS);
   const int64_t tot = block_sum<BS>(del);
   if (threadIdx.x == 0) t.bcnt[L.lb] = -tot;
@@ -2746,8 +2502,7 @@ __device__ __forceinline__ void g_find_body(const GStep* __restrict__ st, const 
   const GStep& g = st[L.step];
   const TableView t = g.v;
   const int64_t lo = (int64_t)L.lb * BS, step = (int64_t)L.nblk * BS;
-  __shared__ WaveLds wl[BS / 64];
-  WaveLds* w = &wl[threadIdx.x >> 6];
+  WaveLds* w = wave_lds<BS>();
   if (g.vk == 1) find_range<1>(t, w, g.keys, g.vout, g.flags, lo, g.q, step);
   else if (g.vk == 2) find_range<2>(t, w, g.keys, g.vout, g.flags, lo, g.q, step);
   else find_range<0>(t, w, g.keys, nullptr, g.flags, lo, g.q, step);

@@ -29,3 +29,39 @@ def test_find_batch_sizes(dev, cap, nb, bits):  # noqa: F811
     pool = np.concatenate([keys, distinct_u64(rng, cap), RESERVED])
     for n in SIZES:
         p.find(pool[rng.integers(0, pool.size, size=n)])
+
+
+@pytest.mark.parametrize("path", [ct.INSERT_SPECULATIVE, ct.INSERT_RESOLVE_FIRST])
+@pytest.mark.parametrize("bits", [0, 32, 64])
+@pytest.mark.parametrize("cap,nb", TABLES)
+def test_insert_erase_batch_sizes(dev, cap, nb, bits, path):  # noqa: F811
+    """Batches of every size in SIZES inserted into and erased from tables that fill up, so that
+    many keys claim in the same bucket at the same time, wrap around, and meet FULL."""
+    rng = rng_for(7100 + cap)
+    p = Pair(dev, cap, bits, bucket_count=nb, path=path)
+    pool = np.concatenate([distinct_u64(rng, 2 * cap), RESERVED])
+
+    def batch(n):
+        k = pool[rng.integers(0, pool.size, size=n)]
+        v = rng.integers(0, 1 << 32, size=n, dtype=np.uint64)
+        return k, v.astype(np.uint32) if bits == 32 else v
+
+    for r, n in enumerate(SIZES):
+        p.insert(*batch(n))
+        p.erase(batch(n)[0])
+        p.find(batch(n)[0])
+        if r % 5 == 0:
+            p.g.debug_inject_claim_losses(r % 3)   # every, none or every second first claim lost
+        p.g.size()                                 # the host's size bound: provable chunks again
+    p.same_state()
+
+
+@pytest.mark.parametrize("cap,nb", [(64, 8), (104, 13), (4096, 0)])
+def test_alloc_release_batch_sizes(dev, cap, nb):  # noqa: F811
+    rng = rng_for(7200 + cap)
+    p = Pair(dev, cap, 32, hash_kind=ct.HASH_VOXEL21, bucket_count=nb, pool=cap // 2)
+    pool = np.concatenate([distinct_u64(rng, cap) >> np.uint64(1), RESERVED])
+    for n in SIZES:
+        p.insert_alloc(pool[rng.integers(0, pool.size, size=n)])
+        p.erase_release(pool[rng.integers(0, pool.size, size=n)])
+    p.same_state()
