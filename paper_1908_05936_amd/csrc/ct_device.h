@@ -72,7 +72,7 @@ struct alignas(256) Header {
   uint32_t spec_first[2];  // lowest chunk index of each out-of-band key in the current chunk
   uint32_t err;            // sticky CT_ERR_* bits
   uint32_t fast;           // 1 when the current chunk cannot reach capacity or empty the pool
-  uint32_t ndup;           // duplicate elements listed for the current chunk
+  uint32_t ndup;           // elements listed by a speculative chunk
   uint32_t nnew;           // flagged elements of the current chunk (set by the rank scan)
   uint64_t dump_count;
   uint64_t live_count;
@@ -125,7 +125,7 @@ struct TableView {
   Header* hdr;
   uint64_t* dd;      // dedup scratch: (fingerprint << 32 | lowest chunk index), kEmpty = free
   uint8_t* dmark;   // per chunk element: 1 = its key occurs more than once in the chunk
-  uint2* dup;       // (chunk index, index of its first occurrence)
+  uint32_t* dup;    // per repeated element: index of its key's first occurrence (for k_fix)
   uint8_t* flag;    // per chunk element: 1 = takes part in the rank scan
   uint64_t* ref;    // per chunk element: claimed slot, or the value an erase releases
   uint32_t* tsum;   // per tile: flagged count, then its exclusive prefix
@@ -248,18 +248,6 @@ __device__ __forceinline__ uint64_t aadd64(uint64_t* p, uint64_t v) {
 }
 __device__ __forceinline__ uint32_t aor32(uint32_t* p, uint32_t v) {
   return __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Reserve a position in an append-only list for every active lane with `pred`, one atomic per wave.
-__device__ __forceinline__ uint32_t wave_append(bool pred, uint32_t* counter) {
-  const uint64_t m = __ballot(pred);
-  uint32_t base = 0;
-  if (m) {
-    const int leader = __builtin_ctzll(m);
-    if (wave_lane() == leader) base = aadd32(counter, (uint32_t)__builtin_popcountll(m));
-    base = __shfl(base, leader, 64);
-  }
-  return base + (uint32_t)__builtin_popcountll(m & ((1ull << wave_lane()) - 1ull));
 }
 
 // Sum of `v` over the wave; call with every lane of the wave active.

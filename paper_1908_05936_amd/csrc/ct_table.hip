@@ -246,15 +246,18 @@ __device__ __forceinline__ void prologue_range(const TableView& t, PoolHeader* p
   if (header && threadIdx.x == 0) chunk_header(t, pool, q, 0u);
 }
 
-// zero_tiles: also zero the chunk's tile sums, for an insert kernel that counts its tiles itself.
+// A chunk with a pool ranks its elements: its insert or erase kernel adds to the tile sums.
+__device__ __forceinline__ void zero_tile_sums(const TableView& t, int64_t q) {
+  for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < (q + kTile - 1) / kTile;
+       j += (int64_t)gridDim.x * kBlock)
+    t.tsum[j] = 0;
+}
+
 __global__ __launch_bounds__(kBlock) void k_prologue(TableView t, PoolHeader* pool,
-                                                     uint32_t dslots, int64_t q, int zero_tiles) {
+                                                     uint32_t dslots, int64_t q) {
+  if (pool) zero_tile_sums(t, q);
   prologue_range(t, pool, dslots, q, (int64_t)blockIdx.x * blockDim.x, prologue_units(dslots, q),
                  (int64_t)gridDim.x * blockDim.x, blockIdx.x == 0);
-  if (zero_tiles)
-    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < (q + kTile - 1) / kTile;
-         j += (int64_t)gridDim.x * blockDim.x)
-      t.tsum[j] = 0;
 }
 
 // Lowest index per distinct key of the chunk.  The block takes 256 consecutive elements at a time
@@ -396,6 +399,7 @@ __device__ __forceinline__ int64_t bin_prologue_units(const TableView& t, int64_
 }
 
 __global__ __launch_bounds__(kBlock) void k_bin_prologue(TableView t, PoolHeader* pool, int64_t q) {
+  if (pool) zero_tile_sums(t, q);
   const int64_t nm = (q + 15) / 16;
   const int64_t hi = bin_prologue_units(t, q);
   const uint4 zero = make_uint4(0, 0, 0, 0);
@@ -754,8 +758,9 @@ __device__ __forceinline__ int64_t insert_range(const TableView& t, WaveLds* w,
     const uint32_t first = active ? first_copy(t, keys, key, i, dmask, mark) : 0u;
     const bool actor = active && first == (uint32_t)i;
     const bool dup = active && !actor;
-    const uint32_t slot = wave_append(dup, &t.hdr->ndup);
-    if (dup) t.dup[slot] = make_uint2((uint32_t)i, first);
+    // what k_fix reads: the mark says that the key is repeated, dup[i] names its first copy
+    if (active && (mark || dup)) t.dup[i] = first;
+    if (dup && !mark) t.dmark[i] = 1;  // a later copy of an out-of-band key
 
     uint8_t st = kNoStatus;
     uint8_t newf = 0;
@@ -807,6 +812,18 @@ __device__ __forceinline__ int64_t insert_range(const TableView& t, WaveLds* w,
   return ins;
 }
 
+// The rank flags per tile, by the kernel that wrote them: each pass of the block covers 256
+// consecutive elements, all in one tile, and each thread re-reads the flag it wrote itself; the
+// tile sums were zeroed by the chunk's prologue.
+__device__ __forceinline__ void count_flags(const TableView& t, int64_t q) {
+  for (int64_t b0 = (int64_t)blockIdx.x * kBlock; b0 < q; b0 += (int64_t)gridDim.x * kBlock) {
+    __syncthreads();  // block_sum's partials are reused
+    const int64_t i = b0 + threadIdx.x;
+    const int64_t c = block_sum((int64_t)(i < q ? t.flag[i] : 0));
+    if (threadIdx.x == 0 && c) aadd32(&t.tsum[b0 / kTile], (uint32_t)c);
+  }
+}
+
 // Held to 5 waves per SIMD (96 VGPRs, no spills), as are the speculative kernels below; the compiler
 // takes 98 to 109 VGPRs, 4 waves.  Of the large-table churn (2^24 keys erased and inserted again,
 // load 0.8) one round took 2.75 ms at 5 waves, 2.83 at 4, 2.78 at 6 and 2.98 at 7, which spill; with
@@ -816,25 +833,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
                                                    const void* __restrict__ vals, int64_t q,
                                                    uint32_t dmask, uint8_t* __restrict__ status,
                                                    int32_t* __restrict__ vout,
-                                                   const uint8_t* __restrict__ skip,
-                                                   int count_tiles) {
+                                                   const uint8_t* __restrict__ skip) {
   const int64_t ins = insert_range<VK, ALLOC>(t, wave_lds<kBlock>(), keys, skip, vals, dmask, status, vout,
                                               (int64_t)blockIdx.x * kBlock, q,
                                               (int64_t)gridDim.x * kBlock);
   // one partial per block, summed by k_apply_count: no same-address atomics across the grid
   const int64_t tot = block_sum(ins);
   if (threadIdx.x == 0) t.bcnt[blockIdx.x] = tot;
-  if (ALLOC && count_tiles) {
-    // the rank flags per tile (what k_tile_count computes): each pass of the block covers 256
-    // consecutive elements, all in one tile, and each thread re-reads the flag it wrote itself;
-    // the tile sums were zeroed by the chunk's prologue
-    for (int64_t b0 = (int64_t)blockIdx.x * kBlock; b0 < q; b0 += (int64_t)gridDim.x * kBlock) {
-      __syncthreads();  // block_sum's partials are reused
-      const int64_t i = b0 + threadIdx.x;
-      const int64_t c = block_sum((int64_t)(i < q ? t.flag[i] : 0));
-      if (threadIdx.x == 0 && c) aadd32(&t.tsum[b0 / kTile], (uint32_t)c);
-    }
-  }
+  if (ALLOC) count_flags(t, q);
 }
 
 // Host-side resizing (a table's capacity is fixed when it is created, Section 4; it grows by a
@@ -927,6 +933,10 @@ __global__ __launch_bounds__(kBlock) void k_erase(TableView t, const uint64_t* _
                                                   uint8_t* __restrict__ erased) {
   const int64_t del = erase_range<RELEASE>(t, wave_lds<kBlock>(), keys, dmask, erased, (int64_t)blockIdx.x * kBlock, q,
                                            (int64_t)gridDim.x * kBlock);
+  if (RELEASE) {  // the removals are the rank flags: their total settles the live count
+    count_flags(t, q);
+    return;
+  }
   const int64_t tot = block_sum(del);
   if (threadIdx.x == 0) t.bcnt[blockIdx.x] = -tot;
 }
@@ -1433,8 +1443,8 @@ __global__ __launch_bounds__(kBlock) void k_spec_swap(TableView t, const uint64_
 }
 
 // Flagged count per tile of kTile elements.
-__global__ __launch_bounds__(kBlock) void k_tile_count(TableView t, int64_t q, int only_slow) {
-  if (only_slow && t.hdr->fast) return;
+__global__ __launch_bounds__(kBlock) void k_tile_count(TableView t, int64_t q) {
+  if (t.hdr->fast) return;
   __shared__ uint32_t part[kBlock / 64];
   const int64_t t0 = (int64_t)blockIdx.x * kTile;
   uint64_t c = 0;
@@ -1478,6 +1488,7 @@ __device__ __forceinline__ void rank_totals(const TableView& t, PoolHeader* pool
       else h->err |= kErrPool;
     }
   } else {
+    h->size = h->size0 - nnew;  // every flagged element removed its key
     const uint64_t room_p = (uint64_t)(pool->cap - pool->top0);
     const uint64_t pushed = nnew < room_p ? nnew : room_p;
     pool->top = pool->top0 + (int64_t)pushed;
@@ -1581,17 +1592,31 @@ __device__ __forceinline__ void final_tile(const TableView& t, PoolHeader* pool,
   const Header* h = t.hdr;
   const uint64_t room = t.cap - h->size0;
   const int sub = threadIdx.x & 7;
+  // one lane per element where nothing is left to claim: a release, or new keys that hold their slot
+  // already (eight lanes per element took 20.5 us for the 26,214 releases of a voxel frame, now 5.4)
+  if (MODE == 2 || (MODE == 1 && fast)) {
+    const int64_t top0 = pool->top0, head = pool->head, pcap = pool->cap;
+    for (uint32_t j = threadIdx.x; j < total; j += kBlock) {
+      const int64_t i = t0 + list[j];
+      const int64_t rank = (int64_t)(rbase + j);
+      if constexpr (MODE == 2) {
+        const int64_t pos = top0 + rank;
+        if (pos < pcap) pstack[ring_pos(head, pcap, pos)] = (int32_t)(uint32_t)t.ref[i];
+      } else {  // fast: capacity and pool cover every new key of the chunk
+        const uint32_t v = (uint32_t)pstack[ring_pos(head, pcap, top0 - 1 - rank)];
+        const uint64_t pos = t.ref[i];
+        if (pos >= kSpecRef) t.hdr->spec_val[pos - kSpecRef] = v;
+        else t.bk[pos >> 3].s[pos & 7].val = v;
+        if (status) status[i] = kInserted;
+        if (vout) vout[i] = (int32_t)v;
+      }
+    }
+    return;
+  }
   for (uint32_t j = threadIdx.x >> 3; j < total; j += kBlock / 8) {
     const int64_t i = t0 + list[j];
     const uint64_t rank = rbase + j;
-    if constexpr (MODE == 2) {
-      if (sub == 0) {
-        const int64_t pos = pool->top0 + (int64_t)rank;
-        if (pos < pool->cap)
-          pstack[ring_pos(pool->head, pool->cap, pos)] = (int32_t)(uint32_t)t.ref[i];
-      }
-      continue;
-    } else {
+    if constexpr (MODE != 2) {
       uint64_t lim = room;
       if constexpr (MODE == 1) {
         const uint64_t avail = (uint64_t)pool->top0;
@@ -1610,9 +1635,7 @@ __device__ __forceinline__ void final_tile(const TableView& t, PoolHeader* pool,
         v = (uint64_t)(uint32_t)pstack[ring_pos(pool->head, pool->cap, pool->top0 - 1 - (int64_t)rank)];
       else v = load_val<VK>(vals, i);
       uint64_t pos;
-      if (MODE == 1 && fast) {
-        pos = t.ref[i];
-      } else if (key >= kTomb) {
+      if (key >= kTomb) {
         pos = kSpecRef + (key - kTomb);
         if (sub == 0) t.hdr->spec_live[key - kTomb] = 1;
       } else {
@@ -1644,20 +1667,32 @@ __global__ __launch_bounds__(kBlock) void k_final(TableView t, PoolHeader* pool,
 }
 
 // Later copies of a key take the outcome of its first occurrence: PRESENT (or its value), unless
-// the first occurrence met FULL, which a later copy meets again.
-__device__ __forceinline__ void fix_range(const TableView& t, uint8_t* __restrict__ status,
+// the first occurrence met FULL, which a later copy meets again.  Reads the marks of all q
+// elements, four per thread (they are cleared in units of 16): a list of the later copies would
+// cost the insert kernel one atomic on one address per wave, 12.6 ns each (a pool-valued insert of
+// 2^19 samples, each block met four times, took 131 us with such a list and takes 19 without; this
+// kernel went from 9 to 11).
+__device__ __forceinline__ void fix_range(const TableView& t, int64_t q, uint8_t* __restrict__ status,
                                           int32_t* __restrict__ vout, int64_t lo, int64_t step) {
-  const int64_t nd = t.hdr->ndup;
-  for (int64_t j = lo + threadIdx.x; j < nd; j += step) {
-    const uint2 d = t.dup[j];
-    if (vout) vout[d.x] = vout[d.y];
-    if (status) status[d.x] = status[d.y] == kFull ? kFull : kPresent;
+  const int64_t units = (q + 3) / 4;
+  for (int64_t j = lo + threadIdx.x; j < units; j += step) {
+    const uint32_t m = reinterpret_cast<const uint32_t*>(t.dmark)[j];
+    if (!m) continue;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int64_t i = 4 * j + k;
+      if (!((m >> (8 * k)) & 0xFFu) || i >= q) continue;
+      const uint32_t f = t.dup[i];
+      if (f == (uint32_t)i) continue;
+      if (vout) vout[i] = vout[f];
+      if (status) status[i] = status[f] == kFull ? kFull : kPresent;
+    }
   }
 }
 
-__global__ __launch_bounds__(kBlock) void k_fix(TableView t, uint8_t* __restrict__ status,
+__global__ __launch_bounds__(kBlock) void k_fix(TableView t, int64_t q, uint8_t* __restrict__ status,
                                                 int32_t* __restrict__ vout) {
-  fix_range(t, status, vout, (int64_t)blockIdx.x * blockDim.x, (int64_t)gridDim.x * blockDim.x);
+  fix_range(t, q, status, vout, (int64_t)blockIdx.x * kBlock, (int64_t)gridDim.x * kBlock);
 }
 
 // find / contains: a wave takes 64 consecutive keys, one per lane (coalesced loads and stores), and
@@ -2626,8 +2661,8 @@ __device__ __forceinline__ void g_copy_body(const GCopy* __restrict__ segs, cons
 __device__ __forceinline__ void g_fix_body(const GStep* __restrict__ st, const GLoc L) {
   const GStep& g = st[L.step];
   const TableView t = g.v;
-  if (t.hdr->spec) return;   // (ndup counts listed elements there, not repeated keys)
-  fix_range(t, g.flags, nullptr, (int64_t)L.lb * kBlock, (int64_t)L.nblk * kBlock);
+  if (t.hdr->spec) return;   // resolved already
+  fix_range(t, g.q, g.flags, nullptr, (int64_t)L.lb * kBlock, (int64_t)L.nblk * kBlock);
 }
 
 // One launch per stage: block b of the launch runs the stage's body for its own step.
@@ -2978,7 +3013,7 @@ void dedup_chunk(ct_table* t, const TableView& v, PoolHeader* pool, const uint64
     launch(t, CT_KERNEL_DEDUP, s, [&] { k_bin_fallback_clear<<<flat_blocks(db / 2), kBlock, 0, s>>>(v, db); });
     launch(t, CT_KERNEL_DEDUP, s, [&] { k_bin_fallback_dedup<<<flat_blocks(q), kBlock, 0, s>>>(v, kc, q, db - 1); });
   } else {
-    launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_prologue<<<flat_blocks(db / 2), kBlock, 0, s>>>(v, pool, db, q, 0); });
+    launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_prologue<<<flat_blocks(db / 2), kBlock, 0, s>>>(v, pool, db, q); });
     launch(t, CT_KERNEL_DEDUP, s, [&] { k_dedup<<<flat_blocks(q), kBlock, 0, s>>>(v, kc, nullptr, q, db - 1); });
   }
 }
@@ -3038,16 +3073,16 @@ ct_status insert_chunks(ct_table* t, const TableView& v, int64_t chunk, const ui
       continue;
     }
     dedup_chunk(t, v, nullptr, kc, q, s);
-    launch(t, CT_KERNEL_INSERT, s, [&] { k_insert<VK, false><<<gb, kBlock, 0, s>>>(v, kc, vc, q, db - 1, sc, nullptr, nullptr, 0); });
+    launch(t, CT_KERNEL_INSERT, s, [&] { k_insert<VK, false><<<gb, kBlock, 0, s>>>(v, kc, vc, q, db - 1, sc, nullptr, nullptr); });
     // a chunk that may meet capacity stores more keys in its ranked pass: no report
     launch(t, CT_KERNEL_APPLY, s, [&] { k_apply_count<<<1, 1024, 0, s>>>(v, gb, surely_fast ? q : 0, 0); });
     if (!surely_fast) {
-      launch(t, CT_KERNEL_RANK, s, [&] { k_tile_count<<<ntiles, kBlock, 0, s>>>(v, q, 1); });
+      launch(t, CT_KERNEL_RANK, s, [&] { k_tile_count<<<ntiles, kBlock, 0, s>>>(v, q); });
       const int inl = ntiles <= kInlineRankTiles ? ntiles : 0;
       if (!inl) launch(t, CT_KERNEL_RANK, s, [&] { k_tile_scan<<<1, 1024, 0, s>>>(v, nullptr, ntiles, 0); });
       launch(t, CT_KERNEL_FINAL, s, [&] { k_final<VK, 0><<<ntiles, kBlock, 0, s>>>(v, nullptr, nullptr, kc, vc, q, sc, nullptr, inl); });
     }
-    if (sc) launch(t, CT_KERNEL_FIX, s, [&] { k_fix<<<flat_blocks(q), kBlock, 0, s>>>(v, sc, nullptr); });
+    if (sc) launch(t, CT_KERNEL_FIX, s, [&] { k_fix<<<flat_blocks((q + 3) / 4), kBlock, 0, s>>>(v, q, sc, nullptr); });
     t->size_ub = std::min<uint64_t>(t->size_ub + (uint64_t)q, (uint64_t)t->desc.capacity);
     ct_status r = launched();
     if (r != CT_OK) return r;
@@ -3082,9 +3117,9 @@ ct_status erase_chunks(ct_table* t, ct_pool* p, const uint64_t* keys, int64_t n,
     }
     dedup_chunk(t, t->v, RELEASE ? p->hdr : nullptr, kc, q, s);
     launch(t, CT_KERNEL_ERASE, s, [&] { k_erase<RELEASE><<<gb, kBlock, 0, s>>>(t->v, kc, q, db - 1, ec); });
-    launch(t, CT_KERNEL_APPLY, s, [&] { k_apply_count<<<1, 1024, 0, s>>>(t->v, gb, RELEASE ? 0 : q, 1); });
-    if (RELEASE) {
-      launch(t, CT_KERNEL_RANK, s, [&] { k_tile_count<<<ntiles, kBlock, 0, s>>>(t->v, q, 0); });
+    if (!RELEASE) {
+      launch(t, CT_KERNEL_APPLY, s, [&] { k_apply_count<<<1, 1024, 0, s>>>(t->v, gb, q, 1); });
+    } else {
       const int inl = ntiles <= kInlineRankTiles ? ntiles : 0;
       if (!inl) launch(t, CT_KERNEL_RANK, s, [&] { k_tile_scan<<<1, 1024, 0, s>>>(t->v, p->hdr, ntiles, 2); });
       launch(t, CT_KERNEL_FINAL, s, [&] { k_final<0, 2><<<ntiles, kBlock, 0, s>>>(t->v, p->hdr, p->stack, kc, nullptr, q, nullptr, nullptr, inl); });
@@ -3171,7 +3206,7 @@ ct_status ct_table_init(void* d_buf, int64_t bytes, const ct_table_desc* d, void
   v.cap = (uint64_t)d->capacity;
   v.dd = reinterpret_cast<uint64_t*>(base + L.off_dd);
   v.dmark = base + L.off_dmark;
-  v.dup = reinterpret_cast<uint2*>(base + L.off_dup);
+  v.dup = reinterpret_cast<uint32_t*>(base + L.off_dup);
   v.flag = base + L.off_flag;
   v.ref = reinterpret_cast<uint64_t*>(base + L.off_ref);
   v.tsum = reinterpret_cast<uint32_t*>(base + L.off_tsum);
@@ -3701,20 +3736,17 @@ ct_status insert_alloc_chunks(ct_table* t, ct_pool* p, const uint64_t* keys, con
     int32_t* vc = vals_out ? vals_out + c0 : nullptr;
     const int gb = group_blocks((q + kSlots - 1) / kSlots);
     const int ntiles = (int)((q + kTile - 1) / kTile);
-    // a masked chunk's prologue also zeroes the tile sums, and its insert kernel counts the
-    // rank flags per tile itself: one launch fewer for the small chunks of a reconstruction frame
     if (mc) {
-      launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_prologue<<<flat_blocks(db / 2), kBlock, 0, s>>>(t->v, p->hdr, db, q, 1); });
+      launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_prologue<<<flat_blocks(db / 2), kBlock, 0, s>>>(t->v, p->hdr, db, q); });
       launch(t, CT_KERNEL_DEDUP, s, [&] { k_dedup<<<flat_blocks(q), kBlock, 0, s>>>(t->v, kc, mc, q, db - 1); });
     } else {
       dedup_chunk(t, t->v, p->hdr, kc, q, s);
     }
-    launch(t, CT_KERNEL_INSERT, s, [&] { k_insert<1, true><<<gb, kBlock, 0, s>>>(t->v, kc, nullptr, q, db - 1, sc, vc, mc, mc ? 1 : 0); });
-    if (!mc) launch(t, CT_KERNEL_RANK, s, [&] { k_tile_count<<<ntiles, kBlock, 0, s>>>(t->v, q, 0); });
+    launch(t, CT_KERNEL_INSERT, s, [&] { k_insert<1, true><<<gb, kBlock, 0, s>>>(t->v, kc, nullptr, q, db - 1, sc, vc, mc); });
     const int inl = ntiles <= kInlineRankTiles ? ntiles : 0;
     if (!inl) launch(t, CT_KERNEL_RANK, s, [&] { k_tile_scan<<<1, 1024, 0, s>>>(t->v, p->hdr, ntiles, 1); });
     launch(t, CT_KERNEL_FINAL, s, [&] { k_final<1, 1><<<ntiles, kBlock, 0, s>>>(t->v, p->hdr, p->stack, kc, nullptr, q, sc, vc, inl); });
-    if (sc || vc) launch(t, CT_KERNEL_FIX, s, [&] { k_fix<<<flat_blocks(q), kBlock, 0, s>>>(t->v, sc, vc); });
+    if (sc || vc) launch(t, CT_KERNEL_FIX, s, [&] { k_fix<<<flat_blocks((q + 3) / 4), kBlock, 0, s>>>(t->v, q, sc, vc); });
     t->size_ub = std::min<uint64_t>(t->size_ub + (uint64_t)q, (uint64_t)t->desc.capacity);
     r = launched();
     if (r != CT_OK) return r;
@@ -4462,7 +4494,7 @@ ct_status ct_insert_batch_noalloc(ct_table* t, const uint64_t* keys, const void*
   TableView w = t->v;  // the table's slots and header, the static array's scratch
   w.dd = reinterpret_cast<uint64_t*>(base + kStaticLayout.dd);
   w.dmark = base + kStaticLayout.dmark;
-  w.dup = reinterpret_cast<uint2*>(base + kStaticLayout.dup);
+  w.dup = reinterpret_cast<uint32_t*>(base + kStaticLayout.dup);
   w.flag = base + kStaticLayout.flag;
   w.ref = reinterpret_cast<uint64_t*>(base + kStaticLayout.ref);
   w.tsum = reinterpret_cast<uint32_t*>(base + kStaticLayout.tsum);
