@@ -420,6 +420,29 @@ ct_status ct_insert_alloc_batch_masked(ct_table *t, ct_pool *p, const uint64_t *
 ct_status ct_erase_release_batch(ct_table *t, ct_pool *p, const uint64_t *keys, int64_t n,
                                  uint8_t *erased, void *stream);
 
+/* --- batches with a caller's workspace ------------------------------------------------------ */
+/* A table that left its chunk to the library (chunk 0) holds scratch for chunks of about capacity /
+   8 keys, so a batch that fills it runs as eight or more chunks, each with its own launches.  With
+   a workspace (device memory of ct_workspace_bytes, 256-byte aligned, for this call's use until the
+   work enqueued by it has run) the batch runs in larger chunks.  Results are the same.
+
+   *bytes: what a batch of n keys can use; 0 when the table's own scratch serves it (a batch of one
+   chunk, a chunk that the caller chose, or the large chunks of the largest tables).  Host only. */
+ct_status ct_workspace_bytes(const ct_table *t, int64_t n, int64_t *bytes);
+
+/* ct_insert_batch, ct_erase_batch, ct_insert_alloc_batch (skip NULL) or ct_insert_alloc_batch_masked,
+   and ct_erase_release_batch.  ws may be NULL, and a workspace smaller than ct_workspace_bytes is
+   left unused: the batch then runs as without one.  CT_E_INVALID for a misaligned ws. */
+ct_status ct_insert_batch_ws(ct_table *t, const uint64_t *keys, const void *vals, int64_t n,
+                             uint8_t *status, void *ws, int64_t ws_bytes, void *stream);
+ct_status ct_erase_batch_ws(ct_table *t, const uint64_t *keys, int64_t n, uint8_t *erased, void *ws,
+                            int64_t ws_bytes, void *stream);
+ct_status ct_insert_alloc_batch_ws(ct_table *t, ct_pool *p, const uint64_t *keys,
+                                   const uint8_t *skip, int64_t n, int32_t *vals_out,
+                                   uint8_t *status, void *ws, int64_t ws_bytes, void *stream);
+ct_status ct_erase_release_batch_ws(ct_table *t, ct_pool *p, const uint64_t *keys, int64_t n,
+                                    uint8_t *erased, void *ws, int64_t ws_bytes, void *stream);
+
 /* --- multi-table plans: a schedule of operations over many tables ------------------------- */
 /* A plan records operations on many tables in schedule order and replays them: operations on one
    table keep their order (the results equal those of the single-table calls made in that order)

@@ -2801,6 +2801,7 @@ struct ct_table {
   int64_t bytes;
   TableView v;
   int64_t chunk;      // Q: elements per chunk (power of two)
+  bool chunk_chosen;  // the caller chose it: batches are cut into such chunks, workspace or not
   uint64_t size_ub;   // upper bound of the live count known to the host
   int64_t dd_bytes;   // bytes of the dedup scratch region at v.dd (the purge's bitmap)
   int32_t insert_path = CT_INSERT_AUTO;  // how insert chunks resolve repeated keys
@@ -2853,6 +2854,8 @@ struct Layout {
 
 static_assert(kBinFineCap % kBlock == 0, "fine-bin entries are held kBlock per register row");
 
+bool layout_scratch(Layout* L, int64_t q, int64_t off);
+
 bool make_layout(const ct_table_desc* d, Layout* L) {
   if (!d || d->capacity < 0) return false;
   if (d->val_kind < 0 || d->val_kind > 2 || d->hash_kind < 0 || d->hash_kind > 1) return false;
@@ -2872,12 +2875,17 @@ bool make_layout(const ct_table_desc* d, Layout* L) {
   }
   if (q < 1024 || q > ((int64_t)1 << 24) || (q & (q - 1))) return false;
   L->nb = nb;
-  L->chunk = q;
-  L->dslots = 2 * q;
-  L->ntiles = (q + kTile - 1) / kTile;
   int64_t off = align_up((int64_t)sizeof(Header));
   L->off_bk = off;
   off = align_up(off + nb * (int64_t)sizeof(Bucket));
+  return layout_scratch(L, q, off);
+}
+
+// The per-chunk scratch of chunks of q elements (a power of two in [1024, 2^24]), from offset `off`.
+bool layout_scratch(Layout* L, int64_t q, int64_t off) {
+  L->chunk = q;
+  L->dslots = 2 * q;
+  L->ntiles = (q + kTile - 1) / kTile;
   L->bins = q >= kBinMinChunk;
   if (L->bins) {
     L->nfine = q / kBinFine;
@@ -2921,6 +2929,27 @@ bool make_layout(const ct_table_desc* d, Layout* L) {
   off = align_up(off + kMaxGroupBlocks * 8 + kStripeRegion);
   L->total = off;
   return true;
+}
+
+// Point the view's scratch at the arrays that L lays out from `base`.
+void scratch_view(TableView* v, uint8_t* base, const Layout& L) {
+  v->dd = reinterpret_cast<uint64_t*>(base + L.off_dd);
+  v->dmark = base + L.off_dmark;
+  v->dup = reinterpret_cast<uint32_t*>(base + L.off_dup);
+  v->flag = base + L.off_flag;
+  v->ref = reinterpret_cast<uint64_t*>(base + L.off_ref);
+  v->tsum = reinterpret_cast<uint32_t*>(base + L.off_tsum);
+  v->bcnt = reinterpret_cast<int64_t*>(base + L.off_bcnt);
+  v->r1k = L.bins ? reinterpret_cast<uint64_t*>(base + L.off_r1k) : nullptr;
+  v->r1i = L.bins ? reinterpret_cast<uint32_t*>(base + L.off_r1i) : nullptr;
+  v->r2k = L.bins ? reinterpret_cast<uint64_t*>(base + L.off_r2k) : nullptr;
+  v->r2i = L.bins ? reinterpret_cast<uint32_t*>(base + L.off_r2i) : nullptr;
+  v->bcur = L.bins ? reinterpret_cast<uint32_t*>(base + L.off_bcur) : nullptr;
+  v->dfirst = L.bins ? reinterpret_cast<uint32_t*>(base + L.off_dfirst) : nullptr;
+  v->c1 = L.bins ? (uint32_t)L.c1 : 0u;
+  v->c2 = L.bins ? (uint32_t)L.c2 : 0u;
+  v->lp = L.bins ? L.lp : 0;
+  v->lp1 = L.bins ? L.lp1 : 0;
 }
 
 inline hipStream_t S(void* s) { return reinterpret_cast<hipStream_t>(s); }
@@ -2998,6 +3027,40 @@ ct_status read_back(const T* dev, T* host, hipStream_t s) {
 // ---------------------------------------------------------------------------------------------
 // insert / erase drivers
 // ---------------------------------------------------------------------------------------------
+// The scratch a batch runs on: the table's own with its chunk, or a caller's workspace with larger
+// chunks.
+struct BatchScratch {
+  TableView v;
+  int64_t chunk;
+};
+
+// Chunk of a batch of n keys given a workspace: the whole batch up to 2^21 keys (228 MB), when that
+// is more than the table's own chunk and the caller left the chunk to the library; else 0.  A
+// default table cuts a batch that fills it into eight or more chunks of 6 to 12 launches each,
+// which is what small and middle tables spend their time on: 4 M repeated keys into a set of 10^6
+// took 1.59 ms in chunks of 2^17 and take 0.42 in chunks of 2^21; building, reading and erasing a
+// map of 2^16 keys (four chunks) 143 us, now 78.  At 2^21 keys a chunk's kernels run several times longer than their
+// launches take; the own chunks of the largest tables (2^23) stay.
+constexpr int64_t kWorkspaceChunk = (int64_t)1 << 21;
+
+int64_t workspace_chunk(const ct_table* t, int64_t n) {
+  if (t->chunk_chosen || n <= t->chunk) return 0;
+  const int64_t q = std::min<int64_t>(pow2ceil(n), kWorkspaceChunk);
+  return q > t->chunk ? q : 0;
+}
+
+// The table's own scratch, or `ws` when it holds the chunk that the batch would like.
+BatchScratch batch_scratch(const ct_table* t, int64_t n, void* ws, int64_t ws_bytes) {
+  BatchScratch b = {t->v, t->chunk};
+  const int64_t q = ws ? workspace_chunk(t, n) : 0;
+  Layout L;
+  if (q && layout_scratch(&L, q, 0) && ws_bytes >= L.total) {
+    scratch_view(&b.v, static_cast<uint8_t*>(ws), L);
+    b.chunk = q;
+  }
+  return b;
+}
+
 // Resolve the repeated keys of one chunk: binned for large chunks, dd otherwise.
 void dedup_chunk(ct_table* t, const TableView& v, PoolHeader* pool, const uint64_t* kc, int64_t q,
                  hipStream_t s) {
@@ -3046,14 +3109,14 @@ void spec_resolve(ct_table* t, const TableView& v, const uint64_t* kc, const voi
   launch(t, CT_KERNEL_FIX, s, [&] { k_spec_swap<VK, ERASE><<<g, kBlock, 0, s>>>(v, kc, vc, q, sc); });
 }
 
-// Insert of n keys in chunks of at most `chunk`, with the per-chunk scratch that view `v` names
-// (the table's own, or another region holding the same arrays).
+// Insert of n keys in the chunks and with the scratch of B.
 template <int VK>
-ct_status insert_chunks(ct_table* t, const TableView& v, int64_t chunk, const uint64_t* keys,
+ct_status insert_chunks(ct_table* t, const BatchScratch& B, const uint64_t* keys,
                         const void* vals, int64_t n, uint8_t* status, hipStream_t s) {
+  const TableView& v = B.v;
   const int vb = VK == 1 ? 4 : 8;
-  for (int64_t c0 = 0; c0 < n; c0 += chunk) {
-    const int64_t q = std::min<int64_t>(chunk, n - c0);
+  for (int64_t c0 = 0; c0 < n; c0 += B.chunk) {
+    const int64_t q = std::min<int64_t>(B.chunk, n - c0);
     const uint32_t db = dedup_slots_for(q);
     const uint64_t* kc = keys + c0;
     const void* vc = VK ? static_cast<const void*>(static_cast<const uint8_t*>(vals) + c0 * vb) : nullptr;
@@ -3090,17 +3153,20 @@ ct_status insert_chunks(ct_table* t, const TableView& v, int64_t chunk, const ui
   return CT_OK;
 }
 
-template <int VK>
-ct_status insert_chunks(ct_table* t, const uint64_t* keys, const void* vals, int64_t n,
-                        uint8_t* status, hipStream_t s) {
-  return insert_chunks<VK>(t, t->v, t->chunk, keys, vals, n, status, s);
+ct_status insert_any(ct_table* t, const BatchScratch& B, const uint64_t* keys, const void* vals,
+                     int64_t n, uint8_t* status, hipStream_t s) {
+  const int vk = t->desc.val_kind;
+  if (vk == CT_VAL_U32) return insert_chunks<1>(t, B, keys, vals, n, status, s);
+  if (vk == CT_VAL_U64) return insert_chunks<2>(t, B, keys, vals, n, status, s);
+  return insert_chunks<0>(t, B, keys, nullptr, n, status, s);
 }
 
 template <bool RELEASE>
-ct_status erase_chunks(ct_table* t, ct_pool* p, const uint64_t* keys, int64_t n, uint8_t* erased,
-                       hipStream_t s) {
-  for (int64_t c0 = 0; c0 < n; c0 += t->chunk) {
-    const int64_t q = std::min<int64_t>(t->chunk, n - c0);
+ct_status erase_chunks(ct_table* t, const BatchScratch& B, ct_pool* p, const uint64_t* keys,
+                       int64_t n, uint8_t* erased, hipStream_t s) {
+  const TableView& v = B.v;
+  for (int64_t c0 = 0; c0 < n; c0 += B.chunk) {
+    const int64_t q = std::min<int64_t>(B.chunk, n - c0);
     const uint32_t db = dedup_slots_for(q);
     const uint64_t* kc = keys + c0;
     uint8_t* ec = erased ? erased + c0 : nullptr;
@@ -3108,21 +3174,21 @@ ct_status erase_chunks(ct_table* t, ct_pool* p, const uint64_t* keys, int64_t n,
     const int ntiles = (int)((q + kTile - 1) / kTile);
     if (!RELEASE && use_speculation(t, 1)) {
       // speculative: remove first, then move each removal to the lowest copy of its key
-      launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_spec_prologue<<<1, 64, 0, s>>>(t->v, q, 0); });
-      launch(t, CT_KERNEL_ERASE, s, [&] { k_erase_spec<<<gb, kBlock, 0, s>>>(t->v, kc, q, ec); });
-      spec_resolve<0, true>(t, t->v, kc, nullptr, q, ec, gb, db, s);
+      launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_spec_prologue<<<1, 64, 0, s>>>(v, q, 0); });
+      launch(t, CT_KERNEL_ERASE, s, [&] { k_erase_spec<<<gb, kBlock, 0, s>>>(v, kc, q, ec); });
+      spec_resolve<0, true>(t, v, kc, nullptr, q, ec, gb, db, s);
       ct_status r = launched();
       if (r != CT_OK) return r;
       continue;
     }
-    dedup_chunk(t, t->v, RELEASE ? p->hdr : nullptr, kc, q, s);
-    launch(t, CT_KERNEL_ERASE, s, [&] { k_erase<RELEASE><<<gb, kBlock, 0, s>>>(t->v, kc, q, db - 1, ec); });
+    dedup_chunk(t, v, RELEASE ? p->hdr : nullptr, kc, q, s);
+    launch(t, CT_KERNEL_ERASE, s, [&] { k_erase<RELEASE><<<gb, kBlock, 0, s>>>(v, kc, q, db - 1, ec); });
     if (!RELEASE) {
-      launch(t, CT_KERNEL_APPLY, s, [&] { k_apply_count<<<1, 1024, 0, s>>>(t->v, gb, q, 1); });
+      launch(t, CT_KERNEL_APPLY, s, [&] { k_apply_count<<<1, 1024, 0, s>>>(v, gb, q, 1); });
     } else {
       const int inl = ntiles <= kInlineRankTiles ? ntiles : 0;
-      if (!inl) launch(t, CT_KERNEL_RANK, s, [&] { k_tile_scan<<<1, 1024, 0, s>>>(t->v, p->hdr, ntiles, 2); });
-      launch(t, CT_KERNEL_FINAL, s, [&] { k_final<0, 2><<<ntiles, kBlock, 0, s>>>(t->v, p->hdr, p->stack, kc, nullptr, q, nullptr, nullptr, inl); });
+      if (!inl) launch(t, CT_KERNEL_RANK, s, [&] { k_tile_scan<<<1, 1024, 0, s>>>(v, p->hdr, ntiles, 2); });
+      launch(t, CT_KERNEL_FINAL, s, [&] { k_final<0, 2><<<ntiles, kBlock, 0, s>>>(v, p->hdr, p->stack, kc, nullptr, q, nullptr, nullptr, inl); });
     }
     ct_status r = launched();
     if (r != CT_OK) return r;
@@ -3130,9 +3196,11 @@ ct_status erase_chunks(ct_table* t, ct_pool* p, const uint64_t* keys, int64_t n,
   return CT_OK;
 }
 
-ct_status check_batch(const ct_table* t, const void* keys, int64_t n) {
-  if (!t || n < 0) return CT_E_INVALID;
+ct_status check_batch(const ct_table* t, const void* keys, int64_t n, const void* ws = nullptr,
+                      int64_t ws_bytes = 0) {
+  if (!t || n < 0 || ws_bytes < 0) return CT_E_INVALID;
   if (n > 0 && !keys) return CT_E_INVALID;
+  if (reinterpret_cast<uintptr_t>(ws) % kAlign) return CT_E_INVALID;
   return CT_OK;
 }
 
@@ -3197,6 +3265,7 @@ ct_status ct_table_init(void* d_buf, int64_t bytes, const ct_table_desc* d, void
   t->base = base;
   t->bytes = bytes;
   t->chunk = L.chunk;
+  t->chunk_chosen = d->chunk != 0;
   t->size_ub = 0;
   t->dd_bytes = L.bins ? (int64_t)kBinCoarse * kBinSub * L.c1 * 8 : L.dslots * 8;
   TableView& v = t->v;
@@ -3204,23 +3273,7 @@ ct_status ct_table_init(void* d_buf, int64_t bytes, const ct_table_desc* d, void
   v.bk = reinterpret_cast<Bucket*>(base + L.off_bk);
   v.nb = (uint64_t)L.nb;
   v.cap = (uint64_t)d->capacity;
-  v.dd = reinterpret_cast<uint64_t*>(base + L.off_dd);
-  v.dmark = base + L.off_dmark;
-  v.dup = reinterpret_cast<uint32_t*>(base + L.off_dup);
-  v.flag = base + L.off_flag;
-  v.ref = reinterpret_cast<uint64_t*>(base + L.off_ref);
-  v.tsum = reinterpret_cast<uint32_t*>(base + L.off_tsum);
-  v.bcnt = reinterpret_cast<int64_t*>(base + L.off_bcnt);
-  v.r1k = L.bins ? reinterpret_cast<uint64_t*>(base + L.off_r1k) : nullptr;
-  v.r1i = L.bins ? reinterpret_cast<uint32_t*>(base + L.off_r1i) : nullptr;
-  v.r2k = L.bins ? reinterpret_cast<uint64_t*>(base + L.off_r2k) : nullptr;
-  v.r2i = L.bins ? reinterpret_cast<uint32_t*>(base + L.off_r2i) : nullptr;
-  v.bcur = L.bins ? reinterpret_cast<uint32_t*>(base + L.off_bcur) : nullptr;
-  v.dfirst = L.bins ? reinterpret_cast<uint32_t*>(base + L.off_dfirst) : nullptr;
-  v.c1 = L.bins ? (uint32_t)L.c1 : 0u;
-  v.c2 = L.bins ? (uint32_t)L.c2 : 0u;
-  v.lp = L.bins ? L.lp : 0;
-  v.lp1 = L.bins ? L.lp1 : 0;
+  scratch_view(&v, base, L);
   v.hash = d->hash_kind;
   v.nb_pow2 = (L.nb & (L.nb - 1)) == 0;
   v.step_mode = v.nb_pow2 ? 1 : (is_prime(L.nb) ? 2 : 0);
@@ -3304,16 +3357,26 @@ ct_status ct_table_value_bytes(const ct_table* t, int32_t* bytes) {
   return CT_OK;
 }
 
-ct_status ct_insert_batch(ct_table* t, const uint64_t* keys, const void* vals, int64_t n,
-                          uint8_t* status, void* stream) {
-  ct_status r = check_batch(t, keys, n);
+ct_status ct_insert_batch_ws(ct_table* t, const uint64_t* keys, const void* vals, int64_t n,
+                             uint8_t* status, void* ws, int64_t ws_bytes, void* stream) {
+  ct_status r = check_batch(t, keys, n, ws, ws_bytes);
   if (r != CT_OK) return r;
   if (n == 0) return CT_OK;
-  const int vk = t->desc.val_kind;
-  if (vk != CT_VAL_NONE && !vals) return CT_E_INVALID;
-  if (vk == CT_VAL_U32) return insert_chunks<1>(t, keys, vals, n, status, S(stream));
-  if (vk == CT_VAL_U64) return insert_chunks<2>(t, keys, vals, n, status, S(stream));
-  return insert_chunks<0>(t, keys, nullptr, n, status, S(stream));
+  if (t->desc.val_kind != CT_VAL_NONE && !vals) return CT_E_INVALID;
+  return insert_any(t, batch_scratch(t, n, ws, ws_bytes), keys, vals, n, status, S(stream));
+}
+
+ct_status ct_insert_batch(ct_table* t, const uint64_t* keys, const void* vals, int64_t n,
+                          uint8_t* status, void* stream) {
+  return ct_insert_batch_ws(t, keys, vals, n, status, nullptr, 0, stream);
+}
+
+ct_status ct_workspace_bytes(const ct_table* t, int64_t n, int64_t* bytes) {
+  if (!t || n < 0 || !bytes) return CT_E_INVALID;
+  Layout L;
+  const int64_t q = workspace_chunk(t, n);
+  *bytes = q && layout_scratch(&L, q, 0) ? L.total : 0;
+  return CT_OK;
 }
 
 ct_status ct_find_batch(ct_table* t, const uint64_t* keys, int64_t n, void* vals_out,
@@ -3333,12 +3396,18 @@ ct_status ct_find_batch(ct_table* t, const uint64_t* keys, int64_t n, void* vals
   return launched();
 }
 
-ct_status ct_erase_batch(ct_table* t, const uint64_t* keys, int64_t n, uint8_t* erased,
-                         void* stream) {
-  ct_status r = check_batch(t, keys, n);
+ct_status ct_erase_batch_ws(ct_table* t, const uint64_t* keys, int64_t n, uint8_t* erased, void* ws,
+                            int64_t ws_bytes, void* stream) {
+  ct_status r = check_batch(t, keys, n, ws, ws_bytes);
   if (r != CT_OK) return r;
   if (n == 0) return CT_OK;
-  return erase_chunks<false>(t, nullptr, keys, n, erased, S(stream));
+  return erase_chunks<false>(t, batch_scratch(t, n, ws, ws_bytes), nullptr, keys, n, erased,
+                             S(stream));
+}
+
+ct_status ct_erase_batch(ct_table* t, const uint64_t* keys, int64_t n, uint8_t* erased,
+                         void* stream) {
+  return ct_erase_batch_ws(t, keys, n, erased, nullptr, 0, stream);
 }
 
 ct_status ct_size(ct_table* t, int64_t* h_size, void* stream) {
@@ -3724,11 +3793,13 @@ namespace {
 // Pool-valued insert of n keys; with `skip`, only the elements whose byte there is zero take part,
 // in index order among themselves (masked batches are sparse: their repeated keys are resolved
 // through dd, whatever the chunk size).
-ct_status insert_alloc_chunks(ct_table* t, ct_pool* p, const uint64_t* keys, const uint8_t* skip,
-                              int64_t n, int32_t* vals_out, uint8_t* status, hipStream_t s) {
+ct_status insert_alloc_chunks(ct_table* t, const BatchScratch& B, ct_pool* p, const uint64_t* keys,
+                              const uint8_t* skip, int64_t n, int32_t* vals_out, uint8_t* status,
+                              hipStream_t s) {
+  const TableView& v = B.v;
   ct_status r = CT_OK;
-  for (int64_t c0 = 0; c0 < n; c0 += t->chunk) {
-    const int64_t q = std::min<int64_t>(t->chunk, n - c0);
+  for (int64_t c0 = 0; c0 < n; c0 += B.chunk) {
+    const int64_t q = std::min<int64_t>(B.chunk, n - c0);
     const uint32_t db = dedup_slots_for(q);
     const uint64_t* kc = keys + c0;
     const uint8_t* mc = skip ? skip + c0 : nullptr;
@@ -3737,16 +3808,16 @@ ct_status insert_alloc_chunks(ct_table* t, ct_pool* p, const uint64_t* keys, con
     const int gb = group_blocks((q + kSlots - 1) / kSlots);
     const int ntiles = (int)((q + kTile - 1) / kTile);
     if (mc) {
-      launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_prologue<<<flat_blocks(db / 2), kBlock, 0, s>>>(t->v, p->hdr, db, q); });
-      launch(t, CT_KERNEL_DEDUP, s, [&] { k_dedup<<<flat_blocks(q), kBlock, 0, s>>>(t->v, kc, mc, q, db - 1); });
+      launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_prologue<<<flat_blocks(db / 2), kBlock, 0, s>>>(v, p->hdr, db, q); });
+      launch(t, CT_KERNEL_DEDUP, s, [&] { k_dedup<<<flat_blocks(q), kBlock, 0, s>>>(v, kc, mc, q, db - 1); });
     } else {
-      dedup_chunk(t, t->v, p->hdr, kc, q, s);
+      dedup_chunk(t, v, p->hdr, kc, q, s);
     }
-    launch(t, CT_KERNEL_INSERT, s, [&] { k_insert<1, true><<<gb, kBlock, 0, s>>>(t->v, kc, nullptr, q, db - 1, sc, vc, mc); });
+    launch(t, CT_KERNEL_INSERT, s, [&] { k_insert<1, true><<<gb, kBlock, 0, s>>>(v, kc, nullptr, q, db - 1, sc, vc, mc); });
     const int inl = ntiles <= kInlineRankTiles ? ntiles : 0;
-    if (!inl) launch(t, CT_KERNEL_RANK, s, [&] { k_tile_scan<<<1, 1024, 0, s>>>(t->v, p->hdr, ntiles, 1); });
-    launch(t, CT_KERNEL_FINAL, s, [&] { k_final<1, 1><<<ntiles, kBlock, 0, s>>>(t->v, p->hdr, p->stack, kc, nullptr, q, sc, vc, inl); });
-    if (sc || vc) launch(t, CT_KERNEL_FIX, s, [&] { k_fix<<<flat_blocks((q + 3) / 4), kBlock, 0, s>>>(t->v, q, sc, vc); });
+    if (!inl) launch(t, CT_KERNEL_RANK, s, [&] { k_tile_scan<<<1, 1024, 0, s>>>(v, p->hdr, ntiles, 1); });
+    launch(t, CT_KERNEL_FINAL, s, [&] { k_final<1, 1><<<ntiles, kBlock, 0, s>>>(v, p->hdr, p->stack, kc, nullptr, q, sc, vc, inl); });
+    if (sc || vc) launch(t, CT_KERNEL_FIX, s, [&] { k_fix<<<flat_blocks((q + 3) / 4), kBlock, 0, s>>>(v, q, sc, vc); });
     t->size_ub = std::min<uint64_t>(t->size_ub + (uint64_t)q, (uint64_t)t->desc.capacity);
     r = launched();
     if (r != CT_OK) return r;
@@ -3758,32 +3829,41 @@ ct_status insert_alloc_chunks(ct_table* t, ct_pool* p, const uint64_t* keys, con
 
 extern "C" {
 
-ct_status ct_insert_alloc_batch(ct_table* t, ct_pool* p, const uint64_t* keys, int64_t n,
-                                int32_t* vals_out, uint8_t* status, void* stream) {
-  ct_status r = check_batch(t, keys, n);
+ct_status ct_insert_alloc_batch_ws(ct_table* t, ct_pool* p, const uint64_t* keys,
+                                   const uint8_t* skip, int64_t n, int32_t* vals_out,
+                                   uint8_t* status, void* ws, int64_t ws_bytes, void* stream) {
+  ct_status r = check_batch(t, keys, n, ws, ws_bytes);
   if (r != CT_OK || !p) return CT_E_INVALID;
   if (t->desc.val_kind != CT_VAL_U32) return CT_E_INVALID;
   if (n == 0) return CT_OK;
-  return insert_alloc_chunks(t, p, keys, nullptr, n, vals_out, status, S(stream));
+  return insert_alloc_chunks(t, batch_scratch(t, n, ws, ws_bytes), p, keys, skip, n, vals_out,
+                             status, S(stream));
+}
+
+ct_status ct_insert_alloc_batch(ct_table* t, ct_pool* p, const uint64_t* keys, int64_t n,
+                                int32_t* vals_out, uint8_t* status, void* stream) {
+  return ct_insert_alloc_batch_ws(t, p, keys, nullptr, n, vals_out, status, nullptr, 0, stream);
 }
 
 ct_status ct_insert_alloc_batch_masked(ct_table* t, ct_pool* p, const uint64_t* keys,
                                        const uint8_t* skip, int64_t n, int32_t* vals_out,
                                        uint8_t* status, void* stream) {
-  ct_status r = check_batch(t, keys, n);
-  if (r != CT_OK || !p || (n > 0 && !skip)) return CT_E_INVALID;
+  if (n > 0 && !skip) return CT_E_INVALID;
+  return ct_insert_alloc_batch_ws(t, p, keys, skip, n, vals_out, status, nullptr, 0, stream);
+}
+
+ct_status ct_erase_release_batch_ws(ct_table* t, ct_pool* p, const uint64_t* keys, int64_t n,
+                                    uint8_t* erased, void* ws, int64_t ws_bytes, void* stream) {
+  ct_status r = check_batch(t, keys, n, ws, ws_bytes);
+  if (r != CT_OK || !p) return CT_E_INVALID;
   if (t->desc.val_kind != CT_VAL_U32) return CT_E_INVALID;
   if (n == 0) return CT_OK;
-  return insert_alloc_chunks(t, p, keys, skip, n, vals_out, status, S(stream));
+  return erase_chunks<true>(t, batch_scratch(t, n, ws, ws_bytes), p, keys, n, erased, S(stream));
 }
 
 ct_status ct_erase_release_batch(ct_table* t, ct_pool* p, const uint64_t* keys, int64_t n,
                                  uint8_t* erased, void* stream) {
-  ct_status r = check_batch(t, keys, n);
-  if (r != CT_OK || !p) return CT_E_INVALID;
-  if (t->desc.val_kind != CT_VAL_U32) return CT_E_INVALID;
-  if (n == 0) return CT_OK;
-  return erase_chunks<true>(t, p, keys, n, erased, S(stream));
+  return ct_erase_release_batch_ws(t, p, keys, n, erased, nullptr, 0, stream);
 }
 
 }  // extern "C"
@@ -3853,11 +3933,9 @@ ct_status run_op(const PlanOp& o, hipStream_t s) {
       launch(t, CT_KERNEL_CLEAR, s, [&] { k_table_reset<<<flat_blocks((int64_t)t->v.nb * kSlots), kBlock, 0, s>>>(t->v, 0); });
       return launched();
     case kOpInsert:
-      if (vk == CT_VAL_U32) return insert_chunks<1>(t, o.keys, o.vals, o.n, o.flags, s);
-      if (vk == CT_VAL_U64) return insert_chunks<2>(t, o.keys, o.vals, o.n, o.flags, s);
-      return insert_chunks<0>(t, o.keys, nullptr, o.n, o.flags, s);
+      return insert_any(t, BatchScratch{t->v, t->chunk}, o.keys, o.vals, o.n, o.flags, s);
     case kOpErase:
-      return erase_chunks<false>(t, nullptr, o.keys, o.n, o.flags, s);
+      return erase_chunks<false>(t, BatchScratch{t->v, t->chunk}, nullptr, o.keys, o.n, o.flags, s);
     default: {
       const int gb = group_blocks((o.n + kSlots - 1) / kSlots);
       launch(t, CT_KERNEL_FIND, s, [&] {
@@ -4506,9 +4584,7 @@ ct_status ct_insert_batch_noalloc(ct_table* t, const uint64_t* keys, const void*
   w.bcur = nullptr;
   w.dfirst = nullptr;
   const int64_t chunk = std::min<int64_t>(t->chunk, kStaticChunk);
-  if (vk == CT_VAL_U32) return insert_chunks<1>(t, w, chunk, keys, vals, n, status, s);
-  if (vk == CT_VAL_U64) return insert_chunks<2>(t, w, chunk, keys, vals, n, status, s);
-  return insert_chunks<0>(t, w, chunk, keys, nullptr, n, status, s);
+  return insert_any(t, BatchScratch{w, chunk}, keys, vals, n, status, s);
 }
 
 }  // extern "C"

@@ -103,6 +103,11 @@ SIGNATURES = {
     "ct_insert_alloc_batch": (C.c_int, [_P, _P, _P, _I64, _P, _P, _P]),
     "ct_insert_alloc_batch_masked": (C.c_int, [_P, _P, _P, _P, _I64, _P, _P, _P]),
     "ct_erase_release_batch": (C.c_int, [_P, _P, _P, _I64, _P, _P]),
+    "ct_workspace_bytes": (C.c_int, [_P, _I64, _PI64]),
+    "ct_insert_batch_ws": (C.c_int, [_P, _P, _P, _I64, _P, _P, _I64, _P]),
+    "ct_erase_batch_ws": (C.c_int, [_P, _P, _I64, _P, _P, _I64, _P]),
+    "ct_insert_alloc_batch_ws": (C.c_int, [_P, _P, _P, _P, _I64, _P, _P, _P, _I64, _P]),
+    "ct_erase_release_batch_ws": (C.c_int, [_P, _P, _P, _I64, _P, _P, _I64, _P]),
     "ct_plan_create": (C.c_int, [C.POINTER(_P)]),
     "ct_plan_destroy": (C.c_int, [_P]),
     "ct_plan_add": (C.c_int, [_P, _P, _I32, _P, _P, _P, _P, _I64]),
@@ -300,6 +305,22 @@ class Table:
     def value_dtype(self):
         return _VAL_DTYPE.get(self.value_kind)
 
+    def _workspace(self, n: int):
+        """(workspace tensor or None, its bytes) for a batch of n keys.  It comes from torch's
+        allocator on the current stream, so a later tensor takes its memory only after this call's
+        kernels.  Without the memory, and while the stream is captured into a graph (which would
+        keep it), the batch runs in the table's own chunks."""
+        if n <= self.chunk or torch.cuda.is_current_stream_capturing():
+            return None, 0
+        nb = C.c_int64(0)
+        _check(lib().ct_workspace_bytes(self._h, n, C.byref(nb)), "ct_workspace_bytes")
+        if nb.value == 0:
+            return None, 0
+        try:
+            return torch.empty(nb.value, dtype=torch.uint8, device=self.device), nb.value
+        except torch.cuda.OutOfMemoryError:
+            return None, 0
+
     def insert(self, keys: torch.Tensor, vals: torch.Tensor | None = None, status: bool = True):
         n = keys.numel()
         _need(keys, torch.int64, None, "keys", self.device)
@@ -308,8 +329,10 @@ class Table:
                 raise CtError("values are required for a map")
             _need(vals, self.value_dtype, n, "vals", self.device)
         st = torch.empty(n, dtype=torch.uint8, device=self.device) if status else None
-        _check(lib().ct_insert_batch(self._h, _ptr(keys), _ptr(vals) if self.value_kind else None,
-                                     n, _ptr(st), _stream(self.device)), "ct_insert_batch")
+        ws, nb = self._workspace(n)
+        _check(lib().ct_insert_batch_ws(self._h, _ptr(keys), _ptr(vals) if self.value_kind else None,
+                                        n, _ptr(st), _ptr(ws), nb, _stream(self.device)),
+               "ct_insert_batch")
         return st
 
     def find(self, keys: torch.Tensor, values: bool = True, found: bool = True, out=None,
@@ -336,8 +359,9 @@ class Table:
         n = keys.numel()
         _need(keys, torch.int64, None, "keys", self.device)
         er = torch.empty(n, dtype=torch.uint8, device=self.device) if status else None
-        _check(lib().ct_erase_batch(self._h, _ptr(keys), n, _ptr(er), _stream(self.device)),
-               "ct_erase_batch")
+        ws, nb = self._workspace(n)
+        _check(lib().ct_erase_batch_ws(self._h, _ptr(keys), n, _ptr(er), _ptr(ws), nb,
+                                       _stream(self.device)), "ct_erase_batch")
         return er
 
     def insert_alloc(self, pool: Pool, keys: torch.Tensor):
@@ -345,8 +369,10 @@ class Table:
         _need(keys, torch.int64, None, "keys", self.device)
         out = torch.empty(n, dtype=torch.int32, device=self.device)
         st = torch.empty(n, dtype=torch.uint8, device=self.device)
-        _check(lib().ct_insert_alloc_batch(self._h, pool._h, _ptr(keys), n, _ptr(out), _ptr(st),
-                                           _stream(self.device)), "ct_insert_alloc_batch")
+        ws, nb = self._workspace(n)
+        _check(lib().ct_insert_alloc_batch_ws(self._h, pool._h, _ptr(keys), None, n, _ptr(out),
+                                              _ptr(st), _ptr(ws), nb, _stream(self.device)),
+               "ct_insert_alloc_batch")
         return out, st
 
     def insert_alloc_masked(self, pool: Pool, keys: torch.Tensor, skip: torch.Tensor,
@@ -360,8 +386,9 @@ class Table:
             out = torch.full((n,), -1, dtype=torch.int32, device=self.device)
         if status is None:
             status = torch.full((n,), 0xFF, dtype=torch.uint8, device=self.device)
-        _check(lib().ct_insert_alloc_batch_masked(self._h, pool._h, _ptr(keys), _ptr(skip), n,
-                                                  _ptr(out), _ptr(status), _stream(self.device)),
+        ws, nb = self._workspace(n)
+        _check(lib().ct_insert_alloc_batch_ws(self._h, pool._h, _ptr(keys), _ptr(skip), n, _ptr(out),
+                                              _ptr(status), _ptr(ws), nb, _stream(self.device)),
                "ct_insert_alloc_batch_masked")
         return out, status
 
@@ -369,8 +396,9 @@ class Table:
         n = keys.numel()
         _need(keys, torch.int64, None, "keys", self.device)
         er = torch.empty(n, dtype=torch.uint8, device=self.device)
-        _check(lib().ct_erase_release_batch(self._h, pool._h, _ptr(keys), n, _ptr(er),
-                                            _stream(self.device)), "ct_erase_release_batch")
+        ws, nb = self._workspace(n)
+        _check(lib().ct_erase_release_batch_ws(self._h, pool._h, _ptr(keys), n, _ptr(er), _ptr(ws),
+                                               nb, _stream(self.device)), "ct_erase_release_batch")
         return er
 
     def size(self) -> int:
