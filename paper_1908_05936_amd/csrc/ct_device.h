@@ -224,7 +224,6 @@ __device__ __forceinline__ int group_base() { return wave_lane() & ~7; }
 __device__ __forceinline__ uint32_t group_bits(uint64_t ballot) {
   return (uint32_t)(ballot >> group_base()) & 0xFFu;
 }
-__device__ __forceinline__ int lowest(uint32_t m) { return __builtin_ctz(m); }
 
 // ---------------------------------------------------------------------------------------------
 // atomics with explicit order and scope.  Claims are relaxed at agent scope: a claim only has to

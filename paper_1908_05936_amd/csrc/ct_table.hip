@@ -56,77 +56,6 @@ __device__ __forceinline__ uint64_t sentinel() {
   return VK == 1 ? 0xFFFFFFFFull : ~0ull;
 }
 
-// ---------------------------------------------------------------------------------------------
-// group-cooperative probes of the home table (8 lanes, converged within the group)
-// ---------------------------------------------------------------------------------------------
-struct Probe {
-  bool found;
-  bool had_empty;    // the bucket where the key was found holds a kEmpty slot
-  uint64_t val;
-  uint64_t pos;      // slot index b*8+c of the key when found
-  uint64_t free_b;   // first bucket with a free slot on the probe path (when !found)
-  bool has_free;
-};
-
-__device__ __forceinline__ Probe probe(const TableView& t, uint64_t key, int sub, bool want_free) {
-  Probe r;
-  r.found = false;
-  r.had_empty = false;
-  r.val = 0;
-  r.pos = kNoPos;
-  r.free_b = 0;
-  r.has_free = false;
-  const Seq q = probe_seq(t, key);
-  uint64_t b = q.home;
-  for (uint64_t step = 0; step < t.nb; ++step) {
-    const Slot s = t.bk[b].s[sub];
-    const uint32_t m = group_bits(__ballot(s.key == key));
-    const uint32_t e = group_bits(__ballot(s.key == kEmpty));
-    if (m) {
-      const int c = lowest(m);
-      r.found = true;
-      r.had_empty = e != 0;
-      r.val = __shfl(s.val, group_base() + c, 64);
-      r.pos = b * kSlots + (uint64_t)c;
-      return r;
-    }
-    if (want_free && !r.has_free) {
-      const uint32_t f = e | group_bits(__ballot(s.key == kTomb));
-      if (f) {
-        r.has_free = true;
-        r.free_b = b;
-      }
-    }
-    if (e) return r;
-    b = next_bucket(t, b, q.step);
-  }
-  return r;
-}
-
-// Claim a free slot for an absent `key`, scanning forward from bucket `b`.  Returns the slot
-// index, or kNoPos when every bucket was tried (only possible when the table is physically full).
-// A stale view can only show a slot as free when it is not: the CAS then fails and reports the
-// truth, so the scan always makes progress.
-__device__ __forceinline__ uint64_t claim(const TableView& t, uint64_t key, uint64_t b,
-                                          uint64_t stride, int sub) {
-  for (uint64_t step = 0; step < t.nb; ++step) {
-    const uint64_t cur = t.bk[b].s[sub].key;
-    uint32_t f = group_bits(__ballot(cur == kEmpty || cur == kTomb));
-    while (f) {
-      const int c = lowest(f);
-      int won = 0;
-      if (sub == c) {
-        uint64_t expected = cur;
-        won = cas64(&t.bk[b].s[c].key, expected, key) ? 1 : 0;
-      }
-      if (group_bits(__ballot(won))) return b * kSlots + (uint64_t)c;
-      f &= f - 1;
-    }
-    b = next_bucket(t, b, stride);
-  }
-  return kNoPos;
-}
-
 // Per lane: lowest chunk index of a key that k_dedup marked as repeated.  The entry is always
 // there; the scan is bounded anyway, and a miss makes the element act for itself and raises
 // kErrInternal.
@@ -1540,7 +1469,7 @@ __global__ __launch_bounds__(1024) void k_tile_scan(TableView t, PoolHeader* poo
 // MODE 2: erase releasing to the pool (pool element top0+rank = value)
 // (the batch moves only the back of the pool: head is fixed while it runs)
 template <int VK, int MODE>
-__device__ __forceinline__ void final_tile(const TableView& t, PoolHeader* pool,
+__device__ __forceinline__ void final_tile(const TableView& t, WaveLds* w, PoolHeader* pool,
                                            int32_t* __restrict__ pstack,
                                            const uint64_t* __restrict__ keys,
                                            const void* __restrict__ vals, int64_t q,
@@ -1591,63 +1520,50 @@ __device__ __forceinline__ void final_tile(const TableView& t, PoolHeader* pool,
   }
   const Header* h = t.hdr;
   const uint64_t room = t.cap - h->size0;
-  const int sub = threadIdx.x & 7;
-  // one lane per element where nothing is left to claim: a release, or new keys that hold their slot
-  // already (eight lanes per element took 20.5 us for the 26,214 releases of a voxel frame, now 5.4)
-  if (MODE == 2 || (MODE == 1 && fast)) {
-    const int64_t top0 = pool->top0, head = pool->head, pcap = pool->cap;
-    for (uint32_t j = threadIdx.x; j < total; j += kBlock) {
-      const int64_t i = t0 + list[j];
-      const int64_t rank = (int64_t)(rbase + j);
-      if constexpr (MODE == 2) {
-        const int64_t pos = top0 + rank;
-        if (pos < pcap) pstack[ring_pos(head, pcap, pos)] = (int32_t)(uint32_t)t.ref[i];
-      } else {  // fast: capacity and pool cover every new key of the chunk
-        const uint32_t v = (uint32_t)pstack[ring_pos(head, pcap, top0 - 1 - rank)];
-        const uint64_t pos = t.ref[i];
-        if (pos >= kSpecRef) t.hdr->spec_val[pos - kSpecRef] = v;
-        else t.bk[pos >> 3].s[pos & 7].val = v;
-        if (status) status[i] = kInserted;
-        if (vout) vout[i] = (int32_t)v;
-      }
-    }
-    return;
+  // One lane per element throughout.  Where nothing is left to claim (a release, or new keys that
+  // hold their slot already), the elements only move values: eight lanes per element took 20.5 us
+  // for the 26,214 releases of a voxel frame, now 5.4.  New keys that still need a slot are placed
+  // 64 at a time: 4 M repeated keys into a set took 127 us here with eight lanes per key, now 80.
+  const bool moves = MODE == 2 || (MODE == 1 && fast);
+  int64_t top0 = 0, head = 0, pcap = 0;
+  if (MODE != 0) {
+    top0 = pool->top0;
+    head = pool->head;
+    pcap = pool->cap;
   }
-  for (uint32_t j = threadIdx.x >> 3; j < total; j += kBlock / 8) {
-    const int64_t i = t0 + list[j];
+  const uint64_t lim = MODE == 1 && (uint64_t)top0 < room ? (uint64_t)top0 : room;
+  for (uint32_t j0 = threadIdx.x & ~63u; j0 < total; j0 += kBlock) {
+    const uint32_t j = j0 + (uint32_t)wave_lane();
+    const bool mine = j < total;
+    const int64_t i = t0 + (mine ? list[j] : list[0]);
     const uint64_t rank = rbase + j;
-    if constexpr (MODE != 2) {
-      uint64_t lim = room;
-      if constexpr (MODE == 1) {
-        const uint64_t avail = (uint64_t)pool->top0;
-        lim = room < avail ? room : avail;
-      }
-      if (rank >= lim) {
-        if (sub == 0) {
-          if (status) status[i] = kFull;
-          if (MODE == 1 && vout) vout[i] = -1;
-        }
-        continue;
-      }
-      const uint64_t key = keys[i];
+    if constexpr (MODE == 2) {
+      const int64_t pos = top0 + (int64_t)rank;
+      if (mine && pos < pcap) pstack[ring_pos(head, pcap, pos)] = (int32_t)(uint32_t)t.ref[i];
+    } else {
+      const bool stored = mine && rank < lim;
       uint64_t v = 0;
-      if constexpr (MODE == 1)
-        v = (uint64_t)(uint32_t)pstack[ring_pos(pool->head, pool->cap, pool->top0 - 1 - (int64_t)rank)];
-      else v = load_val<VK>(vals, i);
-      uint64_t pos;
-      if (key >= kTomb) {
-        pos = kSpecRef + (key - kTomb);
-        if (sub == 0) t.hdr->spec_live[key - kTomb] = 1;
+      if (stored) {
+        if constexpr (MODE == 1) v = (uint64_t)(uint32_t)pstack[ring_pos(head, pcap, top0 - 1 - (int64_t)rank)];
+        else v = load_val<VK>(vals, i);
+      }
+      uint64_t pos = kNoPos;
+      if (moves) {
+        if (stored) pos = t.ref[i];
       } else {
-        const Probe p = probe(t, key, sub, true);
-        pos = p.has_free ? claim(t, key, p.free_b, probe_seq(t, key).step, sub) : kNoPos;
+        const uint64_t key = keys[i];
+        const Place p = place_keys<true, false>(t, w, stored && key < kTomb, key, true, 0, 0);
+        pos = p.pos;
+        if (stored && key >= kTomb) {
+          pos = kSpecRef + (key - kTomb);
+          t.hdr->spec_live[key - kTomb] = 1;
+        }
       }
-      if (pos >= kSpecRef && pos != kNoPos) {
-        if (sub == 0) t.hdr->spec_val[pos - kSpecRef] = v;
-      } else if (pos != kNoPos) {
-        if (sub == (int)(pos & 7)) t.bk[pos >> 3].s[pos & 7].val = v;
+      if (stored && pos != kNoPos) {
+        if (pos >= kSpecRef) t.hdr->spec_val[pos - kSpecRef] = v;
+        else if (VK || MODE == 1) t.bk[pos >> 3].s[pos & 7].val = v;
       }
-      if (sub == 0) {
+      if (mine) {
         if (status) status[i] = pos == kNoPos ? kFull : kInserted;
         if (MODE == 1 && vout) vout[i] = pos == kNoPos ? -1 : (int32_t)(uint32_t)v;
       }
@@ -1663,7 +1579,7 @@ __global__ __launch_bounds__(kBlock) void k_final(TableView t, PoolHeader* pool,
                                                   const void* __restrict__ vals, int64_t q,
                                                   uint8_t* __restrict__ status,
                                                   int32_t* __restrict__ vout, int inline_tiles) {
-  final_tile<VK, MODE>(t, pool, pstack, keys, vals, q, status, vout, blockIdx.x, inline_tiles);
+  final_tile<VK, MODE>(t, MODE == 2 ? nullptr : wave_lds<kBlock>(), pool, pstack, keys, vals, q, status, vout, blockIdx.x, inline_tiles);
 }
 
 // Later copies of a key take the outcome of its first occurrence: PRESENT (or its value), unless
@@ -1672,20 +1588,34 @@ __global__ __launch_bounds__(kBlock) void k_final(TableView t, PoolHeader* pool,
 // cost the insert kernel one atomic on one address per wave, 12.6 ns each (a pool-valued insert of
 // 2^19 samples, each block met four times, took 131 us with such a list and takes 19 without; this
 // kernel went from 9 to 11).
+// A thread's four look-ups of a first copy are in flight together, and while the chunk cannot meet
+// FULL nothing reads the first copy's status.
 __device__ __forceinline__ void fix_range(const TableView& t, int64_t q, uint8_t* __restrict__ status,
                                           int32_t* __restrict__ vout, int64_t lo, int64_t step) {
   const int64_t units = (q + 3) / 4;
+  const bool fast = t.hdr->fast != 0;
   for (int64_t j = lo + threadIdx.x; j < units; j += step) {
     const uint32_t m = reinterpret_cast<const uint32_t*>(t.dmark)[j];
     if (!m) continue;
+    const uint4 d = reinterpret_cast<const uint4*>(t.dup)[j];
+    const uint32_t i = (uint32_t)(4 * j);
+    uint32_t f[4] = {d.x, d.y, d.z, d.w};
+    int32_t v[4] = {};
+    uint8_t st[4] = {};
+#pragma unroll
+    for (int k = 0; k < 4; ++k)  // the first copy, or this element where there is no other
+      if (!((m >> (8 * k)) & 0xFFu) || (int64_t)i + k >= q) f[k] = i;
+    if (vout)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = vout[f[k]];
+    if (status && !fast)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) st[k] = status[f[k]];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const int64_t i = 4 * j + k;
-      if (!((m >> (8 * k)) & 0xFFu) || i >= q) continue;
-      const uint32_t f = t.dup[i];
-      if (f == (uint32_t)i) continue;
-      if (vout) vout[i] = vout[f];
-      if (status) status[i] = status[f] == kFull ? kFull : kPresent;
+      if (!((m >> (8 * k)) & 0xFFu) || (int64_t)i + k >= q || f[k] == i + k) continue;
+      if (vout) vout[i + k] = v[k];
+      if (status) status[i + k] = st[k] == kFull ? kFull : kPresent;
     }
   }
 }
@@ -2622,11 +2552,11 @@ __device__ __forceinline__ void g_final_body(const GStep* __restrict__ st, const
   const TableView t = g.v;
   if (t.hdr->fast) return;   // nothing to rank: leave before any of the tile code
   if (g.vk == 1)
-    final_tile<1, 0>(t, nullptr, nullptr, g.keys, g.vals, g.q, g.flags, nullptr, L.lb, 0);
+    final_tile<1, 0>(t, wave_lds<kBlock>(), nullptr, nullptr, g.keys, g.vals, g.q, g.flags, nullptr, L.lb, 0);
   else if (g.vk == 2)
-    final_tile<2, 0>(t, nullptr, nullptr, g.keys, g.vals, g.q, g.flags, nullptr, L.lb, 0);
+    final_tile<2, 0>(t, wave_lds<kBlock>(), nullptr, nullptr, g.keys, g.vals, g.q, g.flags, nullptr, L.lb, 0);
   else
-    final_tile<0, 0>(t, nullptr, nullptr, g.keys, nullptr, g.q, g.flags, nullptr, L.lb, 0);
+    final_tile<0, 0>(t, wave_lds<kBlock>(), nullptr, nullptr, g.keys, nullptr, g.q, g.flags, nullptr, L.lb, 0);
 }
 
 // A byte range moved by the grouped plan's copy stages (operations merged into one step).
