@@ -327,7 +327,11 @@ __device__ __forceinline__ int64_t bin_prologue_units(const TableView& t, int64_
   return (q + 15) / 16 + ((int64_t)kCoarseCtrWords + ((int64_t)1 << t.lp)) / 4;
 }
 
-__global__ __launch_bounds__(kBlock) void k_bin_prologue(TableView t, PoolHeader* pool, int64_t q) {
+// The kernels of the path that resolves repeated keys first leave at once when the chunk went the
+// speculative way (decided on the device, k_spec_decide); `decided`: the flag is this chunk's.
+__global__ __launch_bounds__(kBlock) void k_bin_prologue(TableView t, PoolHeader* pool, int64_t q,
+                                                         int decided) {
+  if (decided && t.hdr->spec) return;
   if (pool) zero_tile_sums(t, q);
   const int64_t nm = (q + 15) / 16;
   const int64_t hi = bin_prologue_units(t, q);
@@ -410,6 +414,7 @@ constexpr int kFoldProbe = 32;
 
 __global__ __launch_bounds__(kBlock) void k_bin_scatter1(TableView t, const uint64_t* __restrict__ keys,
                                                          int64_t q) {
+  if (t.hdr->spec) return;
   constexpr int kPer = kBinTile / kBlock;
   constexpr uint32_t kFolded = ~0u - 1u;  // hs entry of a copy that stays out of the bins
   __shared__ BinStage S;
@@ -499,6 +504,7 @@ __global__ __launch_bounds__(kBlock) void k_bin_scatter1(TableView t, const uint
 // (tile r, r + blocks_per_seg, ...) and move each into the 2^(lp - lp1) fine bins of c, the same
 // way.
 __global__ __launch_bounds__(kBlock) void k_bin_scatter2(TableView t, int blocks_per_seg) {
+  if (t.hdr->spec) return;
   constexpr int kPer = kBinTile / kBlock;
   __shared__ BinStage S;
   const int g = (int)blockIdx.x / blocks_per_seg;
@@ -544,6 +550,7 @@ __global__ __launch_bounds__(kBlock) void k_bin_scatter2(TableView t, int blocks
 // A bin with more distinct keys (no probe finds a free or matching slot) flags an overflow, and
 // the chunk takes the exact fallback.
 __global__ __launch_bounds__(kBlock) void k_bin_dedup(TableView t) {
+  if (t.hdr->spec) return;
   __shared__ unsigned long long hk[kBinLds];
   __shared__ uint32_t hm[kBinLds];
   __shared__ uint8_t hx[kBinLds];
@@ -620,6 +627,7 @@ __global__ __launch_bounds__(kBlock) void k_bin_dedup(TableView t) {
 
 // Overflow path: clear dd (it aliases the coarse bins) and switch the chunk to dedup_range.
 __global__ __launch_bounds__(kBlock) void k_bin_fallback_clear(TableView t, uint32_t dslots) {
+  if (t.hdr->spec) return;
   if (!t.hdr->dovf) {
     // the bins held: a chunk scattered without folding ends the skew hint
     if (blockIdx.x == 0 && threadIdx.x == 0 && !t.hdr->dagg) t.hdr->dskew = 0;
@@ -639,7 +647,7 @@ __global__ __launch_bounds__(kBlock) void k_bin_fallback_clear(TableView t, uint
 __global__ __launch_bounds__(kBlock) void k_bin_fallback_dedup(TableView t,
                                                                const uint64_t* __restrict__ keys,
                                                                int64_t q, uint32_t dmask) {
-  if (!t.hdr->dovf) return;
+  if (!t.hdr->dovf || t.hdr->spec) return;
   dedup_range(t, keys, nullptr, dmask, (int64_t)blockIdx.x * kBlock, q, (int64_t)gridDim.x * kBlock);
 }
 
@@ -763,6 +771,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
                                                    uint32_t dmask, uint8_t* __restrict__ status,
                                                    int32_t* __restrict__ vout,
                                                    const uint8_t* __restrict__ skip) {
+  if (t.hdr->spec) return;
   const int64_t ins = insert_range<VK, ALLOC>(t, wave_lds<kBlock>(), keys, skip, vals, dmask, status, vout,
                                               (int64_t)blockIdx.x * kBlock, q,
                                               (int64_t)gridDim.x * kBlock);
@@ -903,9 +912,12 @@ __device__ __forceinline__ void chunk_feedback(const TableView& t, int word, int
 // fb_q > 0: the partials are the count changes of an insert (fb_word 0) or erase (fb_word 1)
 // chunk of fb_q keys: report how many keys the chunk stored or removed.
 __global__ __launch_bounds__(1024) void k_apply_count(TableView t, int nblocks, int64_t fb_q,
-                                                      int fb_word) {
+                                                      int fb_word, int decided) {
+  if (decided && t.hdr->spec) return;
   const int64_t s = apply_count_block(t, nblocks);
-  if (threadIdx.x == 0 && fb_q) chunk_feedback(t, fb_word, fb_q, fb_word ? -s : s);
+  // (an insert chunk that may meet capacity stores more keys in its ranked pass: no report)
+  if (threadIdx.x == 0 && fb_q && (fb_word || t.hdr->fast))
+    chunk_feedback(t, fb_word, fb_q, fb_word ? -s : s);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -992,6 +1004,7 @@ template <int VK>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_insert_spec(TableView t, const uint64_t* __restrict__ keys,
                                                         const void* __restrict__ vals, int64_t q,
                                                         uint8_t* __restrict__ status) {
+  if (!t.hdr->spec) return;
   const uint2 c = insert_spec_range<VK>(t, wave_lds<kBlock>(), keys, vals, status, (int64_t)blockIdx.x * kBlock, q,
                                         (int64_t)gridDim.x * kBlock);
   // both counts in one reduction: stored in the low half, listed in the high half
@@ -1047,9 +1060,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
   }
 }
 
-// The host's size bound has proved that the chunk cannot reach capacity; a live count that
-// says otherwise is a library bug and raises kErrInternal.  Also zeroes the listed counts.
-__global__ void k_spec_prologue(TableView t, int64_t q, int insert) {
+// The header of a speculative chunk, by the first wave of its first block: counters snapshot, listed
+// counts zeroed.
+__device__ __forceinline__ void spec_header(const TableView& t) {
   if (threadIdx.x < kListStripes) list_stripes(t)[threadIdx.x * kListStripeWords] = 0;
   if (threadIdx.x == 0) {
     Header* h = t.hdr;
@@ -1060,7 +1073,33 @@ __global__ void k_spec_prologue(TableView t, int64_t q, int insert) {
     h->fast = 1u;
     h->spec = 1u;
     h->dmode = 0u;
-    if (insert && h->size + (uint64_t)q > t.cap) h->err |= kErrInternal;
+  }
+}
+
+// The host's size bound has proved that the chunk cannot reach capacity; a live count that
+// says otherwise is a library bug and raises kErrInternal.
+__global__ void k_spec_prologue(TableView t, int64_t q, int insert) {
+  if (threadIdx.x == 0 && insert && t.hdr->size + (uint64_t)q > t.cap) t.hdr->err |= kErrInternal;
+  spec_header(t);
+}
+
+// Whether the table's last insert (word 0) or erase (word 1) chunk changed at least half its keys.
+__device__ __forceinline__ bool mostly_changed(const Header* h, int word) {
+  const uint64_t f = h->fbd[word];
+  const uint64_t fq = f >> 32, changed = f & 0xFFFFFFFFull;
+  return fq == 0 || 2 * changed >= fq;
+}
+
+// The host could not prove that a large insert chunk stays below capacity: decide from the live
+// count itself, and (unless `always`) from how the last chunk went.  One wave.
+__global__ __launch_bounds__(64) void k_spec_decide(TableView t, int64_t q, int always) {
+  const Header* h = t.hdr;
+  const bool spec = h->size + (uint64_t)q <= t.cap && (always || mostly_changed(h, 0));
+  if (spec) {
+    spec_header(t);
+  } else if (threadIdx.x == 0) {
+    t.hdr->spec = 0u;
+    t.hdr->ndup = 0;
   }
 }
 
@@ -1089,6 +1128,7 @@ __device__ __forceinline__ uint32_t* spec_low(const TableView& t, const SpecPlan
 // live count and the feedback word; the listed counts are summed into the header for the
 // kernels that follow.
 __global__ __launch_bounds__(1024) void k_spec_sum(TableView t, int nblocks, int64_t q, int erase) {
+  if (!t.hdr->spec) return;
   const int64_t change = apply_count_block(t, nblocks);
   if (threadIdx.x == 0) {
     chunk_feedback(t, erase, q, erase ? -change : change);
@@ -1622,6 +1662,7 @@ __device__ __forceinline__ void fix_range(const TableView& t, int64_t q, uint8_t
 
 __global__ __launch_bounds__(kBlock) void k_fix(TableView t, int64_t q, uint8_t* __restrict__ status,
                                                 int32_t* __restrict__ vout) {
+  if (t.hdr->spec) return;
   fix_range(t, q, status, vout, (int64_t)blockIdx.x * kBlock, (int64_t)gridDim.x * kBlock);
 }
 
@@ -2368,10 +2409,7 @@ __device__ __forceinline__ bool g_speculates(const GStep& g) {
   const Header* h = g.v.hdr;
   const bool ins = g.type == kOpInsert;
   if (ins && h->size + (uint64_t)g.q > g.v.cap) return false;   // FULL must be ranked
-  if (g.spath == 2) return true;
-  const uint64_t f = h->fbd[ins ? 0 : 1];
-  const uint64_t fq = f >> 32, changed = f & 0xFFFFFFFFull;
-  return fq == 0 || 2 * changed >= fq;
+  return g.spath == 2 || mostly_changed(h, ins ? 0 : 1);
 }
 
 // Prologue: a speculative step needs only its header snapshot and zeroed listed counts (the dd
@@ -2381,18 +2419,7 @@ __device__ __forceinline__ void g_prologue_body(const GStep* __restrict__ st, co
   const GStep& g = st[L.step];
   const TableView t = g.v;
   if (g_speculates(g)) {
-    if (L.lb != 0) return;
-    if (threadIdx.x < kListStripes) list_stripes(t)[threadIdx.x * kListStripeWords] = 0;
-    if (threadIdx.x == 0) {
-      Header* h = t.hdr;
-      h->size0 = h->size;
-      h->spec_first[0] = h->spec_first[1] = kNone;
-      h->ndup = 0;
-      h->nnew = 0;
-      h->fast = 1u;
-      h->spec = 1u;
-      h->dmode = 0u;
-    }
+    if (L.lb == 0) spec_header(t);
     return;
   }
   prologue_range(t, nullptr, g.db, g.q, (int64_t)L.lb * kBlock, prologue_units(g.db, g.q),
@@ -2993,13 +3020,13 @@ BatchScratch batch_scratch(const ct_table* t, int64_t n, void* ws, int64_t ws_by
 
 // Resolve the repeated keys of one chunk: binned for large chunks, dd otherwise.
 void dedup_chunk(ct_table* t, const TableView& v, PoolHeader* pool, const uint64_t* kc, int64_t q,
-                 hipStream_t s) {
+                 hipStream_t s, int decided = 0) {
   const uint32_t db = dedup_slots_for(q);
   if (v.r1k && q >= kBinMinChunk) {
     // blocks per coarse segment: enough for its expected fill (about c1 / 2) in one tile each
     const int blocks_per_seg = (int)std::max<int64_t>(1, (v.c1 / 2 + kBinTile - 1) / kBinTile);
     const int nfine = 1 << v.lp;
-    launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_bin_prologue<<<flat_blocks(bin_prologue_units_host(v, q)), kBlock, 0, s>>>(v, pool, q); });
+    launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_bin_prologue<<<flat_blocks(bin_prologue_units_host(v, q)), kBlock, 0, s>>>(v, pool, q, decided); });
     launch(t, CT_KERNEL_DEDUP, s, [&] { k_bin_scatter1<<<(int)((q + kBinTile - 1) / kBinTile), kBlock, 0, s>>>(v, kc, q); });
     launch(t, CT_KERNEL_DEDUP, s, [&] { k_bin_scatter2<<<kBinCoarse * kBinSub * blocks_per_seg, kBlock, 0, s>>>(v, blocks_per_seg); });
     launch(t, CT_KERNEL_DEDUP, s, [&] { k_bin_dedup<<<nfine, kBlock, 0, s>>>(v); });
@@ -3022,6 +3049,13 @@ bool use_speculation(const ct_table* t, int word) {
   const uint64_t fq = f >> 32, changed = f & 0xFFFFFFFFull;
   return fq == 0 || 2 * changed >= fq;
 }
+
+// A chunk of at least this many keys that the host cannot prove to stay below capacity enqueues both
+// paths and k_spec_decide picks one on the device: a program that enqueues rounds of erases and
+// inserts ahead of the device never gives the host a bound it can use.  The path not taken costs its
+// launches (about 30 us); the speculative path saves 230 us per 2^23 keys that are mostly new.
+// Batches of 2^21 keys would gain no more than those launches.
+constexpr int64_t kDeviceDecides = (int64_t)1 << 22;
 
 // The resolution kernels of a speculative chunk (after its insert or erase kernel).
 // The resolution kernels stride over their elements with at most kSpecGrid blocks: they read one
@@ -3055,20 +3089,27 @@ ct_status insert_chunks(ct_table* t, const BatchScratch& B, const uint64_t* keys
     const int ntiles = (int)((q + kTile - 1) / kTile);
     // the host bound proves that no element can meet FULL: the rank pass is not needed
     const bool surely_fast = t->size_ub + (uint64_t)q <= (uint64_t)t->desc.capacity;
+    t->size_ub = std::min<uint64_t>(t->size_ub + (uint64_t)q, (uint64_t)t->desc.capacity);
     if (surely_fast && use_speculation(t, 0)) {
       // speculative: insert first, then resolve the copies of keys listed as ambiguous
       launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_spec_prologue<<<1, 64, 0, s>>>(v, q, 1); });
       launch(t, CT_KERNEL_INSERT, s, [&] { k_insert_spec<VK><<<gb, kBlock, 0, s>>>(v, kc, vc, q, sc); });
       spec_resolve<VK, false>(t, v, kc, vc, q, sc, gb, db, s);
-      t->size_ub = std::min<uint64_t>(t->size_ub + (uint64_t)q, (uint64_t)t->desc.capacity);
       ct_status r = launched();
       if (r != CT_OK) return r;
       continue;
     }
-    dedup_chunk(t, v, nullptr, kc, q, s);
+    const int decided = !surely_fast && t->insert_path != CT_INSERT_RESOLVE_FIRST &&
+                        v.r1k && q >= kDeviceDecides;
+    if (decided) {  // the speculative kernels first; whichever path is not taken leaves at once
+      const int always = t->insert_path == CT_INSERT_SPECULATIVE;
+      launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_spec_decide<<<1, 64, 0, s>>>(v, q, always); });
+      launch(t, CT_KERNEL_INSERT, s, [&] { k_insert_spec<VK><<<gb, kBlock, 0, s>>>(v, kc, vc, q, sc); });
+      spec_resolve<VK, false>(t, v, kc, vc, q, sc, gb, db, s);
+    }
+    dedup_chunk(t, v, nullptr, kc, q, s, decided);
     launch(t, CT_KERNEL_INSERT, s, [&] { k_insert<VK, false><<<gb, kBlock, 0, s>>>(v, kc, vc, q, db - 1, sc, nullptr, nullptr); });
-    // a chunk that may meet capacity stores more keys in its ranked pass: no report
-    launch(t, CT_KERNEL_APPLY, s, [&] { k_apply_count<<<1, 1024, 0, s>>>(v, gb, surely_fast ? q : 0, 0); });
+    launch(t, CT_KERNEL_APPLY, s, [&] { k_apply_count<<<1, 1024, 0, s>>>(v, gb, q, 0, decided); });
     if (!surely_fast) {
       launch(t, CT_KERNEL_RANK, s, [&] { k_tile_count<<<ntiles, kBlock, 0, s>>>(v, q); });
       const int inl = ntiles <= kInlineRankTiles ? ntiles : 0;
@@ -3076,7 +3117,6 @@ ct_status insert_chunks(ct_table* t, const BatchScratch& B, const uint64_t* keys
       launch(t, CT_KERNEL_FINAL, s, [&] { k_final<VK, 0><<<ntiles, kBlock, 0, s>>>(v, nullptr, nullptr, kc, vc, q, sc, nullptr, inl); });
     }
     if (sc) launch(t, CT_KERNEL_FIX, s, [&] { k_fix<<<flat_blocks((q + 3) / 4), kBlock, 0, s>>>(v, q, sc, nullptr); });
-    t->size_ub = std::min<uint64_t>(t->size_ub + (uint64_t)q, (uint64_t)t->desc.capacity);
     ct_status r = launched();
     if (r != CT_OK) return r;
   }
@@ -3114,7 +3154,7 @@ ct_status erase_chunks(ct_table* t, const BatchScratch& B, ct_pool* p, const uin
     dedup_chunk(t, v, RELEASE ? p->hdr : nullptr, kc, q, s);
     launch(t, CT_KERNEL_ERASE, s, [&] { k_erase<RELEASE><<<gb, kBlock, 0, s>>>(v, kc, q, db - 1, ec); });
     if (!RELEASE) {
-      launch(t, CT_KERNEL_APPLY, s, [&] { k_apply_count<<<1, 1024, 0, s>>>(v, gb, q, 1); });
+      launch(t, CT_KERNEL_APPLY, s, [&] { k_apply_count<<<1, 1024, 0, s>>>(v, gb, q, 1, 0); });
     } else {
       const int inl = ntiles <= kInlineRankTiles ? ntiles : 0;
       if (!inl) launch(t, CT_KERNEL_RANK, s, [&] { k_tile_scan<<<1, 1024, 0, s>>>(v, p->hdr, ntiles, 2); });
@@ -3489,7 +3529,7 @@ ct_status ct_table_rehash(ct_table* src, ct_table* dst, void* stream) {
   const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(((int64_t)src->v.nb + kBlock / 8 - 1) / (kBlock / 8), kMaxGroupBlocks));
   hipStream_t s = S(stream);
   launch(dst, CT_KERNEL_INSERT, s, [&] { k_rehash<<<grid, kBlock, 0, s>>>(src->v, dst->v); });
-  launch(dst, CT_KERNEL_APPLY, s, [&] { k_apply_count<<<1, 1024, 0, s>>>(dst->v, grid, 0, 0); });
+  launch(dst, CT_KERNEL_APPLY, s, [&] { k_apply_count<<<1, 1024, 0, s>>>(dst->v, grid, 0, 0, 0); });
   dst->size_ub = (uint64_t)(nd + ns);
   return launched();
 }
@@ -3735,6 +3775,7 @@ ct_status insert_alloc_chunks(ct_table* t, const BatchScratch& B, ct_pool* p, co
     const uint8_t* mc = skip ? skip + c0 : nullptr;
     uint8_t* sc = status ? status + c0 : nullptr;
     int32_t* vc = vals_out ? vals_out + c0 : nullptr;
+    t->size_ub = std::min<uint64_t>(t->size_ub + (uint64_t)q, (uint64_t)t->desc.capacity);
     const int gb = group_blocks((q + kSlots - 1) / kSlots);
     const int ntiles = (int)((q + kTile - 1) / kTile);
     if (mc) {
@@ -3748,7 +3789,6 @@ ct_status insert_alloc_chunks(ct_table* t, const BatchScratch& B, ct_pool* p, co
     if (!inl) launch(t, CT_KERNEL_RANK, s, [&] { k_tile_scan<<<1, 1024, 0, s>>>(v, p->hdr, ntiles, 1); });
     launch(t, CT_KERNEL_FINAL, s, [&] { k_final<1, 1><<<ntiles, kBlock, 0, s>>>(v, p->hdr, p->stack, kc, nullptr, q, sc, vc, inl); });
     if (sc || vc) launch(t, CT_KERNEL_FIX, s, [&] { k_fix<<<flat_blocks((q + 3) / 4), kBlock, 0, s>>>(v, q, sc, vc); });
-    t->size_ub = std::min<uint64_t>(t->size_ub + (uint64_t)q, (uint64_t)t->desc.capacity);
     r = launched();
     if (r != CT_OK) return r;
   }
