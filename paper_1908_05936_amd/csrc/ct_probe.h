@@ -27,7 +27,7 @@ struct WaveLds {
 
 typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
 
-constexpr uint32_t kBitsMatch = 0xFFu;      // bits of probe_round's answer: slots holding the key
+constexpr uint32_t kBitsMatch = 0xFFu;      // bits of an answer: slots holding the key
 constexpr int kEmptyShift = 8;              //   slots holding kEmpty
 constexpr int kTombShift = 16;              //   slots holding kTomb (FREE rounds only)
 
@@ -52,8 +52,9 @@ __device__ __forceinline__ uint32_t transpose8(uint32_t x, int sub) {
   return x;
 }
 
-// NJ bucket reads of this lane's group: items j * 8 + g for j < NJ (items past the last re-read it).
-template <bool FREE, bool VAL, int NJ>
+// NJ bucket reads of this lane's group: items j * 8 + g for j < NJ (CLAMP: of n; past the last, it is
+// read again).
+template <bool FREE, bool VAL, int NJ, bool CLAMP>
 __device__ __forceinline__ uint32_t probe_lines(const Bucket* bk, WaveLds* w, uint32_t n, uint32_t g,
                                                 int sub) {
   u64x2 sl[NJ];  // .y is loaded only with VAL
@@ -61,7 +62,7 @@ __device__ __forceinline__ uint32_t probe_lines(const Bucket* bk, WaveLds* w, ui
   uint32_t r[NJ];
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
-    r[j] = NJ == 8 ? (uint32_t)j * 8u + g : min((uint32_t)j * 8u + g, n - 1u);
+    r[j] = CLAMP ? min((uint32_t)j * 8u + g, n - 1u) : (uint32_t)j * 8u + g;
     if (VAL) sl[j] = *reinterpret_cast<const u64x2*>(base + w->off[r[j]]);
     else sl[j].x = *reinterpret_cast<const uint64_t*>(base + w->off[r[j]]);
   }
@@ -81,46 +82,73 @@ __device__ __forceinline__ uint32_t probe_lines(const Bucket* bk, WaveLds* w, ui
   return x;
 }
 
-// One round: every lane with `look` set has its bucket `b` compared with `key`.  Returns the slot
-// bits (kBitsMatch, kEmptyShift, kTombShift) of its bucket, and with VAL the matching slot's value
-// in *val.  Called by all 64 lanes of the wave together; `mask` is the ballot of `look`, not zero.
-template <bool FREE, bool VAL>
-__device__ __forceinline__ uint32_t probe_round(const TableView& t, WaveLds* w, uint64_t mask, bool look,
-                                                uint64_t key, uint32_t b, uint64_t* val) {
-  const int lane = wave_lane();
-  const int sub = lane & 7;
-  const uint32_t g = (uint32_t)lane >> 3;
-  const uint32_t n = (uint32_t)__builtin_popcountll(mask);
-  // more than half the lanes look: item = lane, in an order that leaves each answer on its owner
-  // after the transpose; otherwise the looking lanes are packed
-  const bool packed = n <= 32;
-  const uint32_t rank = packed ? __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                                           __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0))
-                               : (uint32_t)sub * 8u + g;
-  __builtin_amdgcn_wave_barrier();  // the items of the round before have been read
-  if (look || !packed) {
-    w->off[rank] = (uint64_t)b * sizeof(Bucket);
-    w->key[rank] = key;
-  }
-  __builtin_amdgcn_wave_barrier();
-  uint32_t x;
-  if (n > 32) x = probe_lines<FREE, VAL, 8>(t.bk, w, n, g, sub);
-  else if (n > 16) x = probe_lines<FREE, VAL, 4>(t.bk, w, n, g, sub);
-  else if (n > 8) x = probe_lines<FREE, VAL, 2>(t.bk, w, n, g, sub);
-  else x = probe_lines<FREE, VAL, 1>(t.bk, w, n, g, sub);
-  __builtin_amdgcn_wave_barrier();
-  x = transpose8(x, sub);             // lane (g, s) now answers item s * 8 + g
-  if (packed) x = (uint32_t)__shfl((int)x, (int)(((rank & 7u) << 3) | (rank >> 3)), 64);
-  if (VAL) *val = w->val[rank];
-  return x;
-}
-
 // Bucket after b on a key's probe path.  Both terms are below 2^31.
 __device__ __forceinline__ uint32_t next_bucket32(const TableView& t, uint32_t b, uint32_t step) {
   const uint32_t nb = (uint32_t)t.nb;
   const uint32_t nx = b + step;
   return nx >= nb ? nx - nb : nx;
 }
+
+// One round of the lanes with `look` set.  Called by all 64 lanes of the wave together; `mask` is the
+// ballot of `look`, not zero.  Each looking lane gets the answers of `steps` buckets of its path, from
+// `b` on; answer(s) are the slot bits (kBitsMatch, kEmptyShift, kTombShift) of the s-th.
+//
+// AHEAD (batches too small to fill the chip, which wait for memory one bucket after another): when
+// half the lanes or fewer look, the round's 64 bucket reads go to the next 2, 4 or 8 buckets of
+// each.  Otherwise a lane reads one bucket and the looking lanes are packed, so that no line is
+// read in vain.
+template <bool FREE, bool VAL, bool AHEAD>
+struct ProbeRound {
+  WaveLds* w;
+  uint32_t x, rank, shift;  // packed answers, this lane's rank, log2 of steps
+  bool packed;
+
+  __device__ __forceinline__ ProbeRound(const TableView& t, WaveLds* lds, uint64_t mask, bool look,
+                                        uint64_t key, uint32_t b, uint32_t step)
+      : w(lds), shift(0) {
+    const int lane = wave_lane();
+    const int sub = lane & 7;
+    const uint32_t g = (uint32_t)lane >> 3;
+    const uint32_t n = (uint32_t)__builtin_popcountll(mask);
+    // more than half the lanes look: item = lane, in an order that leaves each answer on its owner
+    // after the transpose
+    packed = n <= 32;
+    rank = packed ? __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                              __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0))
+                  : (uint32_t)sub * 8u + g;
+    if (AHEAD) shift = n > 32 ? 0u : n > 16 ? 1u : n > 8 ? 2u : 3u;
+    __builtin_amdgcn_wave_barrier();  // the items of the round before have been read
+    if (look || !packed) {
+      uint32_t nx = b;
+      for (uint32_t s = 0; s < (1u << shift); ++s) {
+        const uint32_t at = (rank << shift) + s;
+        w->off[at] = (uint64_t)nx * sizeof(Bucket);
+        w->key[at] = key;
+        if (AHEAD) nx = next_bucket32(t, nx, step);
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t items = packed ? n << shift : 64u;
+    if (AHEAD) x = items > 32 ? probe_lines<FREE, VAL, 8, true>(t.bk, w, items, g, sub)
+                                         : probe_lines<FREE, VAL, 4, true>(t.bk, w, items, g, sub);
+    else if (n > 32) x = probe_lines<FREE, VAL, 8, false>(t.bk, w, n, g, sub);
+    else if (n > 16) x = probe_lines<FREE, VAL, 4, true>(t.bk, w, n, g, sub);
+    else if (n > 8) x = probe_lines<FREE, VAL, 2, true>(t.bk, w, n, g, sub);
+    else x = probe_lines<FREE, VAL, 1, true>(t.bk, w, n, g, sub);
+    __builtin_amdgcn_wave_barrier();
+    x = transpose8(x, sub);  // lane (g, s) now answers item s * 8 + g
+  }
+
+  __device__ __forceinline__ uint32_t steps() const { return 1u << shift; }
+
+  // All 64 lanes call it together.
+  __device__ __forceinline__ uint32_t answer(uint32_t s, uint64_t* val) const {
+    const uint32_t at = (rank << shift) + s;
+    if (VAL) *val = w->val[at & 63u];
+    if (!packed) return x;
+    return (uint32_t)__shfl((int)x, (int)(((at & 7u) << 3) | ((at >> 3) & 7u)), 64);
+  }
+};
 
 // The WaveLds of this thread's wave in a block of BS threads (one array per kernel).
 template <int BS>
@@ -151,7 +179,7 @@ struct Place {
   uint64_t val;    // value beside the key found (VAL)
 };
 
-template <bool CLAIM, bool VAL>
+template <bool CLAIM, bool VAL, bool AHEAD>
 __device__ __forceinline__ Place place_keys(const TableView& t, WaveLds* w, bool look, uint64_t key,
                                             bool claim, uint32_t inject, uint64_t id) {
   Place r = {false, false, kNoPos, 0};
@@ -163,40 +191,47 @@ __device__ __forceinline__ Place place_keys(const TableView& t, WaveLds* w, bool
   uint32_t xb = kNone, xmask = 0;           // slots of one bucket that were lost to other keys
   bool forced = CLAIM && inject && id % inject == 0;  // test hook: the first claim counts as lost
   for (uint64_t mask = __ballot(look); mask; mask = __ballot(look)) {
-    uint64_t val = 0;
-    const uint32_t x = probe_round<CLAIM, VAL>(t, w, mask, look, key, b, &val);
-    if (!look) continue;
-    if (x & kBitsMatch) {
-      r.found = true;
-      r.had_empty = ((x >> kEmptyShift) & 0xFFu) != 0;
-      r.pos = (uint64_t)b * kSlots + (uint64_t)__builtin_ctz(x & kBitsMatch);
-      if (VAL) r.val = val;
-      look = false;
-      continue;
-    }
-    uint32_t e = (x >> kEmptyShift) & 0xFFu;
-    if constexpr (CLAIM) {
-      uint32_t tb = (x >> kTombShift) & 0xFFu;
-      if (b == xb) {
-        e &= ~xmask;
-        tb &= ~xmask;
+    const ProbeRound<CLAIM, VAL, AHEAD> round(t, w, mask, look, key, b, step);
+    bool claiming = false;
+    bool here = look;       // still on the buckets of this round
+    const uint32_t steps = AHEAD ? round.steps() : 1u;
+    for (uint32_t s = 0; s < steps; ++s) {
+      uint64_t val = 0;
+      const uint32_t x = round.answer(s, &val);
+      if (!here) continue;
+      if (x & kBitsMatch) {
+        r.found = true;
+        r.had_empty = ((x >> kEmptyShift) & 0xFFu) != 0;
+        r.pos = (uint64_t)b * kSlots + (uint64_t)__builtin_ctz(x & kBitsMatch);
+        if (VAL) r.val = val;
+        look = here = false;
+        continue;
       }
-      if (fb == kNone && (e | tb)) {
-        fb = b;
-        fleft = left;
-        ftomb = tb != 0;
-        const uint32_t f = (ftomb ? tb : e) * 0x101u;
-        const uint32_t rot = (step >> 1) & 7u;
-        fc = ((uint32_t)__builtin_ctz(f >> rot) + rot) & 7u;
+      uint32_t e = (x >> kEmptyShift) & 0xFFu;
+      if constexpr (CLAIM) {
+        uint32_t tb = (x >> kTombShift) & 0xFFu;
+        if (b == xb) {
+          e &= ~xmask;
+          tb &= ~xmask;
+        }
+        if (fb == kNone && (e | tb)) {
+          fb = b;
+          fleft = left;
+          ftomb = tb != 0;
+          const uint32_t f = (ftomb ? tb : e) * 0x101u;
+          const uint32_t rot = (step >> 1) & 7u;
+          fc = ((uint32_t)__builtin_ctz(f >> rot) + rot) & 7u;
+        }
       }
+      if (!e && --left != 0) {
+        b = next_bucket32(t, b, step);
+        continue;
+      }
+      look = here = false;
+      claiming = CLAIM && claim && fb != kNone;
     }
-    if (!e && --left != 0) {
-      b = next_bucket32(t, b, step);
-      continue;
-    }
-    look = false;
     if constexpr (CLAIM) {
-      if (!claim || fb == kNone) continue;
+      if (!claiming) continue;
       uint64_t expected = ftomb ? kTomb : kEmpty;
       uint64_t* kw = &t.bk[fb].s[fc].key;
       if (!forced && cas64(kw, expected, key)) {

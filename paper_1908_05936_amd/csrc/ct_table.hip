@@ -671,7 +671,7 @@ __device__ __forceinline__ uint32_t first_copy(const TableView& t, const uint64_
 // completion.  Elements [lo, hi) of a chunk, 64 per wave, the block's waves striding by `step`.
 // `skip` (nullable): elements with a nonzero byte there take no part and keep their outputs.
 // Returns this thread's count of stored keys.
-template <int VK, bool ALLOC>
+template <int VK, bool ALLOC, bool AHEAD>
 __device__ __forceinline__ int64_t insert_range(const TableView& t, WaveLds* w,
                                                 const uint64_t* __restrict__ keys,
                                                 const uint8_t* __restrict__ skip,
@@ -721,7 +721,7 @@ __device__ __forceinline__ int64_t insert_range(const TableView& t, WaveLds* w,
       }
     }
     const bool look = actor && key < kTomb;
-    const Place p = place_keys<true, ALLOC>(t, w, look, key, fast, inject, (uint64_t)i);
+    const Place p = place_keys<true, ALLOC, AHEAD>(t, w, look, key, fast, inject, (uint64_t)i);
     if (look) {
       if (p.found) {
         st = kPresent;
@@ -765,14 +765,14 @@ __device__ __forceinline__ void count_flags(const TableView& t, int64_t q) {
 // takes 98 to 109 VGPRs, 4 waves.  Of the large-table churn (2^24 keys erased and inserted again,
 // load 0.8) one round took 2.75 ms at 5 waves, 2.83 at 4, 2.78 at 6 and 2.98 at 7, which spill; with
 // eight keys per 8-lane group and claims retried one key at a time it took 2.89 ms.
-template <int VK, bool ALLOC>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_insert(TableView t, const uint64_t* __restrict__ keys,
+template <int VK, bool ALLOC, bool AHEAD>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(AHEAD ? 1 : 5))) void k_insert(TableView t, const uint64_t* __restrict__ keys,
                                                    const void* __restrict__ vals, int64_t q,
                                                    uint32_t dmask, uint8_t* __restrict__ status,
                                                    int32_t* __restrict__ vout,
                                                    const uint8_t* __restrict__ skip) {
   if (t.hdr->spec) return;
-  const int64_t ins = insert_range<VK, ALLOC>(t, wave_lds<kBlock>(), keys, skip, vals, dmask, status, vout,
+  const int64_t ins = insert_range<VK, ALLOC, AHEAD>(t, wave_lds<kBlock>(), keys, skip, vals, dmask, status, vout,
                                               (int64_t)blockIdx.x * kBlock, q,
                                               (int64_t)gridDim.x * kBlock);
   // one partial per block, summed by k_apply_count: no same-address atomics across the grid
@@ -798,7 +798,7 @@ __global__ __launch_bounds__(kBlock) void k_rehash(TableView src, TableView dst)
     sl.val = 0;
     if (j < nslots) sl = src.bk[j >> 3].s[j & 7];
     const bool live = sl.key < kTomb;
-    const Place p = place_keys<true, false>(dst, wave_lds<kBlock>(), live, sl.key, true, inject,
+    const Place p = place_keys<true, false, false>(dst, wave_lds<kBlock>(), live, sl.key, true, inject,
                                             (uint64_t)j);
     if (live && !p.found) {
       if (p.pos != kNoPos) {
@@ -823,7 +823,7 @@ __global__ __launch_bounds__(kBlock) void k_rehash(TableView src, TableView dst)
 }
 
 // Erase actors, one element per lane.  RELEASE: the removed value is kept for the ordered push.
-template <bool RELEASE>
+template <bool RELEASE, bool AHEAD>
 __device__ __forceinline__ int64_t erase_range(const TableView& t, WaveLds* w,
                                                const uint64_t* __restrict__ keys, uint32_t dmask,
                                                uint8_t* __restrict__ erased, int64_t lo, int64_t hi,
@@ -846,7 +846,7 @@ __device__ __forceinline__ int64_t erase_range(const TableView& t, WaveLds* w,
         hit = 1;
       }
     }
-    const Place p = place_keys<false, RELEASE>(t, w, actor && key < kTomb, key, false, 0, 0);
+    const Place p = place_keys<false, RELEASE, AHEAD>(t, w, actor && key < kTomb, key, false, 0, 0);
     if (p.found) {
       // kEmpty only where the bucket already holds one: no probe sequence runs through it
       t.bk[p.pos >> 3].s[p.pos & 7].key = p.had_empty ? kEmpty : kTomb;
@@ -865,11 +865,11 @@ __device__ __forceinline__ int64_t erase_range(const TableView& t, WaveLds* w,
   return del;
 }
 
-template <bool RELEASE>
+template <bool RELEASE, bool AHEAD>
 __global__ __launch_bounds__(kBlock) void k_erase(TableView t, const uint64_t* __restrict__ keys,
                                                   int64_t q, uint32_t dmask,
                                                   uint8_t* __restrict__ erased) {
-  const int64_t del = erase_range<RELEASE>(t, wave_lds<kBlock>(), keys, dmask, erased, (int64_t)blockIdx.x * kBlock, q,
+  const int64_t del = erase_range<RELEASE, AHEAD>(t, wave_lds<kBlock>(), keys, dmask, erased, (int64_t)blockIdx.x * kBlock, q,
                                            (int64_t)gridDim.x * kBlock);
   if (RELEASE) {  // the removals are the rank flags: their total settles the live count
     count_flags(t, q);
@@ -960,7 +960,7 @@ __device__ __forceinline__ uint32_t listed_total(const TableView& t) {
 }
 
 // Elements [lo, hi) of a chunk, 64 per wave.  Returns this thread's (stored, listed) counts.
-template <int VK>
+template <int VK, bool AHEAD>
 __device__ __forceinline__ uint2 insert_spec_range(const TableView& t, WaveLds* w,
                                                    const uint64_t* __restrict__ keys,
                                                    const void* __restrict__ vals,
@@ -977,7 +977,7 @@ __device__ __forceinline__ uint2 insert_spec_range(const TableView& t, WaveLds* 
     uint8_t st = kPresent;
     uint8_t claimed = 0;
     const bool look = valid && key < kTomb;
-    const Place p = place_keys<true, false>(t, w, look, key, true, inject, (uint64_t)i);
+    const Place p = place_keys<true, false, AHEAD>(t, w, look, key, true, inject, (uint64_t)i);
     if (look) {
       if (p.found) {
         amb = true;
@@ -1000,12 +1000,12 @@ __device__ __forceinline__ uint2 insert_spec_range(const TableView& t, WaveLds* 
   return make_uint2(ins, listed);
 }
 
-template <int VK>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_insert_spec(TableView t, const uint64_t* __restrict__ keys,
+template <int VK, bool AHEAD>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(AHEAD ? 1 : 5))) void k_insert_spec(TableView t, const uint64_t* __restrict__ keys,
                                                         const void* __restrict__ vals, int64_t q,
                                                         uint8_t* __restrict__ status) {
   if (!t.hdr->spec) return;
-  const uint2 c = insert_spec_range<VK>(t, wave_lds<kBlock>(), keys, vals, status, (int64_t)blockIdx.x * kBlock, q,
+  const uint2 c = insert_spec_range<VK, AHEAD>(t, wave_lds<kBlock>(), keys, vals, status, (int64_t)blockIdx.x * kBlock, q,
                                         (int64_t)gridDim.x * kBlock);
   // both counts in one reduction: stored in the low half, listed in the high half
   const int64_t tot = block_sum((int64_t)c.x + ((int64_t)c.y << 32));
@@ -1023,6 +1023,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
 // afterwards the lowest listed copy takes the removal over from a higher remover.  A copy cannot
 // miss a key that is still there: an erase writes kEmpty only into buckets that already hold one,
 // so no probe sequence is cut short.  Out-of-band keys are always listed.
+template <bool AHEAD>
 __device__ __forceinline__ uint2 erase_spec_range(const TableView& t, WaveLds* w,
                                                   const uint64_t* __restrict__ keys,
                                                   uint8_t* __restrict__ erased, int64_t lo,
@@ -1032,7 +1033,7 @@ __device__ __forceinline__ uint2 erase_spec_range(const TableView& t, WaveLds* w
     const int64_t i = w0 + wave_lane();
     const bool valid = i < hi;
     const uint64_t key = keys[min(i, hi - 1)];
-    const Place p = place_keys<false, false>(t, w, valid && key < kTomb, key, false, 0, 0);
+    const Place p = place_keys<false, false, AHEAD>(t, w, valid && key < kTomb, key, false, 0, 0);
     uint8_t hit = 0;
     if (p.found) {
       uint64_t expected = key;
@@ -1048,9 +1049,10 @@ __device__ __forceinline__ uint2 erase_spec_range(const TableView& t, WaveLds* w
   return make_uint2(del, listed);
 }
 
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_erase_spec(TableView t, const uint64_t* __restrict__ keys,
+template <bool AHEAD>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(AHEAD ? 1 : 5))) void k_erase_spec(TableView t, const uint64_t* __restrict__ keys,
                                                        int64_t q, uint8_t* __restrict__ erased) {
-  const uint2 c = erase_spec_range(t, wave_lds<kBlock>(), keys, erased, (int64_t)blockIdx.x * kBlock, q,
+  const uint2 c = erase_spec_range<AHEAD>(t, wave_lds<kBlock>(), keys, erased, (int64_t)blockIdx.x * kBlock, q,
                                    (int64_t)gridDim.x * kBlock);
   const int64_t tot = block_sum((int64_t)c.x + ((int64_t)c.y << 32));
   if (threadIdx.x == 0) {
@@ -1592,7 +1594,7 @@ __device__ __forceinline__ void final_tile(const TableView& t, WaveLds* w, PoolH
         if (stored) pos = t.ref[i];
       } else {
         const uint64_t key = keys[i];
-        const Place p = place_keys<true, false>(t, w, stored && key < kTomb, key, true, 0, 0);
+        const Place p = place_keys<true, false, false>(t, w, stored && key < kTomb, key, true, 0, 0);
         pos = p.pos;
         if (stored && key >= kTomb) {
           pos = kSpecRef + (key - kTomb);
@@ -1666,6 +1668,223 @@ __global__ __launch_bounds__(kBlock) void k_fix(TableView t, int64_t q, uint8_t*
   fix_range(t, q, status, vout, (int64_t)blockIdx.x * kBlock, (int64_t)gridDim.x * kBlock);
 }
 
+// ---------------------------------------------------------------------------------------------
+// Small batches: the whole operation in one launch of one workgroup.
+//
+// What bounds a batch of some hundred keys is launches, not work: the pipelines above take 5 to 8
+// of them, 3 to 4 us each.  Here one workgroup finds the repeated keys in LDS, places the first
+// copies, ranks the new ones in index order where capacity or a pool asks for it, gives the later
+// copies their outcome, and settles the counters.  kSmallPer elements per thread, element
+// e * blockDim + tid, so index order is (e, wave, lane).
+// ---------------------------------------------------------------------------------------------
+enum SmallOp : int { sInsert, sAlloc, sErase, sRelease };
+constexpr int kSmallPer = 2;
+constexpr int kSmallMax = 1024 * kSmallPer;
+
+// hslots: a power of two >= 2 n (repeated-key table, load at most one half).
+// The loops over a thread's elements stay rolled, with the elements' state in LDS, and both placing
+// passes share one copy of place_keys: such a launch runs its code once, so instruction fetch is
+// part of its time.  500 keys erased, inserted and partly looked up: 62 us as 15 launches, 28 as 3,
+// of which the inserts' kernel is 16.7 us and the erases' 9 (22 and 9.6 without reading ahead).
+template <int VK, int OP>
+__global__ __launch_bounds__(1024) void k_small(TableView t, PoolHeader* pool,
+                                                int32_t* __restrict__ pstack,
+                                                const uint64_t* __restrict__ keys,
+                                                const uint8_t* __restrict__ skip,
+                                                const void* __restrict__ vals, int32_t n,
+                                                uint32_t hslots, uint8_t* __restrict__ status,
+                                                int32_t* __restrict__ vout) {
+  constexpr bool kIns = OP == sInsert || OP == sAlloc;
+  constexpr bool kPool = OP == sAlloc || OP == sRelease;
+  __shared__ uint64_t lk[kSmallMax];       // by index: key
+  __shared__ uint64_t rf[kSmallMax];       //   slot of a new key, value released, value allocated
+  __shared__ uint32_t H[2 * kSmallMax];    // repeated-key table: lowest index of the slot's key
+  __shared__ uint16_t fst[kSmallMax];      //   H slot of the key, then index of its first copy
+  __shared__ uint16_t rk[kSmallMax];       //   rank among the flagged
+  __shared__ uint8_t ost[kSmallMax];       //   outcome
+  __shared__ uint8_t flg[kSmallMax];       //   takes part in the ranking
+  __shared__ uint32_t sfirst[2], flagged[kSmallPer][16], changed_sum;
+  constexpr uint16_t kSkipped = 0xFFFF;
+  WaveLds* w = wave_lds<1024>();
+  Header* hdr = t.hdr;
+  const int bd = (int)blockDim.x, tid = (int)threadIdx.x, wave = tid >> 6;
+  const uint64_t size0 = hdr->size;
+  const uint64_t room = t.cap - size0;
+  const uint32_t inject = kIns ? hdr->inject : 0u;
+  int64_t top0 = 0, head = 0, pcap = 0;
+  if (kPool) {
+    top0 = pool->top;
+    head = pool->head;
+    pcap = pool->cap;
+  }
+  // no element can meet FULL: a new key claims its slot at once
+  const bool fast = size0 + (uint64_t)n <= t.cap && (OP != sAlloc || top0 >= n);
+  const uint64_t lim = OP == sAlloc && (uint64_t)top0 < room ? (uint64_t)top0 : room;
+
+  for (uint32_t j = tid; j < hslots; j += bd) H[j] = kNone;
+  if (tid < 2) sfirst[tid] = kNone;
+  if (tid == 2) changed_sum = 0;
+#pragma unroll 1
+  for (int i = tid; i < n; i += bd) lk[i] = keys[i];
+  __syncthreads();
+#pragma unroll 1
+  for (int i = tid; i < n; i += bd) {
+    const uint64_t key = lk[i];
+    uint32_t s = 0;
+    if (skip && skip[i]) {
+      s = kSkipped;
+    } else if (key >= kTomb) {
+      atomicMin(&sfirst[key - kTomb], (uint32_t)i);
+    } else {
+      s = (uint32_t)dedup_mix(key) & (hslots - 1);
+      for (;;) {  // at most n keys in 2 n slots: a free or matching slot exists
+        const uint32_t prev = atomicCAS(&H[s], kNone, (uint32_t)i);
+        if (prev == kNone) break;
+        if (lk[prev] == key) {
+          atomicMin(&H[s], (uint32_t)i);
+          break;
+        }
+        s = (s + 1) & (hslots - 1);
+      }
+    }
+    fst[i] = (uint16_t)s;
+  }
+  __syncthreads();
+
+  uint32_t changed = 0, nnew = 0;
+  const bool ranked = kPool || !fast;
+  // pass 0: probe the first copies (and claim, while FULL is out of the question); pass 1, for
+  // inserts that may meet FULL: the first `lim` new keys in index order claim
+  const int passes = kIns && !fast ? 2 : 1;
+#pragma unroll 1
+  for (int pass = 0; pass < passes; ++pass) {
+#pragma unroll 1
+    for (int e = 0; e * bd < n; ++e) {
+      const int i = e * bd + tid;
+      const uint64_t key = i < n ? lk[i] : 0;
+      const bool special = key >= kTomb;
+      bool mine = false;
+      if (i < n) {
+        if (pass == 0) {
+          const uint32_t s = fst[i];
+          const uint32_t first = s == kSkipped ? (uint32_t)kSkipped
+                                 : special ? sfirst[key - kTomb] : H[s];
+          fst[i] = (uint16_t)first;
+          mine = first == (uint32_t)i;
+        } else {
+          mine = flg[i] && rk[i] < lim;
+        }
+      }
+      const Place p = place_keys<kIns, kPool, true>(t, w, mine && !special, key, kIns && (fast || pass),
+                                                    pass ? 0 : inject, (uint64_t)i);
+      bool found = p.found;
+      uint64_t val = p.val, pos = p.pos;
+      if (mine && special) {
+        found = pass == 0 && hdr->spec_live[key - kTomb] != 0;
+        val = hdr->spec_val[key - kTomb];
+        pos = kSpecRef + (key - kTomb);
+      }
+      bool flag = false;
+      uint8_t st = kIns ? (uint8_t)kPresent : (uint8_t)0;
+      if (mine) {
+        if constexpr (kIns) {
+          if (!found && !fast && pass == 0) {
+            flag = true;      // FULL unless pass 1 stores it
+            st = kFull;
+            val = ~0ull;
+          } else if (!found && pos == kNoPos) {
+            st = kFull;       // no free slot anywhere: cannot happen below capacity
+            aor32(&hdr->err, kErrFull);
+          } else if (!found) {
+            st = kInserted;
+            flag = true;
+            ++changed;
+            val = pos;
+            if (OP == sInsert) {
+              const uint64_t v = load_val<VK>(vals, i);
+              if (special) {
+                hdr->spec_live[key - kTomb] = 1;
+                hdr->spec_val[key - kTomb] = v;
+              } else if (VK) {
+                t.bk[pos >> 3].s[pos & 7].val = v;
+              }
+            }
+          }
+        } else if (found) {
+          if (special) hdr->spec_live[key - kTomb] = 0;
+          // kEmpty only where the bucket already holds one: no probe sequence runs through it
+          else t.bk[pos >> 3].s[pos & 7].key = p.had_empty ? kEmpty : kTomb;
+          st = 1;
+          flag = true;
+          ++changed;
+        }
+        rf[i] = val;
+        ost[i] = st;
+      }
+      if (pass == 0 && ranked) {
+        if (i < n) flg[i] = flag;
+        const uint64_t m = __ballot(flag);
+        if (wave_lane() == 0) flagged[e][wave] = (uint32_t)__builtin_popcountll(m);
+        if (flag) rk[i] = (uint16_t)__builtin_popcountll(m & ((1ull << wave_lane()) - 1ull));
+      }
+    }
+    if (pass == 0 && ranked) {  // ranks in index order: (element, wave, lane)
+      __syncthreads();
+#pragma unroll 1
+      for (int e = 0; e * bd < n; ++e) {
+        const int i = e * bd + tid;
+        for (int v = 0; v < (bd >> 6); ++v) {
+          if (v == wave && i < n && flg[i]) rk[i] = (uint16_t)(rk[i] + nnew);
+          nnew += flagged[e][v];
+        }
+      }
+    }
+  }
+  if (kPool) {  // (each thread's own elements: no barrier needed)
+#pragma unroll 1
+    for (int i = tid; i < n; i += bd) {
+      if (!flg[i]) continue;
+      const int64_t r = rk[i];
+      if (OP == sRelease) {
+        const int64_t at = top0 + r;
+        if (at < pcap) pstack[ring_pos(head, pcap, at)] = (int32_t)(uint32_t)rf[i];
+      } else if (ost[i] == kInserted) {
+        const uint32_t v = (uint32_t)pstack[ring_pos(head, pcap, top0 - 1 - r)];
+        const uint64_t pos = rf[i];
+        if (pos >= kSpecRef) {
+          hdr->spec_live[pos - kSpecRef] = 1;
+          hdr->spec_val[pos - kSpecRef] = v;
+        } else {
+          t.bk[pos >> 3].s[pos & 7].val = v;
+        }
+        rf[i] = v;
+      }
+    }
+  }
+  const uint64_t sum = wave_sum(changed);
+  if (wave_lane() == 0 && sum) atomicAdd(&changed_sum, (uint32_t)sum);
+  __syncthreads();
+#pragma unroll 1
+  for (int i = tid; i < n; i += bd) {  // later copies take the outcome of the first
+    const uint32_t f = fst[i];
+    if (f == kSkipped) continue;
+    uint8_t st = ost[f];
+    if (f != (uint32_t)i) st = kIns ? (st == kFull ? kFull : kPresent) : 0;
+    if (status) status[i] = st;
+    if (OP == sAlloc && vout) vout[i] = (int32_t)(uint32_t)rf[f];
+  }
+  if (tid == 0) {
+    hdr->size0 = size0;
+    if (kPool) pool->top0 = top0;
+    if (OP == sAlloc) rank_totals(t, pool, nnew, 1);
+    else if (OP == sRelease) rank_totals(t, pool, nnew, 2);
+    else if (kIns && !fast) rank_totals(t, nullptr, nnew, 0);
+    else hdr->size = kIns ? size0 + changed_sum : size0 - changed_sum;
+    if (OP == sErase) chunk_feedback(t, 1, n, changed_sum);
+    if (OP == sInsert && fast) chunk_feedback(t, 0, n, changed_sum);
+  }
+}
+
 // find / contains: a wave takes 64 consecutive keys, one per lane (coalesced loads and stores), and
 // probes them in rounds until every lane has its answer.
 template <int VK>
@@ -1689,7 +1908,8 @@ __device__ __forceinline__ void find_range(const TableView& t, WaveLds* w,
     uint32_t left = (uint32_t)t.nb;
     for (uint64_t mask = __ballot(look); mask; mask = __ballot(look)) {
       uint64_t val = 0;
-      const uint32_t x = probe_round<false, VK != 0>(t, w, mask, look, key, b, &val);
+      const ProbeRound<false, VK != 0, false> round(t, w, mask, look, key, b, 0);
+      const uint32_t x = round.answer(0, &val);
       if (look) {
         if (x & kBitsMatch) {
           hit = true;
@@ -2456,19 +2676,19 @@ __device__ __forceinline__ void g_insert_body(const GStep* __restrict__ st, cons
   WaveLds* w = wave_lds<BS>();
   if (t.hdr->spec) {
     uint2 c;
-    if (g.vk == 1) c = insert_spec_range<1>(t, w, g.keys, g.vals, g.flags, lo, g.q, step);
-    else if (g.vk == 2) c = insert_spec_range<2>(t, w, g.keys, g.vals, g.flags, lo, g.q, step);
-    else c = insert_spec_range<0>(t, w, g.keys, nullptr, g.flags, lo, g.q, step);
+    if (g.vk == 1) c = insert_spec_range<1, false>(t, w, g.keys, g.vals, g.flags, lo, g.q, step);
+    else if (g.vk == 2) c = insert_spec_range<2, false>(t, w, g.keys, g.vals, g.flags, lo, g.q, step);
+    else c = insert_spec_range<0, false>(t, w, g.keys, nullptr, g.flags, lo, g.q, step);
     g_spec_counts<BS>(t, c, L.lb, false);
     return;
   }
   int64_t ins;
   if (g.vk == 1)
-    ins = insert_range<1, false>(t, w, g.keys, nullptr, g.vals, g.db - 1, g.flags, nullptr, lo, g.q, step);
+    ins = insert_range<1, false, false>(t, w, g.keys, nullptr, g.vals, g.db - 1, g.flags, nullptr, lo, g.q, step);
   else if (g.vk == 2)
-    ins = insert_range<2, false>(t, w, g.keys, nullptr, g.vals, g.db - 1, g.flags, nullptr, lo, g.q, step);
+    ins = insert_range<2, false, false>(t, w, g.keys, nullptr, g.vals, g.db - 1, g.flags, nullptr, lo, g.q, step);
   else
-    ins = insert_range<0, false>(t, w, g.keys, nullptr, nullptr, g.db - 1, g.flags, nullptr, lo, g.q, step);
+    ins = insert_range<0, false, false>(t, w, g.keys, nullptr, nullptr, g.db - 1, g.flags, nullptr, lo, g.q, step);
   const int64_t tot = block_sum<BS>(ins);
   if (threadIdx.x == 0) t.bcnt[L.lb] = tot;
 }
@@ -2478,12 +2698,12 @@ __device__ __forceinline__ void g_erase_body(const GStep* __restrict__ st, const
   const GStep& g = st[L.step];
   const TableView t = g.v;
   if (t.hdr->spec) {
-    const uint2 c = erase_spec_range(t, wave_lds<BS>(), g.keys, g.flags, (int64_t)L.lb * BS, g.q,
+    const uint2 c = erase_spec_range<false>(t, wave_lds<BS>(), g.keys, g.flags, (int64_t)L.lb * BS, g.q,
                                      (int64_t)L.nblk * BS);
     g_spec_counts<BS>(t, c, L.lb, true);
     return;
   }
-  const int64_t del = erase_range<false>(t, wave_lds<BS>(), g.keys, g.db - 1, g.flags, (int64_t)L.lb * BS,
+  const int64_t del = erase_range<false, false>(t, wave_lds<BS>(), g.keys, g.db - 1, g.flags, (int64_t)L.lb * BS,
                                          g.q, (int64_t)L.nblk * BS);
   const int64_t tot = block_sum<BS>(del);
   if (threadIdx.x == 0) t.bcnt[L.lb] = -tot;
@@ -3057,6 +3277,38 @@ bool use_speculation(const ct_table* t, int word) {
 // Batches of 2^21 keys would gain no more than those launches.
 constexpr int64_t kDeviceDecides = (int64_t)1 << 22;
 
+// Inserts and erases of at most this many keys read ahead on their probe paths (ProbeRound): their
+// waves do not fill the chip, so a lane waits for one bucket after another while the memory has
+// room.  60,000 keys erased and inserted again at load 0.8 took 86 us without and 79 with; at 2^18
+// keys (a voxel frame) the extra lines cost as much as they save (61 us without, 66 with).  Finds
+// walk shorter paths and gained nothing.
+constexpr int64_t kAheadMax = 65536;
+
+void find_kernel(int vk, hipStream_t s, const TableView& v, const uint64_t* keys, int64_t n, void* out,
+                 uint8_t* found) {
+  const int gb = group_blocks((n + kSlots - 1) / kSlots);
+  if (vk == CT_VAL_U32) k_find<1><<<gb, kBlock, 0, s>>>(v, keys, n, out, found);
+  else if (vk == CT_VAL_U64) k_find<2><<<gb, kBlock, 0, s>>>(v, keys, n, out, found);
+  else k_find<0><<<gb, kBlock, 0, s>>>(v, keys, n, nullptr, found);
+}
+
+// Batches (and last chunks) of at most this many keys run as one workgroup's launch: 2048 keys erased,
+// inserted and partly looked up took 66 us as separate launches and take 50; the limit is what one
+// workgroup holds at two keys per thread.
+constexpr int64_t kSmallBatch = kSmallMax;
+
+template <int VK, int OP>
+ct_status small_batch(ct_table* t, const TableView& v, ct_pool* p, const uint64_t* keys,
+                      const uint8_t* skip, const void* vals, int64_t n, uint8_t* status,
+                      int32_t* vout, hipStream_t s) {
+  const int threads = (int)std::min<int64_t>(1024, std::max<int64_t>(64, pow2ceil(n)));
+  launch(t, OP == sInsert || OP == sAlloc ? CT_KERNEL_INSERT : CT_KERNEL_ERASE, s, [&] {
+    k_small<VK, OP><<<1, threads, 0, s>>>(v, p ? p->hdr : nullptr, p ? p->stack : nullptr, keys, skip,
+                                          vals, (int32_t)n, dedup_slots_for(n), status, vout);
+  });
+  return launched();
+}
+
 // The resolution kernels of a speculative chunk (after its insert or erase kernel).
 // The resolution kernels stride over their elements with at most kSpecGrid blocks: they read one
 // header word and leave when nothing is listed, and a small grid keeps that cheap.
@@ -3090,10 +3342,15 @@ ct_status insert_chunks(ct_table* t, const BatchScratch& B, const uint64_t* keys
     // the host bound proves that no element can meet FULL: the rank pass is not needed
     const bool surely_fast = t->size_ub + (uint64_t)q <= (uint64_t)t->desc.capacity;
     t->size_ub = std::min<uint64_t>(t->size_ub + (uint64_t)q, (uint64_t)t->desc.capacity);
+    if (q <= kSmallBatch) {
+      ct_status r = small_batch<VK, sInsert>(t, v, nullptr, kc, nullptr, vc, q, sc, nullptr, s);
+      if (r != CT_OK) return r;
+      continue;
+    }
     if (surely_fast && use_speculation(t, 0)) {
       // speculative: insert first, then resolve the copies of keys listed as ambiguous
       launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_spec_prologue<<<1, 64, 0, s>>>(v, q, 1); });
-      launch(t, CT_KERNEL_INSERT, s, [&] { k_insert_spec<VK><<<gb, kBlock, 0, s>>>(v, kc, vc, q, sc); });
+      launch(t, CT_KERNEL_INSERT, s, [&] { (q <= kAheadMax ? k_insert_spec<VK, true> : k_insert_spec<VK, false>)<<<gb, kBlock, 0, s>>>(v, kc, vc, q, sc); });
       spec_resolve<VK, false>(t, v, kc, vc, q, sc, gb, db, s);
       ct_status r = launched();
       if (r != CT_OK) return r;
@@ -3104,11 +3361,11 @@ ct_status insert_chunks(ct_table* t, const BatchScratch& B, const uint64_t* keys
     if (decided) {  // the speculative kernels first; whichever path is not taken leaves at once
       const int always = t->insert_path == CT_INSERT_SPECULATIVE;
       launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_spec_decide<<<1, 64, 0, s>>>(v, q, always); });
-      launch(t, CT_KERNEL_INSERT, s, [&] { k_insert_spec<VK><<<gb, kBlock, 0, s>>>(v, kc, vc, q, sc); });
+      launch(t, CT_KERNEL_INSERT, s, [&] { k_insert_spec<VK, false><<<gb, kBlock, 0, s>>>(v, kc, vc, q, sc); });
       spec_resolve<VK, false>(t, v, kc, vc, q, sc, gb, db, s);
     }
     dedup_chunk(t, v, nullptr, kc, q, s, decided);
-    launch(t, CT_KERNEL_INSERT, s, [&] { k_insert<VK, false><<<gb, kBlock, 0, s>>>(v, kc, vc, q, db - 1, sc, nullptr, nullptr); });
+    launch(t, CT_KERNEL_INSERT, s, [&] { (q <= kAheadMax ? k_insert<VK, false, true> : k_insert<VK, false, false>)<<<gb, kBlock, 0, s>>>(v, kc, vc, q, db - 1, sc, nullptr, nullptr); });
     launch(t, CT_KERNEL_APPLY, s, [&] { k_apply_count<<<1, 1024, 0, s>>>(v, gb, q, 0, decided); });
     if (!surely_fast) {
       launch(t, CT_KERNEL_RANK, s, [&] { k_tile_count<<<ntiles, kBlock, 0, s>>>(v, q); });
@@ -3142,17 +3399,23 @@ ct_status erase_chunks(ct_table* t, const BatchScratch& B, ct_pool* p, const uin
     uint8_t* ec = erased ? erased + c0 : nullptr;
     const int gb = group_blocks((q + kSlots - 1) / kSlots);
     const int ntiles = (int)((q + kTile - 1) / kTile);
+    if (q <= kSmallBatch) {
+      ct_status r = small_batch<1, RELEASE ? sRelease : sErase>(t, v, p, kc, nullptr, nullptr, q, ec,
+                                                                nullptr, s);
+      if (r != CT_OK) return r;
+      continue;
+    }
     if (!RELEASE && use_speculation(t, 1)) {
       // speculative: remove first, then move each removal to the lowest copy of its key
       launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_spec_prologue<<<1, 64, 0, s>>>(v, q, 0); });
-      launch(t, CT_KERNEL_ERASE, s, [&] { k_erase_spec<<<gb, kBlock, 0, s>>>(v, kc, q, ec); });
+      launch(t, CT_KERNEL_ERASE, s, [&] { (q <= kAheadMax ? k_erase_spec<true> : k_erase_spec<false>)<<<gb, kBlock, 0, s>>>(v, kc, q, ec); });
       spec_resolve<0, true>(t, v, kc, nullptr, q, ec, gb, db, s);
       ct_status r = launched();
       if (r != CT_OK) return r;
       continue;
     }
     dedup_chunk(t, v, RELEASE ? p->hdr : nullptr, kc, q, s);
-    launch(t, CT_KERNEL_ERASE, s, [&] { k_erase<RELEASE><<<gb, kBlock, 0, s>>>(v, kc, q, db - 1, ec); });
+    launch(t, CT_KERNEL_ERASE, s, [&] { (q <= kAheadMax ? k_erase<RELEASE, true> : k_erase<RELEASE, false>)<<<gb, kBlock, 0, s>>>(v, kc, q, db - 1, ec); });
     if (!RELEASE) {
       launch(t, CT_KERNEL_APPLY, s, [&] { k_apply_count<<<1, 1024, 0, s>>>(v, gb, q, 1, 0); });
     } else {
@@ -3356,13 +3619,7 @@ ct_status ct_find_batch(ct_table* t, const uint64_t* keys, int64_t n, void* vals
   const int vk = t->desc.val_kind;
   if (vk == CT_VAL_NONE && vals_out) return CT_E_INVALID;
   if (n == 0) return CT_OK;
-  const int gb = group_blocks((n + kSlots - 1) / kSlots);
-  hipStream_t s = S(stream);
-  launch(t, CT_KERNEL_FIND, s, [&] {
-    if (vk == CT_VAL_U32) k_find<1><<<gb, kBlock, 0, s>>>(t->v, keys, n, vals_out, found);
-    else if (vk == CT_VAL_U64) k_find<2><<<gb, kBlock, 0, s>>>(t->v, keys, n, vals_out, found);
-    else k_find<0><<<gb, kBlock, 0, s>>>(t->v, keys, n, nullptr, found);
-  });
+  launch(t, CT_KERNEL_FIND, S(stream), [&] { find_kernel(vk, S(stream), t->v, keys, n, vals_out, found); });
   return launched();
 }
 
@@ -3775,6 +4032,12 @@ ct_status insert_alloc_chunks(ct_table* t, const BatchScratch& B, ct_pool* p, co
     const uint8_t* mc = skip ? skip + c0 : nullptr;
     uint8_t* sc = status ? status + c0 : nullptr;
     int32_t* vc = vals_out ? vals_out + c0 : nullptr;
+    if (q <= kSmallBatch) {
+      r = small_batch<1, sAlloc>(t, v, p, kc, mc, nullptr, q, sc, vc, s);
+      if (r != CT_OK) return r;
+      t->size_ub = std::min<uint64_t>(t->size_ub + (uint64_t)q, (uint64_t)t->desc.capacity);
+      continue;
+    }
     t->size_ub = std::min<uint64_t>(t->size_ub + (uint64_t)q, (uint64_t)t->desc.capacity);
     const int gb = group_blocks((q + kSlots - 1) / kSlots);
     const int ntiles = (int)((q + kTile - 1) / kTile);
@@ -3784,7 +4047,7 @@ ct_status insert_alloc_chunks(ct_table* t, const BatchScratch& B, ct_pool* p, co
     } else {
       dedup_chunk(t, v, p->hdr, kc, q, s);
     }
-    launch(t, CT_KERNEL_INSERT, s, [&] { k_insert<1, true><<<gb, kBlock, 0, s>>>(v, kc, nullptr, q, db - 1, sc, vc, mc); });
+    launch(t, CT_KERNEL_INSERT, s, [&] { (q <= kAheadMax ? k_insert<1, true, true> : k_insert<1, true, false>)<<<gb, kBlock, 0, s>>>(v, kc, nullptr, q, db - 1, sc, vc, mc); });
     const int inl = ntiles <= kInlineRankTiles ? ntiles : 0;
     if (!inl) launch(t, CT_KERNEL_RANK, s, [&] { k_tile_scan<<<1, 1024, 0, s>>>(v, p->hdr, ntiles, 1); });
     launch(t, CT_KERNEL_FINAL, s, [&] { k_final<1, 1><<<ntiles, kBlock, 0, s>>>(v, p->hdr, p->stack, kc, nullptr, q, sc, vc, inl); });
@@ -3907,12 +4170,7 @@ ct_status run_op(const PlanOp& o, hipStream_t s) {
     case kOpErase:
       return erase_chunks<false>(t, BatchScratch{t->v, t->chunk}, nullptr, o.keys, o.n, o.flags, s);
     default: {
-      const int gb = group_blocks((o.n + kSlots - 1) / kSlots);
-      launch(t, CT_KERNEL_FIND, s, [&] {
-        if (vk == CT_VAL_U32) k_find<1><<<gb, kBlock, 0, s>>>(t->v, o.keys, o.n, o.vout, o.flags);
-        else if (vk == CT_VAL_U64) k_find<2><<<gb, kBlock, 0, s>>>(t->v, o.keys, o.n, o.vout, o.flags);
-        else k_find<0><<<gb, kBlock, 0, s>>>(t->v, o.keys, o.n, nullptr, o.flags);
-      });
+      launch(t, CT_KERNEL_FIND, s, [&] { find_kernel(vk, s, t->v, o.keys, o.n, o.vout, o.flags); });
       return launched();
     }
   }

@@ -10,7 +10,8 @@ from paper_1908_05936_amd.workloads import distinct_u64, rng_for
 
 pytestmark = pytest.mark.gpu
 
-SIZES = [1, 2, 7, 8, 9, 15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 129, 255, 256, 257, 1000]
+SIZES = [1, 2, 7, 8, 9, 15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 129, 255, 256, 257, 1000,
+         1023, 1025, 2047, 2048, 2049]   # up to 2048 updates run as one workgroup
 # (capacity, buckets): one bucket, a power of two, a prime, neither (linear steps); all physically
 # full or nearly, so that absent keys walk several buckets
 TABLES = [(8, 1), (64, 8), (104, 13), (72, 9), (1000, 0)]
