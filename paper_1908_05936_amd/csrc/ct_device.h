@@ -50,8 +50,9 @@ constexpr int kBinLds = 2048;           // LDS hash slots of the fine-bin dedup:
                                         // bin must be fewer (else the chunk takes the fallback)
 constexpr int kMaxFinePerCoarse = 256;  // fine bins per coarse bin at the largest chunk (2^24)
 constexpr int kMaxGroupBlocks = 16384;  // blocks of one insert/erase launch: its count partials
-constexpr int kStripeRegion = 4096;     // behind the partials: the speculative insert's listed
-                                        // counts, 32 words on separate 128-byte lines
+constexpr int kCountStripes = 32;       // count words of a speculative chunk, behind the partials
+constexpr int kCountStride = 16;        // u64 words between them: one 128-byte line each
+constexpr int kStripeRegion = kCountStripes * kCountStride * 8;
 
 enum : uint8_t { kPresent = 0, kInserted = 1, kFull = 2, kNoStatus = 0xFF };
 enum : uint32_t { kErrFull = 1u, kErrPool = 2u, kErrInternal = 0x80000000u };
@@ -130,6 +131,7 @@ struct TableView {
   uint64_t* ref;    // per chunk element: claimed slot, or the value an erase releases
   uint32_t* tsum;   // per tile: flagged count, then its exclusive prefix
   int64_t* bcnt;    // per block of the last insert/erase kernel: change of the live count
+  uint64_t* stripes; // counts of a speculative chunk (the table's own, zero between batches)
   // binned dedup (chunks of at least kBinMinChunk elements): elements are scattered by a hash of
   // their key into P1 coarse bins, then into P = P1 * P2 fine bins, and each fine bin resolves its
   // repeated keys in LDS.  A coarse bin is kBinSub segments: scatter block b appends to segment

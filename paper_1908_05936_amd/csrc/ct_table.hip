@@ -104,6 +104,7 @@ __device__ __forceinline__ void reset_range(const TableView& t, int64_t lo, int6
     if (zero_err) {
       h->err = 0;
       h->inject = 0;
+      for (int j = 0; j < kCountStripes; ++j) t.stripes[j * kCountStride] = 0;
     }
     // an empty table starts a fresh history: its next insert and erase chunks speculate
     h->fbd[0] = h->fbd[1] = 0;
@@ -943,20 +944,24 @@ __global__ __launch_bounds__(1024) void k_apply_count(TableView t, int nblocks, 
 // out-of-band keys are always listed and resolved by one thread.  With distinct keys absent from
 // the table nothing is listed, and the resolution kernels return at once.
 // ---------------------------------------------------------------------------------------------
-constexpr int kListStripes = 32;          // listed-count stripes, one per 128-byte line
-constexpr int kListStripeWords = 32;      // u32 words between stripes
 enum : uint8_t { kFlagNone = 0, kFlagClaimed = 1, kFlagListed = 2 };
 
-// The listed-count stripes sit behind the block partials of the table's bcnt region.
-__device__ __forceinline__ uint32_t* list_stripes(const TableView& t) {
-  return reinterpret_cast<uint32_t*>(t.bcnt + kMaxGroupBlocks);
+// A speculative chunk's counts: every block adds (elements stored or removed << 32 | listed) to one
+// of kCountStripes words on separate 128-byte lines of the table, which are zero between batches.
+// (Per-block partials summed by one block took 10.8 us per 2^23-key chunk, and zeroing the words
+// first another launch.)
+__device__ __forceinline__ void spec_count(const TableView& t, int64_t block, int64_t tot) {
+  if (tot) aadd64(&t.stripes[(block % kCountStripes) * kCountStride], (uint64_t)tot);
 }
 
-__device__ __forceinline__ uint32_t listed_total(const TableView& t) {
-  const uint32_t* st = list_stripes(t);
-  uint32_t n = 0;
-  for (int j = 0; j < kListStripes; ++j) n += st[j * kListStripeWords];
-  return n;
+// Their sum; the first wave of a block calls it.
+__device__ __forceinline__ uint64_t spec_total(const TableView& t) {
+  const int lane = wave_lane();
+  return wave_sum(lane < kCountStripes ? t.stripes[lane * kCountStride] : 0ull);
+}
+
+__device__ __forceinline__ void spec_zero(const TableView& t) {
+  if (threadIdx.x < kCountStripes) t.stripes[threadIdx.x * kCountStride] = 0;
 }
 
 // Elements [lo, hi) of a chunk, 64 per wave.  Returns this thread's (stored, listed) counts.
@@ -1003,18 +1008,12 @@ __device__ __forceinline__ uint2 insert_spec_range(const TableView& t, WaveLds* 
 template <int VK, bool AHEAD>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(AHEAD ? 1 : 5))) void k_insert_spec(TableView t, const uint64_t* __restrict__ keys,
                                                         const void* __restrict__ vals, int64_t q,
-                                                        uint8_t* __restrict__ status) {
-  if (!t.hdr->spec) return;
+                                                        uint8_t* __restrict__ status, int decided) {
+  if (decided && !t.hdr->spec) return;
   const uint2 c = insert_spec_range<VK, AHEAD>(t, wave_lds<kBlock>(), keys, vals, status, (int64_t)blockIdx.x * kBlock, q,
                                         (int64_t)gridDim.x * kBlock);
-  // both counts in one reduction: stored in the low half, listed in the high half
-  const int64_t tot = block_sum((int64_t)c.x + ((int64_t)c.y << 32));
-  if (threadIdx.x == 0) {
-    t.bcnt[blockIdx.x] = tot & 0xFFFFFFFFll;
-    const uint32_t nl = (uint32_t)(tot >> 32);
-    // one atomic per block with listed elements, spread over the stripes
-    if (nl) aadd32(&list_stripes(t)[(blockIdx.x % kListStripes) * kListStripeWords], nl);
-  }
+  const int64_t tot = block_sum(((int64_t)c.x << 32) + (int64_t)c.y);
+  if (threadIdx.x == 0) spec_count(t, blockIdx.x, tot);
 }
 
 // Speculative erase: every element probes; a found key is removed with one CAS (key -> kEmpty
@@ -1054,35 +1053,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(AHEAD ? 
                                                        int64_t q, uint8_t* __restrict__ erased) {
   const uint2 c = erase_spec_range<AHEAD>(t, wave_lds<kBlock>(), keys, erased, (int64_t)blockIdx.x * kBlock, q,
                                    (int64_t)gridDim.x * kBlock);
-  const int64_t tot = block_sum((int64_t)c.x + ((int64_t)c.y << 32));
-  if (threadIdx.x == 0) {
-    t.bcnt[blockIdx.x] = -(tot & 0xFFFFFFFFll);
-    const uint32_t nl = (uint32_t)(tot >> 32);
-    if (nl) aadd32(&list_stripes(t)[(blockIdx.x % kListStripes) * kListStripeWords], nl);
-  }
-}
-
-// The header of a speculative chunk, by the first wave of its first block: counters snapshot, listed
-// counts zeroed.
-__device__ __forceinline__ void spec_header(const TableView& t) {
-  if (threadIdx.x < kListStripes) list_stripes(t)[threadIdx.x * kListStripeWords] = 0;
-  if (threadIdx.x == 0) {
-    Header* h = t.hdr;
-    h->size0 = h->size;
-    h->spec_first[0] = h->spec_first[1] = kNone;
-    h->ndup = 0;
-    h->nnew = 0;
-    h->fast = 1u;
-    h->spec = 1u;
-    h->dmode = 0u;
-  }
-}
-
-// The host's size bound has proved that the chunk cannot reach capacity; a live count that
-// says otherwise is a library bug and raises kErrInternal.
-__global__ void k_spec_prologue(TableView t, int64_t q, int insert) {
-  if (threadIdx.x == 0 && insert && t.hdr->size + (uint64_t)q > t.cap) t.hdr->err |= kErrInternal;
-  spec_header(t);
+  const int64_t tot = block_sum(((int64_t)c.x << 32) + (int64_t)c.y);
+  if (threadIdx.x == 0) spec_count(t, blockIdx.x, tot);
 }
 
 // Whether the table's last insert (word 0) or erase (word 1) chunk changed at least half its keys.
@@ -1093,14 +1065,13 @@ __device__ __forceinline__ bool mostly_changed(const Header* h, int word) {
 }
 
 // The host could not prove that a large insert chunk stays below capacity: decide from the live
-// count itself, and (unless `always`) from how the last chunk went.  One wave.
-__global__ __launch_bounds__(64) void k_spec_decide(TableView t, int64_t q, int always) {
+// count itself, and (unless `always`) from how the last chunk went.  One thread.
+__global__ void k_spec_decide(TableView t, int64_t q, int always) {
   const Header* h = t.hdr;
   const bool spec = h->size + (uint64_t)q <= t.cap && (always || mostly_changed(h, 0));
-  if (spec) {
-    spec_header(t);
-  } else if (threadIdx.x == 0) {
-    t.hdr->spec = 0u;
+  if (threadIdx.x == 0) {
+    t.hdr->spec = spec ? 1u : 0u;
+    t.hdr->fast = spec ? 1u : 0u;  // (the ranked completion leaves at once)
     t.hdr->ndup = 0;
   }
 }
@@ -1126,24 +1097,25 @@ __device__ __forceinline__ uint32_t* spec_low(const TableView& t, const SpecPlan
   return reinterpret_cast<uint32_t*>(t.dd + p.slots);
 }
 
-// One block: the count change of the insert or erase kernel (`nblocks` partials) goes into the
-// live count and the feedback word; the listed counts are summed into the header for the
-// kernels that follow.
-__global__ __launch_bounds__(1024) void k_spec_sum(TableView t, int nblocks, int64_t q, int erase) {
-  if (!t.hdr->spec) return;
-  const int64_t change = apply_count_block(t, nblocks);
-  if (threadIdx.x == 0) {
-    chunk_feedback(t, erase, q, erase ? -change : change);
-    t.hdr->ndup = listed_total(t);
-  }
+// The counters after a speculative insert or erase of q elements whose counts are `tot`: live count,
+// feedback words, and what the resolution reads.  One thread.  An insert ran because its chunk
+// cannot reach capacity; a live count that says otherwise is a library bug.
+__device__ __forceinline__ void spec_settle(const TableView& t, int64_t q, bool erase, uint64_t tot) {
+  Header* h = t.hdr;
+  const uint64_t changed = tot >> 32;
+  if (!erase && h->size + (uint64_t)q > t.cap) h->err |= kErrInternal;
+  h->size = erase ? h->size - changed : h->size + changed;
+  chunk_feedback(t, erase, q, (int64_t)changed);
+  h->spec_first[0] = h->spec_first[1] = kNone;
+  h->ndup = (uint32_t)tot;
 }
 
-// Clears the dd entries (and, in the claimer direction, the lowest-index words) the resolution
-// uses; nothing when no element is listed.
+// Clears the dd entries (and, in the claimer direction, the lowest-index words) the resolution of
+// `nd` listed elements uses; nothing when no element is listed.
 // (The resolution stages take their block b of nb as arguments, so that the grouped plan can run
 // them per step; the single-table kernels pass blockIdx.x and gridDim.x.)
-__device__ __forceinline__ void spec_clear_range(const TableView& t, int64_t q, int64_t b, int64_t nb) {
-  const uint32_t nd = t.hdr->ndup;
+__device__ __forceinline__ void spec_clear_range(const TableView& t, int64_t q, uint32_t nd, int64_t b,
+                                                 int64_t nb) {
   if (nd == 0) return;
   const SpecPlan p = spec_plan(nd, q);
   const int64_t units = p.slots / 2;
@@ -1158,8 +1130,19 @@ __device__ __forceinline__ void spec_clear_range(const TableView& t, int64_t q, 
   }
 }
 
-__global__ __launch_bounds__(kBlock) void k_spec_clear(TableView t, int64_t q) {
-  spec_clear_range(t, q, blockIdx.x, gridDim.x);
+// Every block sums the counts for itself; the first also settles the counters.
+__global__ __launch_bounds__(kBlock) void k_spec_clear(TableView t, int64_t q, int erase, int decided) {
+  if (decided && !t.hdr->spec) return;
+  __shared__ uint64_t tot;
+  if (threadIdx.x < 64) {
+    const uint64_t v = spec_total(t);
+    if (threadIdx.x == 0) {
+      tot = v;
+      if (blockIdx.x == 0) spec_settle(t, q, erase != 0, v);
+    }
+  }
+  __syncthreads();
+  spec_clear_range(t, q, (uint32_t)tot, blockIdx.x, gridDim.x);
 }
 
 // dd slot of `key` among entries (tag | chunk index); kNone when absent.
@@ -1187,7 +1170,7 @@ __device__ __forceinline__ uint32_t dd_find(const TableView& t, const uint64_t* 
 // header word in both directions.
 __device__ __forceinline__ void spec_build_range(const TableView& t, const uint64_t* __restrict__ keys,
                                                  int64_t q, int64_t blk, int64_t nblk) {
-  const uint32_t nd = t.hdr->ndup;  // written by k_spec_sum
+  const uint32_t nd = t.hdr->ndup;  // written by spec_settle
   if (nd == 0) return;
   const SpecPlan p = spec_plan(nd, q);
   const uint32_t dmask = p.slots - 1;
@@ -1304,7 +1287,7 @@ __device__ __forceinline__ void spec_probe_range(const TableView& t, const uint6
                                                  const void* __restrict__ vals, int64_t q,
                                                  uint8_t* __restrict__ status, int64_t blk,
                                                  int64_t nblk) {
-  const uint32_t nd = t.hdr->ndup;  // written by k_spec_sum
+  const uint32_t nd = t.hdr->ndup;  // written by spec_settle
   if (nd == 0) return;
   const SpecPlan p = spec_plan(nd, q);
   const uint32_t dmask = p.slots - 1;
@@ -1367,7 +1350,7 @@ __device__ __forceinline__ void spec_swap_range(const TableView& t, const uint64
                                                 const void* __restrict__ vals, int64_t q,
                                                 uint8_t* __restrict__ status, int64_t blk,
                                                 int64_t nblk) {
-  const uint32_t nd = t.hdr->ndup;  // written by k_spec_sum
+  const uint32_t nd = t.hdr->ndup;  // written by spec_settle
   if (nd == 0) return;
   if (blk == 0 && threadIdx.x == 0) {
     Header* h = t.hdr;
@@ -1410,6 +1393,7 @@ template <int VK, bool ERASE>
 __global__ __launch_bounds__(kBlock) void k_spec_swap(TableView t, const uint64_t* __restrict__ keys,
                                                       const void* __restrict__ vals, int64_t q,
                                                       uint8_t* __restrict__ status) {
+  if (blockIdx.x == 0) spec_zero(t);  // for the next batch
   spec_swap_range<VK, ERASE>(t, keys, vals, q, status, blockIdx.x, gridDim.x);
 }
 
@@ -2639,7 +2623,11 @@ __device__ __forceinline__ void g_prologue_body(const GStep* __restrict__ st, co
   const GStep& g = st[L.step];
   const TableView t = g.v;
   if (g_speculates(g)) {
-    if (L.lb == 0) spec_header(t);
+    if (L.lb == 0 && threadIdx.x == 0) {
+      t.hdr->ndup = 0;
+      t.hdr->fast = 1u;
+      t.hdr->spec = 1u;
+    }
     return;
   }
   prologue_range(t, nullptr, g.db, g.q, (int64_t)L.lb * kBlock, prologue_units(g.db, g.q),
@@ -2651,19 +2639,6 @@ __device__ __forceinline__ void g_dedup_body(const GStep* __restrict__ st, const
   const TableView t = g.v;
   if (t.hdr->spec) return;
   dedup_range(t, g.keys, nullptr, g.db - 1, (int64_t)L.lb * kBlock, g.q, (int64_t)L.nblk * kBlock);
-}
-
-// Block totals of a speculative insert or erase: the count change into the block's partial, the
-// listed elements onto one of the listed-count stripes.
-template <int BS>
-__device__ __forceinline__ void g_spec_counts(const TableView& t, uint2 c, int32_t lb, bool erase) {
-  const int64_t tot = block_sum<BS>((int64_t)c.x + ((int64_t)c.y << 32));
-  if (threadIdx.x == 0) {
-    const int64_t changed = tot & 0xFFFFFFFFll;
-    t.bcnt[lb] = erase ? -changed : changed;
-    const uint32_t nl = (uint32_t)(tot >> 32);
-    if (nl) aadd32(&list_stripes(t)[(lb % kListStripes) * kListStripeWords], nl);
-  }
 }
 
 // The grouped find / insert / erase stages run with BS threads per block (the plan's block size):
@@ -2679,7 +2654,8 @@ __device__ __forceinline__ void g_insert_body(const GStep* __restrict__ st, cons
     if (g.vk == 1) c = insert_spec_range<1, false>(t, w, g.keys, g.vals, g.flags, lo, g.q, step);
     else if (g.vk == 2) c = insert_spec_range<2, false>(t, w, g.keys, g.vals, g.flags, lo, g.q, step);
     else c = insert_spec_range<0, false>(t, w, g.keys, nullptr, g.flags, lo, g.q, step);
-    g_spec_counts<BS>(t, c, L.lb, false);
+    const int64_t tot = block_sum<BS>(((int64_t)c.x << 32) + (int64_t)c.y);
+    if (threadIdx.x == 0) spec_count(t, L.lb, tot);
     return;
   }
   int64_t ins;
@@ -2700,7 +2676,8 @@ __device__ __forceinline__ void g_erase_body(const GStep* __restrict__ st, const
   if (t.hdr->spec) {
     const uint2 c = erase_spec_range<false>(t, wave_lds<BS>(), g.keys, g.flags, (int64_t)L.lb * BS, g.q,
                                      (int64_t)L.nblk * BS);
-    g_spec_counts<BS>(t, c, L.lb, true);
+    const int64_t tot = block_sum<BS>(((int64_t)c.x << 32) + (int64_t)c.y);
+    if (threadIdx.x == 0) spec_count(t, L.lb, tot);
     return;
   }
   const int64_t del = erase_range<false, false>(t, wave_lds<BS>(), g.keys, g.db - 1, g.flags, (int64_t)L.lb * BS,
@@ -2725,19 +2702,24 @@ __device__ __forceinline__ void g_find_body(const GStep* __restrict__ st, const 
 __device__ __forceinline__ void g_apply_body(const GStep* __restrict__ st, const GLoc L) {
   const GStep& g = st[L.step];
   const TableView t = g.v;
-  const int64_t change = apply_count_block(t, g.gb);
-  if (threadIdx.x == 0) {
-    const bool erase = g.type == kOpErase;
-    chunk_feedback(t, erase ? 1 : 0, g.q, erase ? -change : change);
-    if (t.hdr->spec) t.hdr->ndup = listed_total(t);
+  const bool erase = g.type == kOpErase;
+  if (t.hdr->spec) {
+    if (threadIdx.x < 64) {
+      const uint64_t tot = spec_total(t);
+      if (threadIdx.x == 0) spec_settle(t, g.q, erase, tot);
+      spec_zero(t);
+    }
+    return;
   }
+  const int64_t change = apply_count_block(t, g.gb);
+  if (threadIdx.x == 0) chunk_feedback(t, erase ? 1 : 0, g.q, erase ? -change : change);
 }
 
 // Resolution of a speculative step (the single-table kernels' range code, per step).
 __device__ __forceinline__ void g_sclear_body(const GStep* __restrict__ st, const GLoc L) {
   const GStep& g = st[L.step];
   if (!g.v.hdr->spec) return;
-  spec_clear_range(g.v, g.q, L.lb, L.nblk);
+  spec_clear_range(g.v, g.q, g.v.hdr->ndup, L.lb, L.nblk);
 }
 
 __device__ __forceinline__ void g_sbuild_body(const GStep* __restrict__ st, const GLoc L) {
@@ -3316,10 +3298,9 @@ constexpr int kSpecGrid = 1024;
 
 template <int VK, bool ERASE>
 void spec_resolve(ct_table* t, const TableView& v, const uint64_t* kc, const void* vc, int64_t q,
-                  uint8_t* sc, int gb, uint32_t db, hipStream_t s) {
+                  uint8_t* sc, uint32_t db, hipStream_t s, int decided = 0) {
   const int g = std::min(flat_blocks(q), kSpecGrid);
-  launch(t, CT_KERNEL_APPLY, s, [&] { k_spec_sum<<<1, 1024, 0, s>>>(v, gb, q, ERASE ? 1 : 0); });
-  launch(t, CT_KERNEL_APPLY, s, [&] { k_spec_clear<<<std::min(flat_blocks(db / 2), kSpecGrid), kBlock, 0, s>>>(v, q); });
+  launch(t, CT_KERNEL_APPLY, s, [&] { k_spec_clear<<<std::min(flat_blocks(db / 2), kSpecGrid), kBlock, 0, s>>>(v, q, ERASE ? 1 : 0, decided); });
   launch(t, CT_KERNEL_DEDUP, s, [&] { k_spec_build<<<g, kBlock, 0, s>>>(v, kc, q); });
   launch(t, CT_KERNEL_FIX, s, [&] { k_spec_probe<VK, ERASE><<<g, kBlock, 0, s>>>(v, kc, vc, q, sc); });
   launch(t, CT_KERNEL_FIX, s, [&] { k_spec_swap<VK, ERASE><<<g, kBlock, 0, s>>>(v, kc, vc, q, sc); });
@@ -3349,9 +3330,8 @@ ct_status insert_chunks(ct_table* t, const BatchScratch& B, const uint64_t* keys
     }
     if (surely_fast && use_speculation(t, 0)) {
       // speculative: insert first, then resolve the copies of keys listed as ambiguous
-      launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_spec_prologue<<<1, 64, 0, s>>>(v, q, 1); });
-      launch(t, CT_KERNEL_INSERT, s, [&] { (q <= kAheadMax ? k_insert_spec<VK, true> : k_insert_spec<VK, false>)<<<gb, kBlock, 0, s>>>(v, kc, vc, q, sc); });
-      spec_resolve<VK, false>(t, v, kc, vc, q, sc, gb, db, s);
+      launch(t, CT_KERNEL_INSERT, s, [&] { (q <= kAheadMax ? k_insert_spec<VK, true> : k_insert_spec<VK, false>)<<<gb, kBlock, 0, s>>>(v, kc, vc, q, sc, 0); });
+      spec_resolve<VK, false>(t, v, kc, vc, q, sc, db, s);
       ct_status r = launched();
       if (r != CT_OK) return r;
       continue;
@@ -3360,9 +3340,9 @@ ct_status insert_chunks(ct_table* t, const BatchScratch& B, const uint64_t* keys
                         v.r1k && q >= kDeviceDecides;
     if (decided) {  // the speculative kernels first; whichever path is not taken leaves at once
       const int always = t->insert_path == CT_INSERT_SPECULATIVE;
-      launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_spec_decide<<<1, 64, 0, s>>>(v, q, always); });
-      launch(t, CT_KERNEL_INSERT, s, [&] { k_insert_spec<VK, false><<<gb, kBlock, 0, s>>>(v, kc, vc, q, sc); });
-      spec_resolve<VK, false>(t, v, kc, vc, q, sc, gb, db, s);
+      launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_spec_decide<<<1, 1, 0, s>>>(v, q, always); });
+      launch(t, CT_KERNEL_INSERT, s, [&] { k_insert_spec<VK, false><<<gb, kBlock, 0, s>>>(v, kc, vc, q, sc, 1); });
+      spec_resolve<VK, false>(t, v, kc, vc, q, sc, db, s, 1);
     }
     dedup_chunk(t, v, nullptr, kc, q, s, decided);
     launch(t, CT_KERNEL_INSERT, s, [&] { (q <= kAheadMax ? k_insert<VK, false, true> : k_insert<VK, false, false>)<<<gb, kBlock, 0, s>>>(v, kc, vc, q, db - 1, sc, nullptr, nullptr); });
@@ -3407,9 +3387,8 @@ ct_status erase_chunks(ct_table* t, const BatchScratch& B, ct_pool* p, const uin
     }
     if (!RELEASE && use_speculation(t, 1)) {
       // speculative: remove first, then move each removal to the lowest copy of its key
-      launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_spec_prologue<<<1, 64, 0, s>>>(v, q, 0); });
       launch(t, CT_KERNEL_ERASE, s, [&] { (q <= kAheadMax ? k_erase_spec<true> : k_erase_spec<false>)<<<gb, kBlock, 0, s>>>(v, kc, q, ec); });
-      spec_resolve<0, true>(t, v, kc, nullptr, q, ec, gb, db, s);
+      spec_resolve<0, true>(t, v, kc, nullptr, q, ec, db, s);
       ct_status r = launched();
       if (r != CT_OK) return r;
       continue;
@@ -3507,6 +3486,7 @@ ct_status ct_table_init(void* d_buf, int64_t bytes, const ct_table_desc* d, void
   v.nb = (uint64_t)L.nb;
   v.cap = (uint64_t)d->capacity;
   scratch_view(&v, base, L);
+  v.stripes = reinterpret_cast<uint64_t*>(base + L.off_bcnt + kMaxGroupBlocks * 8);
   v.hash = d->hash_kind;
   v.nb_pow2 = (L.nb & (L.nb - 1)) == 0;
   v.step_mode = v.nb_pow2 ? 1 : (is_prime(L.nb) ? 2 : 0);
