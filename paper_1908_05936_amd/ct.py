@@ -161,12 +161,19 @@ def _check(rc: int, what: str):
         raise CtError(f"{what}: {msg} ({rc})")
 
 
+# The current stream as the hipStream_t itself: torch.cuda.current_stream builds a Stream object on the
+# way, 1.9 of the 9.4 us that a lookup of 256 keys took on the host (0.1 this way).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(device) -> int:
+    if _raw_stream is not None and device.index is not None:
+        return _raw_stream(device.index)
     return torch.cuda.current_stream(device).cuda_stream
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _need(t, dtype, n, name, device):
