@@ -9,8 +9,9 @@
 //   kDevInsert  insert, find and contains, the same key from several threads included: a key is
 //               stored once, and exactly one of its inserters sees INSERTED.  Inserts claim only
 //               empty slots, never tombstones, and a slot never becomes empty again while the
-//               kernel runs, so every inserter of a key walks the same probe sequence to the same
-//               first empty slot.  A find of a key that another thread is inserting at that moment
+//               kernel runs, and inside a bucket the empty slots are asked for in an order fixed per
+//               key, so every inserter of a key walks the same sequence of slots to the same
+//               first empty one.  A find of a key that another thread is inserting at that moment
 //               may see the key before its value: the value is defined once the kernel has ended.
 //   kDevErase   erase, find and contains: each present key is removed once (exactly one of its
 //               erasers sees true).  An erase leaves an empty slot only where its bucket already
@@ -34,6 +35,7 @@
 #pragma once
 
 #include "ct_device.h"
+#include "ct_probe.h"
 
 namespace ct {
 
@@ -58,99 +60,202 @@ __device__ __forceinline__ uint64_t dev_key(const TableView& t, uint64_t pos) {
   return __hip_atomic_load(&t.bk[pos >> 3].s[pos & 7].key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// This lane's probe of `key` from slot `from` of its sequence (from = home * 8 at the start):
-// the key's slot, or kNoPos once a bucket with an empty slot ends the sequence (or every bucket
-// was seen); *empty gets the first empty slot at or after `from` in sequence order, else kNoPos.
+// Empty slots of a bucket are asked for from a slot that depends on the key (k-th in order: slot
+// (k + rot) & 7), so that keys of one bucket inserted at the same time mostly ask for different
+// slots.
+__device__ __forceinline__ uint32_t dev_rot(const Seq& sq) { return (uint32_t)(sq.step >> 1) & 7u; }
+
+// This lane's probe of `key` from position k0 (in the key's slot order) of bucket b on: the key's
+// slot, or kNoPos once a bucket with an empty slot ends the sequence (or every bucket was seen);
+// *empty gets the first empty slot in that order, else kNoPos.
 __device__ __forceinline__ uint64_t dev_probe(const TableView& t, uint64_t key, const Seq& sq,
-                                              uint64_t b, int c0, uint64_t* empty) {
+                                              uint64_t b, uint32_t k0, uint64_t* empty) {
   *empty = kNoPos;
+  const uint32_t rot = dev_rot(sq);
   for (uint64_t r = 0; r < t.nb; ++r) {
     // the bucket's eight key words in flight together, then the scan: the order of the reads
     // within a bucket does not matter, since a slot never returns to a state it has left
     uint64_t kk[kSlots];
 #pragma unroll
     for (int c = 0; c < kSlots; ++c) kk[c] = dev_key(t, b * kSlots + (uint64_t)c);
-    bool end = false;
+    uint32_t eq = 0, em = 0;
 #pragma unroll
     for (int c = 0; c < kSlots; ++c) {
-      if (c < c0) continue;
-      if (kk[c] == key) return b * kSlots + (uint64_t)c;
-      if (kk[c] == kEmpty && !end) {
-        end = true;
-        if (*empty == kNoPos) *empty = b * kSlots + (uint64_t)c;
-      }
+      if ((((uint32_t)c - rot) & 7u) < k0) continue;
+      eq |= kk[c] == key ? 1u << c : 0u;
+      em |= kk[c] == kEmpty ? 1u << c : 0u;
     }
-    if (end) return kNoPos;
-    c0 = 0;
+    if (eq) return b * kSlots + (uint64_t)__builtin_ctz(eq);
+    if (em) {
+      *empty = b * kSlots + (uint64_t)(((uint32_t)__builtin_ctz((em * 0x101u) >> rot) + rot) & 7u);
+      return kNoPos;
+    }
+    k0 = 0;
     b = next_bucket(t, b, sq.step);
   }
   return kNoPos;
 }
 
-// The same probe from the home bucket for a wave whose 64 lanes all call it together.  In step
-// r (0..7) lane v reads slot v & 7 of the bucket that owner lane 8r + (v >> 3) probes next, so
-// eight lanes read one 128-byte line together and a step of the wave makes 64 line requests
-// instead of 512.  Ballots hand each owner the eight comparisons of its bucket.  Owners whose
-// probe has ended read nothing useful (their lanes still read for the others), and the loop ends
-// when every owner has ended, after at most nb buckets each.
-__device__ __forceinline__ uint64_t dev_probe_wave(const TableView& t, uint64_t key, const Seq& sq,
-                                                   uint64_t* empty) {
-  const int lane = (int)wave_lane();
-  const int me_round = lane >> 3;        // the step in which this lane's bucket is read
-  const int me_shift = 8 * (lane & 7);   // and the ballot bits that hold its slots
-  uint64_t b = sq.home;
-  uint64_t res = kNoPos;
-  uint64_t seen = 0;
-  bool pending = true;
-  *empty = kNoPos;
-  for (;;) {
-    const uint64_t pm = __ballot(pending);
-    if (!pm) break;
-    uint64_t kk[kSlots];
+// NJ bucket reads of this lane's group of eight: bucket and key come from lane src0 + j * stride.
+template <int NJ>
+__device__ __forceinline__ uint32_t dev_lines(const TableView& t, uint64_t key, uint32_t b, uint32_t src0,
+                                              uint32_t stride, uint32_t last, int sub) {
+  uint64_t kk[NJ];
+  uint32_t x = 0;
 #pragma unroll
-    for (int r = 0; r < kSlots; ++r) {
-      const int o = 8 * r + (lane >> 3);
-      const uint64_t bo = __shfl(b, o, 64);
-      const bool po = (pm >> o) & 1ull;
-      // an ended owner's lanes read slot v & 7 of bucket 0: a load every lane makes, in bounds
-      kk[r] = dev_key(t, (po ? bo : 0ull) * kSlots + (uint64_t)(lane & 7));
-    }
-    uint32_t my_eq = 0, my_em = 0;
-#pragma unroll
-    for (int r = 0; r < kSlots; ++r) {
-      const int o = 8 * r + (lane >> 3);
-      const uint64_t ko = __shfl(key, o, 64);
-      const uint64_t eq = __ballot(kk[r] == ko);
-      const uint64_t em = __ballot(kk[r] == kEmpty);
-      if (r == me_round) {
-        my_eq = (uint32_t)(eq >> me_shift) & 0xFFu;
-        my_em = (uint32_t)(em >> me_shift) & 0xFFu;
-      }
-    }
-    if (pending) {
-      if (my_eq) {
-        res = b * kSlots + (uint64_t)__builtin_ctz(my_eq);
-        if (my_em && (uint32_t)__builtin_ctz(my_em) < (uint32_t)__builtin_ctz(my_eq))
-          *empty = b * kSlots + (uint64_t)__builtin_ctz(my_em);
-        pending = false;
-      } else if (my_em) {
-        *empty = b * kSlots + (uint64_t)__builtin_ctz(my_em);
-        pending = false;
-      } else if (++seen >= t.nb) {
-        pending = false;
-      } else {
-        b = next_bucket(t, b, sq.step);
-      }
-    }
+  for (int j = 0; j < NJ; ++j) {
+    const int src = (int)min(src0 + (uint32_t)j * stride, last);
+    kk[j] = dev_key(t, (uint64_t)(uint32_t)__shfl((int)b, src, 64) * kSlots + (uint64_t)sub);
   }
-  return res;
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const uint64_t key_j = __shfl(key, (int)min(src0 + (uint32_t)j * stride, last), 64);
+    x |= kk[j] == key_j ? 1u << j : 0u;
+    x |= kk[j] == kEmpty ? 1u << (kEmptyShift + j) : 0u;
+  }
+  return x;
 }
 
-// The probe from the home bucket: the whole wave together where it can, else lane by lane.
-__device__ __forceinline__ uint64_t dev_probe_home(const TableView& t, uint64_t key, const Seq& sq,
-                                                   uint64_t* empty) {
-  if (__ballot(1) == ~0ull) return dev_probe_wave(t, key, sq, empty);
-  return dev_probe(t, key, sq, sq.home, 0, empty);
+// Slot bits (kBitsMatch, kEmptyShift) of bucket `b` for every lane with `look` set; `mask` is the ballot
+// of `look`, not zero, and all 64 lanes call it together.  Eight lanes read one bucket, and past
+// the first round the lanes that still look are packed, as in the batch kernels' ProbeRound; keys
+// and buckets move between lanes by cross-lane moves, so that a user's kernel spends no LDS on it.
+// 2^23 keys inserted into an empty table, looked up and a quarter erased through ct_dev_apply (load
+// 0.8 at the end): 1.19 ms with a ballot per bucket, ended lanes read again and lost claims
+// continued lane by lane; 1.06 ms now (600, 309 and 101 us).  The inserts run at 14 G keys/s, where a
+// gather, a claim and a store at random reach 18.
+__device__ __forceinline__ uint32_t dev_round(const TableView& t, uint64_t mask, bool look, uint64_t key,
+                                              uint32_t b) {
+  const int lane = wave_lane();
+  const int sub = lane & 7;
+  const uint32_t g = (uint32_t)lane >> 3;
+  const uint32_t n = (uint32_t)__builtin_popcountll(mask);
+  if (n > 32)  // this group's own eight lanes
+    return transpose8(dev_lines<8>(t, key, b, 8u * g, 1u, 63u, sub), sub);
+  const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+  // lane `rank` gets this lane's key and bucket; a lane that does not look sends to the last lane,
+  // which at most 32 looking lanes never read
+  const int to = (int)((look ? rank : 63u) << 2);
+  const uint32_t klo = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)(uint32_t)key);
+  const uint32_t khi = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)(uint32_t)(key >> 32));
+  const uint32_t bb = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)b);
+  const uint64_t kk = (uint64_t)klo | ((uint64_t)khi << 32);
+  uint32_t x;
+  if (n > 16) x = dev_lines<4>(t, kk, bb, g, 8u, n - 1u, sub);
+  else if (n > 8) x = dev_lines<2>(t, kk, bb, g, 8u, n - 1u, sub);
+  else x = dev_lines<1>(t, kk, bb, g, 8u, n - 1u, sub);
+  x = transpose8(x, sub);  // lane (g, s) now answers item s * 8 + g
+  return (uint32_t)__shfl((int)x, (int)(((rank & 7u) << 3) | ((rank >> 3) & 7u)), 64);
+}
+
+// Where the keys of a whole wave are, or where they go: every lane with `look` set walks its key's
+// sequence to the key (found) or to the first bucket with an empty slot; with CLAIM it then takes
+// an empty slot, and `found` also tells that another thread stored the key first.  All 64 lanes
+// call it together and stay until every lane has ended.
+//
+// A claim that loses goes on to the bucket's next empty slot in the key's order without reading it
+// again: slots only go from empty to a key (and on to a tombstone), so a slot that another inserter
+// of the key found taken is one that this lane asks for and loses too, and a slot that holds the
+// key answers the claim with it.
+struct DevPlace {
+  bool found, had_empty;
+  uint64_t pos;  // slot of the key or of the claim; kNoPos: none
+};
+
+template <bool CLAIM>
+__device__ __forceinline__ DevPlace dev_place_wave(const TableView& t, uint64_t key, bool look) {
+  DevPlace r = {false, false, kNoPos};
+  const Seq sq = probe_seq(t, key);
+  const uint32_t step = (uint32_t)sq.step, rot = dev_rot(sq);
+  uint32_t b = (uint32_t)sq.home, left = (uint32_t)t.nb;
+  for (uint64_t mask = __ballot(look); mask; mask = __ballot(look)) {
+    const uint32_t x = dev_round(t, mask, look, key, b);
+    if (!look) continue;
+    uint32_t em = (x >> kEmptyShift) & 0xFFu;
+    if (x & kBitsMatch) {
+      r.found = true;
+      r.had_empty = em != 0;
+      r.pos = (uint64_t)b * kSlots + (uint64_t)__builtin_ctz(x & kBitsMatch);
+      look = false;
+      continue;
+    }
+    if (CLAIM) {
+      bool claiming = em != 0;
+      while (claiming) {
+        const uint32_t c = ((uint32_t)__builtin_ctz((em * 0x101u) >> rot) + rot) & 7u;
+        uint64_t expected = kEmpty;
+        if (cas64(&t.bk[b].s[c].key, expected, key)) {
+          r.pos = (uint64_t)b * kSlots + c;
+          look = claiming = false;
+        } else if (expected == key) {
+          r.found = true;
+          look = claiming = false;
+        } else {
+          em &= ~(1u << c);
+          claiming = em != 0;
+        }
+      }
+    } else if (em) {
+      look = false;
+    }
+    look = look && --left != 0;
+    b = next_bucket32(t, b, step);
+  }
+  return r;
+}
+
+// The slot of `key`, kNoPos when it is absent: the whole wave together where it can, else lane by
+// lane.  EMPTY: *had_empty tells whether its bucket holds an empty slot.  `look` false: no answer
+// wanted.
+template <bool EMPTY>
+__device__ __forceinline__ uint64_t dev_slot_of(const TableView& t, uint64_t key, bool look,
+                                                bool* had_empty) {
+  if (__ballot(1) == ~0ull) {
+    const DevPlace p = dev_place_wave<false>(t, key, look);
+    *had_empty = p.had_empty;
+    return p.found ? p.pos : kNoPos;
+  }
+  *had_empty = false;
+  if (!look) return kNoPos;
+  const Seq sq = probe_seq(t, key);
+  uint64_t empty;
+  const uint64_t pos = dev_probe(t, key, sq, sq.home, 0, &empty);
+  if (EMPTY && pos != kNoPos)
+    for (int c = 0; c < kSlots; ++c) *had_empty |= dev_key(t, (pos & ~7ull) + (uint64_t)c) == kEmpty;
+  return pos;
+}
+
+// Claims an empty slot on the sequence of `key`: the slot, or kNoPos with *present telling whether the
+// key is stored already (else no empty slot is left).
+__device__ __forceinline__ uint64_t dev_claim(const TableView& t, uint64_t key, bool look, bool* present) {
+  *present = false;
+  if (__ballot(1) == ~0ull) {
+    const DevPlace p = dev_place_wave<true>(t, key, look);
+    *present = p.found;
+    return p.found ? kNoPos : p.pos;
+  }
+  if (!look) return kNoPos;
+  const Seq sq = probe_seq(t, key);
+  uint64_t empty;
+  *present = dev_probe(t, key, sq, sq.home, 0, &empty) != kNoPos;
+  while (!*present && empty != kNoPos) {
+    uint64_t expected = kEmpty;
+    if (cas64(&t.bk[empty >> 3].s[empty & 7].key, expected, key)) return empty;
+    if (expected == key) {  // another thread stored it in the same first empty slot
+      *present = true;
+      break;
+    }
+    // another key took the slot: go on from the next slot of the sequence
+    uint64_t b = empty >> 3;
+    uint32_t k = (((uint32_t)(empty & 7) - dev_rot(sq)) & 7u) + 1u;
+    if (k == (uint32_t)kSlots) {
+      k = 0;
+      b = next_bucket(t, b, sq.step);
+    }
+    *present = dev_probe(t, key, sq, b, k, &empty) != kNoPos;
+  }
+  return kNoPos;
 }
 
 // The wave's lanes that reach this call add `sign` each to the live count (or to their stripe).
@@ -207,6 +312,8 @@ __device__ __forceinline__ bool dev_reserve(const DevView& v) {
 template <class Take>
 __device__ inline uint8_t dev_insert_mixed(const DevView& v, uint64_t key, Take take) {
   const TableView& t = v.t;
+  bool present;
+  const uint64_t pos = dev_claim(t, key, key < kTomb, &present);
   if (key >= kTomb) {
     const int s = (int)(key - kTomb);
     uint32_t* live = &t.hdr->spec_live[s];
@@ -229,37 +336,22 @@ __device__ inline uint8_t dev_insert_mixed(const DevView& v, uint64_t key, Take 
     t.hdr->spec_val[s] = val;
     return kInserted;
   }
-  const Seq sq = probe_seq(t, key);
-  uint64_t empty;
-  if (dev_probe_home(t, key, sq, &empty) != kNoPos) return kPresent;
-  for (;;) {
-    if (empty == kNoPos) return kFull;  // no empty slot left on the key's sequence
-    uint64_t* kw = &t.bk[empty >> 3].s[empty & 7].key;
-    uint64_t expected = kEmpty;
-    if (cas64(kw, expected, key)) {
-      uint64_t val = 0;
-      const bool unit = dev_reserve(v);
-      if (!unit || !take(&val)) {
-        expected = key;
-        if (cas64(kw, expected, kTomb)) {
-          if (unit) dev_uncount(v);
-          return kFull;
-        }
-        if (!unit) dev_count(v);  // erased after the claim: that erase returned this unit
-        return kInserted;
-      }
-      t.bk[empty >> 3].s[empty & 7].val = val;
-      return kInserted;
+  if (present) return kPresent;
+  if (pos == kNoPos) return kFull;  // no empty slot left on the key's sequence
+  uint64_t* kw = &t.bk[pos >> 3].s[pos & 7].key;
+  uint64_t val = 0;
+  const bool unit = dev_reserve(v);
+  if (!unit || !take(&val)) {
+    uint64_t expected = key;
+    if (cas64(kw, expected, kTomb)) {
+      if (unit) dev_uncount(v);
+      return kFull;
     }
-    if (expected == key) return kPresent;
-    uint64_t b = empty >> 3;
-    int c = (int)(empty & 7) + 1;
-    if (c == kSlots) {
-      c = 0;
-      b = next_bucket(t, b, sq.step);
-    }
-    if (dev_probe(t, key, sq, b, c, &empty) != kNoPos) return kPresent;
+    if (!unit) dev_count(v);  // erased after the claim: that erase returned this unit
+    return kInserted;
   }
+  t.bk[pos >> 3].s[pos & 7].val = val;
+  return kInserted;
 }
 
 // The insert, with the stored value produced after the claim: `take(&value)` runs once the thread
@@ -271,6 +363,8 @@ template <class Take>
 __device__ inline uint8_t dev_insert_with(const DevView& v, uint64_t key, Take take) {
   const TableView& t = v.t;
   if (v.mode == kDevMixed) return dev_insert_mixed(v, key, take);
+  bool present;
+  const uint64_t pos = dev_claim(t, key, key < kTomb, &present);
   if (key >= kTomb) {  // out-of-band keys live in the header
     const int s = (int)(key - kTomb);
     uint32_t expected = 0;
@@ -290,37 +384,21 @@ __device__ inline uint8_t dev_insert_with(const DevView& v, uint64_t key, Take t
     t.hdr->spec_val[s] = val;
     return kInserted;
   }
-  const Seq sq = probe_seq(t, key);
-  uint64_t empty;
-  if (dev_probe_home(t, key, sq, &empty) != kNoPos) return kPresent;
-  for (;;) {
-    if (empty == kNoPos) return kFull;  // every bucket holds keys or tombstones
-    uint64_t* kw = &t.bk[empty >> 3].s[empty & 7].key;
-    uint64_t expected = kEmpty;
-    if (cas64(kw, expected, key)) {
-      uint64_t val = 0;
-      if (!dev_reserve(v)) {
-        __hip_atomic_store(kw, kTomb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return kFull;
-      }
-      if (!take(&val)) {
-        dev_uncount(v);
-        __hip_atomic_store(kw, kTomb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return kFull;
-      }
-      t.bk[empty >> 3].s[empty & 7].val = val;
-      return kInserted;
-    }
-    if (expected == key) return kPresent;  // another thread stored it in the same first empty slot
-    // another key took the slot: go on from the next slot of the sequence
-    uint64_t b = empty >> 3;
-    int c = (int)(empty & 7) + 1;
-    if (c == kSlots) {
-      c = 0;
-      b = next_bucket(t, b, sq.step);
-    }
-    if (dev_probe(t, key, sq, b, c, &empty) != kNoPos) return kPresent;
+  if (present) return kPresent;
+  if (pos == kNoPos) return kFull;  // every bucket holds keys or tombstones
+  uint64_t* kw = &t.bk[pos >> 3].s[pos & 7].key;
+  uint64_t val = 0;
+  if (!dev_reserve(v)) {
+    __hip_atomic_store(kw, kTomb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return kFull;
   }
+  if (!take(&val)) {
+    dev_uncount(v);
+    __hip_atomic_store(kw, kTomb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return kFull;
+  }
+  t.bk[pos >> 3].s[pos & 7].val = val;
+  return kInserted;
 }
 
 __device__ inline uint8_t dev_insert(const DevView& v, uint64_t key, uint64_t val) {
@@ -333,6 +411,8 @@ __device__ inline uint8_t dev_insert(const DevView& v, uint64_t key, uint64_t va
 // Whether the key was present (and is now removed).
 __device__ inline bool dev_erase(const DevView& v, uint64_t key) {
   const TableView& t = v.t;
+  bool had_empty;
+  const uint64_t pos = dev_slot_of<true>(t, key, key < kTomb, &had_empty);
   if (key >= kTomb) {
     const int s = (int)(key - kTomb);
     uint32_t expected = 1;
@@ -342,16 +422,12 @@ __device__ inline bool dev_erase(const DevView& v, uint64_t key) {
     dev_uncount(v);
     return true;
   }
-  const Seq sq = probe_seq(t, key);
-  uint64_t empty;
-  const uint64_t pos = dev_probe_home(t, key, sq, &empty);
   if (pos == kNoPos) return false;
   // an empty slot only where the bucket already holds one, and never while inserts run
-  bool has_empty = false;
-  if (v.mode != kDevMixed)
-    for (int c = 0; c < kSlots; ++c) has_empty |= dev_key(t, (pos & ~7ull) + (uint64_t)c) == kEmpty;
   uint64_t expected = key;
-  if (!cas64(&t.bk[pos >> 3].s[pos & 7].key, expected, has_empty ? kEmpty : kTomb)) return false;
+  if (!cas64(&t.bk[pos >> 3].s[pos & 7].key, expected,
+             had_empty && v.mode != kDevMixed ? kEmpty : kTomb))
+    return false;
   dev_uncount(v);
   return true;
 }
@@ -359,15 +435,14 @@ __device__ inline bool dev_erase(const DevView& v, uint64_t key) {
 // Whether the key is present; *val (nullable) gets its value.
 __device__ inline bool dev_find(const DevView& v, uint64_t key, uint64_t* val) {
   const TableView& t = v.t;
+  bool had_empty;
+  const uint64_t pos = dev_slot_of<false>(t, key, key < kTomb, &had_empty);
   if (key >= kTomb) {
     const int s = (int)(key - kTomb);
     if (!__hip_atomic_load(&t.hdr->spec_live[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return false;
     if (val) *val = t.hdr->spec_val[s];
     return true;
   }
-  const Seq sq = probe_seq(t, key);
-  uint64_t empty;
-  const uint64_t pos = dev_probe_home(t, key, sq, &empty);
   if (pos == kNoPos) return false;
   if (val) *val = t.bk[pos >> 3].s[pos & 7].val;
   return true;
