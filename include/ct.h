@@ -424,11 +424,13 @@ ct_status ct_erase_release_batch(ct_table *t, ct_pool *p, const uint64_t *keys, 
 /* A table that left its chunk to the library (chunk 0) holds scratch for chunks of about capacity /
    8 keys, so a batch that fills it runs as eight or more chunks, each with its own launches.  With
    a workspace (device memory of ct_workspace_bytes, 256-byte aligned, for this call's use until the
-   work enqueued by it has run) the batch runs in larger chunks.  Results are the same.
+   work enqueued by it has run) the batch runs in larger chunks, and a large insert of several keys
+   per bucket brings the keys to the buckets.  Results are the same.
 
-   *bytes: what a batch of n keys can use; 0 when the table's own scratch serves it (a batch of one
-   chunk, a chunk that the caller chose, or the large chunks of the largest tables).  Host only. */
-ct_status ct_workspace_bytes(const ct_table *t, int64_t n, int64_t *bytes);
+   *bytes: what a batch of n keys can use now, for an insert (CT_OP_INSERT; also insert_alloc) or an
+   erase (CT_OP_ERASE); 0 when the table's own scratch serves it (a batch of one chunk, a chunk that
+   the caller chose, or the large chunks of the largest tables).  Host only. */
+ct_status ct_workspace_bytes(const ct_table *t, int32_t op, int64_t n, int64_t *bytes);
 
 /* ct_insert_batch, ct_erase_batch, ct_insert_alloc_batch (skip NULL) or ct_insert_alloc_batch_masked,
    and ct_erase_release_batch.  ws may be NULL, and a workspace smaller than ct_workspace_bytes is

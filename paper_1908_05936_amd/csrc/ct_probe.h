@@ -182,13 +182,18 @@ struct Place {
 
 template <bool CLAIM, bool VAL, bool AHEAD>
 __device__ __forceinline__ Place place_keys(const TableView& t, WaveLds* w, bool look, uint64_t key,
-                                            bool claim, uint32_t inject, uint64_t id) {
+                                            bool claim, uint32_t inject, uint64_t id,
+                                            bool home_full = false) {
   Place r = {false, false, kNoPos, 0};
   const Seq q = probe_seq(t, key);
   const uint32_t step = (uint32_t)q.step;
   uint32_t b = (uint32_t)q.home, left = (uint32_t)t.nb;
   uint32_t fb = kNone, fleft = 0;           // first bucket with a free slot on the path
   uint32_t fe = 0, ft = 0;                  // its empty slots and tombstones
+  if (home_full) {  // known: begin at the second bucket of the path
+    b = next_bucket32(t, b, step);
+    look = look && --left != 0;
+  }
   bool forced = CLAIM && inject && id % inject == 0;  // test hook: the first claim counts as lost
   for (uint64_t mask = __ballot(look); mask; mask = __ballot(look)) {
     const ProbeRound<CLAIM, VAL, AHEAD> round(t, w, mask, look, key, b, step);

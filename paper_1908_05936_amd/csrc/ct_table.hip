@@ -21,11 +21,13 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "ct.h"
@@ -944,7 +946,7 @@ __global__ __launch_bounds__(1024) void k_apply_count(TableView t, int nblocks, 
 // out-of-band keys are always listed and resolved by one thread.  With distinct keys absent from
 // the table nothing is listed, and the resolution kernels return at once.
 // ---------------------------------------------------------------------------------------------
-enum : uint8_t { kFlagNone = 0, kFlagClaimed = 1, kFlagListed = 2 };
+enum : uint8_t { kFlagNone = 0, kFlagClaimed = 1, kFlagListed = 2, kFlagLeft = 3, kFlagSure = 4 };
 
 // A speculative chunk's counts: every block adds (elements stored or removed << 32 | listed) to one
 // of kCountStripes words on separate 128-byte lines of the table, which are zero between batches.
@@ -1395,6 +1397,407 @@ __global__ __launch_bounds__(kBlock) void k_spec_swap(TableView t, const uint64_
                                                       uint8_t* __restrict__ status) {
   if (blockIdx.x == 0) spec_zero(t);  // for the next batch
   spec_swap_range<VK, ERASE>(t, keys, vals, q, status, blockIdx.x, gridDim.x);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Partitioned insert: a speculative insert of a large batch with several keys per bucket.
+//
+// What bounds the plain one is the claim: a gather, a 64-bit compare-and-swap at the memory side and a
+// store into a random line, 18 G/s on this chip at most.  When the batch holds several keys per
+// bucket, it is cheaper to bring the keys to the buckets: they move, by the high bits of their home
+// bucket, into coarse and then fine bins of kPartBuckets buckets each; a workgroup loads a fine
+// bin's buckets into LDS, claims slots there with LDS compare-and-swaps, and writes the buckets back.
+// Every access to memory is a stream.  2^26 keys with 64-bit values filling a table to load 0.8
+// (clearing it and looking 2^22 keys up included): 4.33 ms plain, 2.98 partitioned.
+//
+// An element whose home bucket holds its key is present; one whose home bucket shows an empty slot is
+// absent from the table and claims there.  Copies of a key meet in one fine bin: while a bucket is
+// in LDS, the value word of a slot claimed from the batch holds the lowest batch index that
+// asked for its key, and that element stores the key and its value.  (Leaving copies to the
+// speculative insert's resolution: 2^24 keys of 2^21 distinct took 2.7 ms, 1.1 plain.)
+// Every other element is left over and placed by the ordinary probe afterwards: those whose home bucket
+// is full (one in fourteen at load 0.8) through a list per coarse bin, which takes the place of the
+// bin's own elements, and the rare rest (home bucket full but for tombstones; no room in a bin,
+// which takes keys repeated very often) by a mark in their flags.  Only copies of those can be left
+// unresolved; they end listed, and the speculative insert's resolution pairs them with the claimers.
+// The buckets of a fine bin belong to one workgroup while the bins are inserted, and nothing else
+// runs on the table.
+// Copies of a key may meet in different kernels, each of which sees the claims of those before it.
+// Within one, free slots of a bucket only become keys, and all copies ask for them in the same
+// order, so a copy finds the key, loses its claim to it, or finds the bucket full like every later
+// copy.
+// ---------------------------------------------------------------------------------------------
+constexpr int kPartBits = 8;
+constexpr int kPartBuckets = 1 << kPartBits;   // buckets of a fine bin: 34 KB of LDS
+constexpr int kPartStride = 2 * kSlots + 1;    // u64 words of a bucket in LDS (odd: lanes spread)
+constexpr int kPartThreads = 512;
+constexpr int kPartPer = 5;                    // elements of a fine bin a thread, at most
+constexpr int kPartLeft = 512;                 // left-over positions gathered in LDS per fine bin
+constexpr int kPartWindow = 8 * kBlock;        // flags that a block looks over at a time
+constexpr int kPartXcds = 8;                   // blocks go to the chip's L2 domains in turn
+constexpr int kPartCtr = kBinSub * kCtrStride; // counter words of a coarse bin (one line a segment)
+
+struct PartView {
+  uint64_t *r1k, *r2k;   // keys, values and batch indices of the coarse and the fine bins
+  void *r1v, *r2v;
+  uint32_t *r1i, *r2i;
+  uint32_t *cur1, *cur2; // fill counts: coarse segments kCtrStride words apart, fine bins
+  uint32_t *nleft;       // left-over elements of each coarse bin, kCtrStride words apart
+  uint32_t *nover;       // 1: some element is marked kFlagLeft, or listed
+  uint8_t* flag;         // by batch index: kFlagLeft for elements that found no room in a bin;
+                         // kFlagSure for claimers while no copy of any key may be listed
+  uint32_t c1, c2;       // capacities of a coarse segment and of a fine bin
+  int lp2;               // log2 of the fine bins of a coarse bin
+};
+
+__device__ __forceinline__ uint32_t home32(const TableView& t, uint64_t key) {
+  return (uint32_t)scale32(fmix64(key), t.nb);
+}
+
+template <int VK>
+struct PartStage {
+  uint64_t k[kBinTile];
+  typename std::conditional<VK == 1, uint32_t, uint64_t>::type v[VK ? kBinTile : 1];
+  uint32_t i[kBinTile];
+  uint8_t b[kBinTile];
+  uint32_t cnt[256], base[256], loc[256];
+};
+
+// The block's staged elements (code = rank << 8 | bin, ~0 for none) go to the bins in runs of
+// consecutive positions, as bin_write does; an element past a bin's capacity is left over.
+template <int VK, int PER>
+__device__ __forceinline__ void part_write(const PartView& P, PartStage<VK>& S, uint32_t nbins,
+                                           const uint64_t (&k)[PER], const uint64_t (&v)[PER],
+                                           const uint32_t (&ix)[PER], const uint32_t (&code)[PER],
+                                           uint32_t* cur, uint32_t cur_stride, int64_t bin0,
+                                           uint32_t bin_stride, uint32_t cap, uint64_t* outk,
+                                           void* outv, uint32_t* outi) {
+  const uint32_t c = threadIdx.x < nbins ? S.cnt[threadIdx.x] : 0u;
+  uint32_t total;
+  const uint32_t pre = block_exclusive_scan(c, &total);
+  if (threadIdx.x < nbins) {
+    S.base[threadIdx.x] = c ? aadd32(&cur[threadIdx.x * cur_stride], c) : 0u;
+    S.loc[threadIdx.x] = pre;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    if (code[e] == ~0u) continue;
+    const uint32_t b = code[e] & 0xFFu;
+    const uint32_t p = S.loc[b] + (code[e] >> 8);
+    S.k[p] = k[e];
+    if (VK) S.v[p] = (decltype(S.v[0] + 0))v[e];
+    S.i[p] = ix[e];
+    S.b[p] = (uint8_t)b;
+  }
+  __syncthreads();
+  const uint32_t staged = min(total, (uint32_t)kBinTile);
+  for (uint32_t p = threadIdx.x; p < staged; p += kBlock) {
+    const uint32_t b = S.b[p];
+    const uint32_t pos = S.base[b] + (p - S.loc[b]);
+    if (pos < cap) {
+      const int64_t at = (bin0 + (int64_t)b * bin_stride) * cap + pos;
+      outk[at] = S.k[p];
+      if (VK) store_val<VK>(outv, at, S.v[p]);
+      outi[at] = S.i[p];
+    } else {
+      P.flag[S.i[p]] = kFlagLeft;
+      *P.nover = 1;
+    }
+  }
+}
+
+// Coarse scatter, one tile of kBinTile elements per block into segment block mod kBinSub.  Statuses and
+// flags start as those of a claimer; the kernels that follow write the exceptions.  Bound by
+// memory: 38 bytes a key with 64-bit values, 2^26 keys in 0.65 ms, 3.9 TB/s.
+template <int VK>
+__global__ __launch_bounds__(kBlock) void k_part_coarse(TableView t, PartView P,
+                                                        const uint64_t* __restrict__ keys,
+                                                        const void* __restrict__ vals, int64_t n,
+                                                        int ncoarse, uint8_t* __restrict__ status) {
+  constexpr int kPer = kBinTile / kBlock;
+  __shared__ PartStage<VK> S;
+  const int64_t t0 = (int64_t)blockIdx.x * kBinTile;
+  uint64_t k[kPer], v[kPer];
+  uint32_t ix[kPer], code[kPer];
+#pragma unroll
+  for (int e = 0; e < kPer; ++e) {   // loads first, clamped
+    const int64_t i = min(t0 + e * kBlock + (int64_t)threadIdx.x, n - 1);
+    k[e] = keys[i];
+    v[e] = load_val<VK>(vals, i);
+  }
+  S.cnt[threadIdx.x] = 0;
+  __syncthreads();
+  int64_t special = 0;
+#pragma unroll
+  for (int e = 0; e < kPer; ++e) {
+    const int64_t i = t0 + e * kBlock + threadIdx.x;
+    code[e] = ~0u;
+    ix[e] = (uint32_t)i;
+    if (i >= n) continue;
+    const bool normal = k[e] < kTomb;
+    P.flag[i] = normal ? kFlagSure : kFlagListed;
+    if (status) status[i] = normal ? kInserted : kPresent;
+    if (normal) {
+      const uint32_t b = home32(t, k[e]) >> (kPartBits + P.lp2);
+      code[e] = (atomicAdd(&S.cnt[b], 1u) << 8) | b;
+    } else {
+      ++special;
+    }
+  }
+  const int64_t listed = block_sum(special);  // (a barrier between the counts and their use)
+  if (threadIdx.x == 0) spec_count(t, blockIdx.x, listed);
+  __syncthreads();
+  const uint32_t seg = blockIdx.x % kBinSub;
+  part_write<VK, kPer>(P, S, (uint32_t)ncoarse, k, v, ix, code, P.cur1 + seg * kCtrStride, kPartCtr, seg,
+                       kBinSub, P.c1, P.r1k, P.r1v, P.r1i);
+}
+
+// Fine scatter of the coarse bins from `coarse0` on: the blocks of a segment take its tiles in turn.
+// The fine bins of these coarse bins start at r2's beginning.  A tile leaves about eight elements
+// to each fine bin, half a line; blocks of one coarse bin share an L2 (blockIdx modulo kPartXcds),
+// where those halves meet before they go to memory: 2^26 keys took 1.08 ms with the segments'
+// blocks on all of them and take 0.67, 4.0 TB/s.
+template <int VK>
+__global__ __launch_bounds__(kBlock) void k_part_fine(TableView t, PartView P, int coarse0,
+                                                      int ncoarse, int blocks_per_seg) {
+  constexpr int kPer = kBinTile / kBlock;
+  __shared__ PartStage<VK> S;
+  const int r = (int)blockIdx.x / kPartXcds, per = kBinSub * blocks_per_seg;
+  const int c = coarse0 + r / per * kPartXcds + (int)blockIdx.x % kPartXcds;
+  if (c >= ncoarse) return;
+  const int64_t seg = (int64_t)c * kBinSub + r % per / blocks_per_seg;
+  const uint32_t n1 = min(P.cur1[seg * kCtrStride], P.c1);
+  const int64_t src = seg * P.c1;
+  const uint32_t nf = 1u << P.lp2;
+  for (uint32_t j0 = (uint32_t)(r % blocks_per_seg) * kBinTile; j0 < n1;
+       j0 += (uint32_t)blocks_per_seg * kBinTile) {
+    uint64_t k[kPer], v[kPer];
+    uint32_t ix[kPer], code[kPer];
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {   // loads first, clamped (n1 > j0 >= 0)
+      const uint32_t j = min(j0 + e * kBlock + threadIdx.x, n1 - 1u);
+      k[e] = P.r1k[src + j];
+      v[e] = load_val<VK>(P.r1v, src + j);
+      ix[e] = P.r1i[src + j];
+    }
+    S.cnt[threadIdx.x] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+      code[e] = ~0u;
+      if (j0 + e * kBlock + threadIdx.x < n1) {
+        const uint32_t b = (home32(t, k[e]) >> kPartBits) & (nf - 1u);
+        code[e] = (atomicAdd(&S.cnt[b], 1u) << 8) | b;
+      }
+    }
+    __syncthreads();
+    part_write<VK, kPer>(P, S, nf, k, v, ix, code, P.cur2 + ((uint32_t)c << P.lp2), 1u,
+                         (int64_t)(c - coarse0) << P.lp2, 1u, P.c2, P.r2k, P.r2v, P.r2i);
+    __syncthreads();  // the stage is refilled by the next tile
+  }
+}
+
+// One fine bin per block: its buckets in LDS, claims there, buckets back.  Bound by memory: 20
+// bytes a key and the buckets both ways, 2^26 keys into 2^26/0.8 slots in 0.89 ms, 4.5 TB/s.
+// Reading the elements ahead of the buckets' barrier gained nothing: four blocks a CU cover it.
+template <int VK>
+__global__ __launch_bounds__(kPartThreads) void k_part_insert(TableView t, PartView P, int coarse0,
+                                                              uint8_t* __restrict__ status) {
+  __shared__ uint64_t L[kPartBuckets * kPartStride];
+  __shared__ uint32_t left[kPartLeft], nleft, lbase;
+  const int64_t fl = ((int64_t)(blockIdx.x / (kPartXcds << P.lp2) * kPartXcds + blockIdx.x % kPartXcds) << P.lp2) +
+                     (blockIdx.x / kPartXcds & ((1u << P.lp2) - 1u));  // fine bin within the group
+  const int64_t f = ((int64_t)coarse0 << P.lp2) + fl;
+  const int64_t b0 = f << kPartBits;
+  if (b0 >= (int64_t)t.nb) return;
+  const uint32_t n = min(P.cur2[f], P.c2);
+  if (n == 0) return;
+  const int64_t src = fl * P.c2;
+  const int nslots = (int)min((int64_t)kPartBuckets, (int64_t)t.nb - b0) * kSlots;
+  Slot* slots = t.bk[b0].s;  // the bin's buckets are contiguous
+  for (int j = threadIdx.x; j < nslots; j += kPartThreads) {
+    const Slot sl = slots[j];
+    uint64_t* w = &L[(j >> 3) * kPartStride + 2 * (j & 7)];
+    const bool taken = sl.key < kTomb;
+    w[0] = sl.key;
+    w[1] = taken ? sl.val : ~0ull;
+    const uint64_t mask = __ballot(taken) >> (threadIdx.x & 56u);  // the bucket's slots taken before
+    if ((j & 7) == 0) L[(j >> 3) * kPartStride + 2 * kSlots] = mask & 0xFFu;
+  }
+  if (threadIdx.x == 0) nleft = 0;
+  __syncthreads();
+  uint32_t claimed = 0;
+  uint64_t val[kPartPer];
+  uint32_t idx[kPartPer], slot[kPartPer];  // slot: LDS word of the value; 0: none
+#pragma unroll
+  for (int e = 0; e < kPartPer; ++e) {
+    slot[e] = 0;
+    const uint32_t j = threadIdx.x + e * kPartThreads;
+    if (j >= n) continue;
+    const uint64_t key = P.r2k[src + j];
+    val[e] = load_val<VK>(P.r2v, src + j);
+    idx[e] = P.r2i[src + j];
+    const uint32_t at = (home32(t, key) & (kPartBuckets - 1u)) * kPartStride;
+    unsigned long long* w = reinterpret_cast<unsigned long long*>(&L[at]);
+    uint32_t m = 0, em = 0, tb = 0;
+#pragma unroll
+    for (int c = 0; c < kSlots; ++c) {
+      const uint64_t x = w[2 * c];
+      m |= x == key ? 1u << c : 0u;
+      em |= x == kEmpty ? 1u << c : 0u;
+      tb |= x == kTomb ? 1u << c : 0u;
+    }
+    uint32_t c = m ? (uint32_t)__builtin_ctz(m) : 0u;
+    bool met = m != 0, over = !met && !em, full = over && !tb;
+    bool won = false;
+    while (!met && !over && !won) {  // absent: every pass takes a slot or learns that it is gone
+      const uint32_t fr = tb ? tb : em;
+      const uint32_t rot = (uint32_t)(key >> 61);
+      c = ((uint32_t)__builtin_ctz((fr * 0x101u) >> rot) + rot) & 7u;
+      const unsigned long long want = tb ? kTomb : kEmpty;
+      const unsigned long long got = atomicCAS(&w[2 * c], want, (unsigned long long)key);
+      won = got == want;
+      met = got == key;
+      em &= ~(1u << c);
+      tb &= ~(1u << c);
+      over = full = !met && !won && !(em | tb);
+    }
+    claimed += won;
+    if (over) {
+      const uint32_t p = full ? atomicAdd(&nleft, 1u) : ~0u;
+      if (p < (uint32_t)kPartLeft) {
+        left[p] = j;
+      } else {
+        P.flag[idx[e]] = kFlagLeft;
+        *P.nover = 1;
+      }
+    } else if (w[2 * kSlots] >> c & 1u) {  // there before the batch
+      P.flag[idx[e]] = kFlagNone;
+      if (status) status[idx[e]] = kPresent;
+    } else {
+      slot[e] = at + 2 * c + 1;
+      atomicMin(&w[2 * c + 1], (unsigned long long)idx[e]);
+    }
+  }
+  __syncthreads();
+  const uint32_t c = (uint32_t)(f >> P.lp2);
+  const uint32_t nl = min(nleft, (uint32_t)kPartLeft);
+  if (threadIdx.x == 0 && nl) lbase = aadd32(&P.nleft[c * kCtrStride], nl);
+#pragma unroll
+  for (int e = 0; e < kPartPer; ++e) {
+    if (slot[e] && L[slot[e]] != idx[e]) {  // a lower copy stores the key
+      slot[e] = 0;
+      P.flag[idx[e]] = kFlagNone;
+      if (status) status[idx[e]] = kPresent;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < kPartPer; ++e)
+    if (slot[e]) L[slot[e]] = VK ? val[e] : 0;
+  __syncthreads();
+  for (int j = threadIdx.x; j < nslots; j += kPartThreads) {
+    const uint64_t* w = &L[(j >> 3) * kPartStride + 2 * (j & 7)];
+    Slot sl;
+    sl.key = w[0];
+    sl.val = sl.key < kTomb ? w[1] : 0;
+    slots[j] = sl;
+  }
+  const int64_t tot = block_sum<kPartThreads>((int64_t)claimed);
+  if (threadIdx.x == 0) spec_count(t, blockIdx.x, tot << 32);
+  const int64_t dst = (int64_t)c * kBinSub * P.c1 + lbase;  // the coarse bin has been taken apart
+  for (uint32_t j = threadIdx.x; j < nl; j += kPartThreads) {
+    P.r1k[dst + j] = P.r2k[src + left[j]];
+    if (VK) store_val<VK>(P.r1v, dst + j, load_val<VK>(P.r2v, src + left[j]));
+    P.r1i[dst + j] = P.r2i[src + left[j]];
+  }
+}
+
+// One left-over element per lane, by the ordinary probe.  Returns (stored, listed).
+template <int VK>
+__device__ __forceinline__ uint2 part_place(const TableView& t, const PartView& P, bool mine, uint64_t key,
+                                            uint64_t val, int64_t i, uint32_t inject, bool home_full,
+                                            uint8_t* __restrict__ status) {
+  const Place p = place_keys<true, false, false>(t, wave_lds<kBlock>(), mine, key, true, inject,
+                                                 (uint64_t)i, home_full);
+  if (!mine) return make_uint2(0, 0);
+  uint8_t f = kFlagClaimed;
+  if (p.found) {
+    f = kFlagListed;
+    if (status) status[i] = kPresent;
+  } else if (p.pos == kNoPos) {
+    f = kFlagNone;  // no free slot anywhere: cannot happen below capacity
+    if (status) status[i] = kFull;
+    aor32(&t.hdr->err, kErrFull);
+  } else if (VK) {
+    t.bk[p.pos >> 3].s[p.pos & 7].val = val;
+  }
+  if (!home_full || f != kFlagClaimed) P.flag[i] = f;  // (else it is kFlagSure)
+  return make_uint2(f == kFlagClaimed, f == kFlagListed);
+}
+
+// The left-over lists of the coarse bins, `blocks` blocks each: keys whose home bucket is full.
+// Random claims again, 4.6 million of 2^26 keys in 0.36 ms; with their indices alone in the lists,
+// keys and values gathered from the batch and the home bucket probed again, 0.78.
+template <int VK>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_part_left(TableView t, PartView P, int blocks,
+                                                                         uint8_t* __restrict__ status) {
+  const uint32_t c = blockIdx.x / (uint32_t)blocks;
+  const uint32_t m = P.nleft[c * kCtrStride];
+  const int64_t src = (int64_t)c * kBinSub * P.c1;
+  const uint32_t inject = t.hdr->inject;
+  uint32_t claimed = 0, listed = 0;
+  for (uint32_t j0 = blockIdx.x % (uint32_t)blocks * kBlock + (threadIdx.x & ~63u); j0 < m;
+       j0 += (uint32_t)blocks * kBlock) {
+    const uint32_t j = min(j0 + (uint32_t)wave_lane(), m - 1u);
+    const uint2 n = part_place<VK>(t, P, j0 + wave_lane() < m, P.r1k[src + j], load_val<VK>(P.r1v, src + j),
+                                   P.r1i[src + j], inject, true, status);
+    claimed += n.x;
+    listed += n.y;
+  }
+  if (listed) *P.nover = 1;
+  const int64_t tot = block_sum(((int64_t)claimed << 32) + (int64_t)listed);
+  if (threadIdx.x == 0) spec_count(t, blockIdx.x, tot);
+}
+
+// The elements marked kFlagLeft: a block gathers those of a window of flags.  Copies of a key may be
+// listed from here on, so every claimer's flag becomes kFlagClaimed.
+template <int VK>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_part_over(TableView t, PartView P,
+                                                                         const uint64_t* __restrict__ keys,
+                                                                         const void* __restrict__ vals, int64_t n,
+                                                                         uint8_t* __restrict__ status) {
+  if (*P.nover == 0) return;
+  __shared__ uint16_t list[kPartWindow];
+  __shared__ uint32_t m;
+  const uint32_t inject = t.hdr->inject;
+  uint32_t claimed = 0, listed = 0;
+  for (int64_t w0 = (int64_t)blockIdx.x * kPartWindow; w0 < n; w0 += (int64_t)gridDim.x * kPartWindow) {
+    if (threadIdx.x == 0) m = 0;
+    __syncthreads();
+    const int64_t i0 = w0 + 8 * (int)threadIdx.x;
+    // (the flags are laid out to a multiple of 8)
+    const uint64_t f = i0 < n ? *reinterpret_cast<const uint64_t*>(P.flag + i0) : 0;
+    uint64_t is = f & (f >> 1) & 0x0101010101010101ull;  // kFlagLeft alone has both bits
+    if (n - i0 < 8 && i0 < n) is &= (1ull << (8 * (int)(n - i0))) - 1;
+    const uint64_t sure = f & 0x0404040404040404ull;
+    if (sure) *reinterpret_cast<uint64_t*>(P.flag + i0) = (f ^ sure) | sure >> 2;
+    uint32_t at = is ? atomicAdd(&m, (uint32_t)__popcll(is)) : 0u;
+    for (; is; is &= is - 1) list[at++] = (uint16_t)(8 * threadIdx.x + (__builtin_ctzll(is) >> 3));
+    __syncthreads();
+    const uint32_t mm = m;
+    for (uint32_t j0 = threadIdx.x & ~63u; j0 < mm; j0 += kBlock) {
+      const uint32_t j = j0 + wave_lane();
+      const int64_t i = w0 + list[min(j, mm - 1u)];
+      const uint2 c = part_place<VK>(t, P, j < mm, keys[i], load_val<VK>(vals, i), i, inject, false, status);
+      claimed += c.x;
+      listed += c.y;
+    }
+    __syncthreads();  // the list is refilled
+  }
+  const int64_t tot = block_sum(((int64_t)claimed << 32) + (int64_t)listed);
+  if (threadIdx.x == 0) spec_count(t, blockIdx.x, tot);
 }
 
 // Flagged count per tile of kTile elements.
@@ -3306,6 +3709,111 @@ void spec_resolve(ct_table* t, const TableView& v, const uint64_t* kc, const voi
   launch(t, CT_KERNEL_FIX, s, [&] { k_spec_swap<VK, ERASE><<<g, kBlock, 0, s>>>(v, kc, vc, q, sc); });
 }
 
+// The workspace of a partitioned insert.
+struct PartLayout {
+  int64_t ncoarse, nfine, group;   // group: coarse bins whose fine bins r2 holds at a time
+  int64_t c1, c2, blocks_per_seg;
+  int lp2;
+  int64_t off_r1k, off_r1v, off_r1i, off_r2k, off_r2v, off_r2i, off_flag, off_ctr, ctr_words;
+  int64_t total;
+};
+
+// Which batches take the partitioned path: speculative ones (they cannot reach capacity, and the
+// table's last chunk stored most of its keys) of at least three keys per bucket and 2^23 keys.
+// Measured with 64-bit values into an empty table, plain against partitioned: at three keys per
+// bucket 2^22 keys 235 us against 244, 2^24 keys 1070 against 797; at two, 2^24 keys 1035 against
+// 949, which its workspace of 30 bytes a key outweighs; at one, 1052 against 1432 (each bucket
+// goes both ways whole).  Smaller batches end up in the caches, where random claims are cheap.  Tables
+// beyond 2^24 buckets would need a third level of bins.  Generic keys only: the spatial hash fills
+// its bins unevenly.
+constexpr int64_t kPartMinKeys = (int64_t)1 << 23;
+constexpr int64_t kPartMinRatio = 3;
+// The fine bins are filled and inserted in this many groups, which share their memory: one group
+// would save 1 % of the time for another 10 bytes of workspace a key, four cost 2 %.
+constexpr int kPartGroups = 2;
+
+bool part_layout(const ct_table* t, int64_t n, PartLayout* L) {
+  const int64_t nb = (int64_t)t->v.nb;
+  if (t->chunk_chosen || t->v.hash != CT_HASH_MIX64 || n < kPartMinKeys || n < kPartMinRatio * nb ||
+      n > ((int64_t)1 << 30))
+    return false;
+  const int vb = t->desc.val_kind == CT_VAL_U64 ? 8 : t->desc.val_kind == CT_VAL_U32 ? 4 : 0;
+  L->nfine = (nb + kPartBuckets - 1) / kPartBuckets;
+  int bits = 0;
+  while (((int64_t)1 << bits) < L->nfine) ++bits;
+  L->lp2 = std::min(8, bits / 2);
+  L->ncoarse = (L->nfine + ((int64_t)1 << L->lp2) - 1) >> L->lp2;
+  if (L->ncoarse > 256) return false;
+  // capacities: the mean of uniform hashes and eight standard deviations
+  auto cap_for = [](double mean) { return (int64_t)(mean + 8.0 * std::sqrt(mean)) + 64; };
+  const double per_bucket = (double)n / (double)nb;
+  L->c1 = cap_for(per_bucket * kPartBuckets * (double)((int64_t)1 << L->lp2) / kBinSub * 1.02);
+  L->c2 = std::min<int64_t>(cap_for(per_bucket * kPartBuckets), kPartPer * kPartThreads);
+  L->group = (L->ncoarse + kPartGroups * kPartXcds - 1) / (kPartGroups * kPartXcds) * kPartXcds;
+  L->blocks_per_seg = std::max<int64_t>(1, (L->c1 + kBinTile - 1) / kBinTile);
+  const int64_t n1 = L->ncoarse * kBinSub * L->c1, n2 = (L->group << L->lp2) * L->c2;
+  int64_t off = 0;
+  auto take = [&](int64_t bytes) {
+    const int64_t o = off;
+    off = align_up(off + bytes);
+    return o;
+  };
+  L->off_r1k = take(n1 * 8);
+  L->off_r1v = take(n1 * vb);
+  L->off_r1i = take(n1 * 4);
+  // the resolution's entries take r1's place: at most pow2ceil(n) of them, 12 bytes each
+  off = std::max(off, align_up(12 * pow2ceil(n)));
+  L->off_r2k = take(n2 * 8);
+  L->off_r2v = take(n2 * vb);
+  L->off_r2i = take(n2 * 4);
+  L->off_flag = take(n);
+  L->ctr_words = L->ncoarse * (kPartCtr + kCtrStride) + kCtrStride + (L->ncoarse << L->lp2);
+  L->off_ctr = take(L->ctr_words * 4);
+  L->total = off;
+  return true;
+}
+
+bool part_wanted(const ct_table* t, int64_t n, PartLayout* L) {
+  return t->size_ub + (uint64_t)n <= (uint64_t)t->desc.capacity && use_speculation(t, 0) &&
+         part_layout(t, n, L);
+}
+
+template <int VK>
+ct_status part_insert(ct_table* t, const PartLayout& L, uint8_t* ws, const uint64_t* keys,
+                      const void* vals, int64_t n, uint8_t* status, hipStream_t s) {
+  PartView P;
+  P.r1k = reinterpret_cast<uint64_t*>(ws + L.off_r1k);
+  P.r1v = ws + L.off_r1v;
+  P.r1i = reinterpret_cast<uint32_t*>(ws + L.off_r1i);
+  P.r2k = reinterpret_cast<uint64_t*>(ws + L.off_r2k);
+  P.r2v = ws + L.off_r2v;
+  P.r2i = reinterpret_cast<uint32_t*>(ws + L.off_r2i);
+  P.flag = ws + L.off_flag;
+  P.cur1 = reinterpret_cast<uint32_t*>(ws + L.off_ctr);
+  P.nleft = P.cur1 + L.ncoarse * kPartCtr;
+  P.nover = P.nleft + L.ncoarse * kCtrStride;
+  P.cur2 = P.nover + kCtrStride;
+  P.c1 = (uint32_t)L.c1;
+  P.c2 = (uint32_t)L.c2;
+  P.lp2 = L.lp2;
+  TableView v = t->v;  // the resolution reads the flags and its entries from the workspace
+  v.flag = P.flag;
+  v.dd = P.r1k;
+  t->size_ub = std::min<uint64_t>(t->size_ub + (uint64_t)n, (uint64_t)t->desc.capacity);
+  launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_purge_clear<<<flat_blocks(L.ctr_words), kBlock, 0, s>>>(P.cur1, L.ctr_words); });
+  launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_part_coarse<VK><<<(int)((n + kBinTile - 1) / kBinTile), kBlock, 0, s>>>(v, P, keys, vals, n, (int)L.ncoarse, status); });
+  for (int64_t c0 = 0; c0 < L.ncoarse; c0 += L.group) {
+    const int64_t nc = (std::min(L.group, L.ncoarse - c0) + kPartXcds - 1) / kPartXcds * kPartXcds;
+    launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_part_fine<VK><<<(int)(nc * kBinSub * L.blocks_per_seg), kBlock, 0, s>>>(v, P, (int)c0, (int)L.ncoarse, (int)L.blocks_per_seg); });
+    launch(t, CT_KERNEL_INSERT, s, [&] { k_part_insert<VK><<<(int)(nc << L.lp2), kPartThreads, 0, s>>>(v, P, (int)c0, status); });
+  }
+  const int lb = (int)std::max<int64_t>(1, 2048 / L.ncoarse);
+  launch(t, CT_KERNEL_INSERT, s, [&] { k_part_left<VK><<<(int)L.ncoarse * lb, kBlock, 0, s>>>(v, P, lb, status); });
+  launch(t, CT_KERNEL_INSERT, s, [&] { k_part_over<VK><<<(int)std::min<int64_t>((n + kPartWindow - 1) / kPartWindow, kSpecGrid), kBlock, 0, s>>>(v, P, keys, vals, n, status); });
+  spec_resolve<VK, false>(t, v, keys, vals, n, status, dedup_slots_for(std::min<int64_t>(n, (int64_t)1 << 26)), s);
+  return launched();
+}
+
 // Insert of n keys in the chunks and with the scratch of B.
 template <int VK>
 ct_status insert_chunks(ct_table* t, const BatchScratch& B, const uint64_t* keys,
@@ -3575,7 +4083,15 @@ ct_status ct_insert_batch_ws(ct_table* t, const uint64_t* keys, const void* vals
   ct_status r = check_batch(t, keys, n, ws, ws_bytes);
   if (r != CT_OK) return r;
   if (n == 0) return CT_OK;
-  if (t->desc.val_kind != CT_VAL_NONE && !vals) return CT_E_INVALID;
+  const int vk = t->desc.val_kind;
+  if (vk != CT_VAL_NONE && !vals) return CT_E_INVALID;
+  PartLayout P;
+  if (ws && part_wanted(t, n, &P) && ws_bytes >= P.total) {
+    uint8_t* w = static_cast<uint8_t*>(ws);
+    if (vk == CT_VAL_U32) return part_insert<1>(t, P, w, keys, vals, n, status, S(stream));
+    if (vk == CT_VAL_U64) return part_insert<2>(t, P, w, keys, vals, n, status, S(stream));
+    return part_insert<0>(t, P, w, keys, nullptr, n, status, S(stream));
+  }
   return insert_any(t, batch_scratch(t, n, ws, ws_bytes), keys, vals, n, status, S(stream));
 }
 
@@ -3584,8 +4100,13 @@ ct_status ct_insert_batch(ct_table* t, const uint64_t* keys, const void* vals, i
   return ct_insert_batch_ws(t, keys, vals, n, status, nullptr, 0, stream);
 }
 
-ct_status ct_workspace_bytes(const ct_table* t, int64_t n, int64_t* bytes) {
-  if (!t || n < 0 || !bytes) return CT_E_INVALID;
+ct_status ct_workspace_bytes(const ct_table* t, int32_t op, int64_t n, int64_t* bytes) {
+  if (!t || n < 0 || !bytes || (op != CT_OP_INSERT && op != CT_OP_ERASE)) return CT_E_INVALID;
+  PartLayout P;
+  if (op == CT_OP_INSERT && part_wanted(t, n, &P)) {
+    *bytes = P.total;
+    return CT_OK;
+  }
   Layout L;
   const int64_t q = workspace_chunk(t, n);
   *bytes = q && layout_scratch(&L, q, 0) ? L.total : 0;

@@ -49,9 +49,9 @@ def test_workspace_arguments(dev):  # noqa: F811
     t = ct.Table(5000, ct.VAL_NONE, device=dev)
     nb = C.c_int64(0)
     L = ct.lib()
-    assert L.ct_workspace_bytes(t._h, t.chunk, C.byref(nb)) == ct.CT_OK and nb.value == 0
-    assert L.ct_workspace_bytes(t._h, t.chunk + 1, C.byref(nb)) == ct.CT_OK and nb.value > 0
-    assert L.ct_workspace_bytes(t._h, -1, C.byref(nb)) == ct.CT_E_INVALID
+    assert L.ct_workspace_bytes(t._h, ct.OP_INSERT, t.chunk, C.byref(nb)) == ct.CT_OK and nb.value == 0
+    assert L.ct_workspace_bytes(t._h, ct.OP_INSERT, t.chunk + 1, C.byref(nb)) == ct.CT_OK and nb.value > 0
+    assert L.ct_workspace_bytes(t._h, ct.OP_INSERT, -1, C.byref(nb)) == ct.CT_E_INVALID
     keys = g64(distinct_u64(rng_for(7302), 3000), dev)
     ws = torch.empty(nb.value, dtype=torch.uint8, device=dev)
     args = (t._h, ct._ptr(keys), None, 3000, None)
@@ -60,4 +60,4 @@ def test_workspace_arguments(dev):  # noqa: F811
     assert L.ct_insert_batch_ws(*args, ws.data_ptr(), 256, s) == ct.CT_OK       # too small: unused
     assert t.size() == 3000 and t.check() == 0
     own = ct.Table(5000, ct.VAL_NONE, chunk=1024, device=dev)                   # a chosen chunk stays
-    assert L.ct_workspace_bytes(own._h, 4096, C.byref(nb)) == ct.CT_OK and nb.value == 0
+    assert L.ct_workspace_bytes(own._h, ct.OP_INSERT, 4096, C.byref(nb)) == ct.CT_OK and nb.value == 0
