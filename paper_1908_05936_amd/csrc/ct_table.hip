@@ -202,7 +202,9 @@ __global__ __launch_bounds__(kBlock) void k_prologue(TableView t, PoolHeader* po
 // up marked, unique keys stay unmarked, and the entry ends at the key's lowest index.  All
 // indices held by one entry belong to one key, so the fingerprint plus one look at that
 // element's key identifies the entry exactly.  A key repeated many times therefore costs one
-// global operation per window, not per copy.  Needs blockDim.x == kBlock.
+// global operation per window, not per copy.  Needs blockDim.x == kBlock.  Bound by latency at the
+// sizes that come here: keys and skip bytes are asked for before the LDS table is cleared, and the
+// entries of dd before the window is resolved (2^15 keys 9.8 us without that, 8.4 with).
 // `skip` (nullable): elements with a nonzero byte there take no part (a masked insert).
 __device__ __forceinline__ void dedup_range(const TableView& t, const uint64_t* __restrict__ keys,
                                             const uint8_t* __restrict__ skip, uint32_t dmask,
@@ -211,19 +213,22 @@ __device__ __forceinline__ void dedup_range(const TableView& t, const uint64_t* 
   __shared__ unsigned long long wk[kW];
   __shared__ uint32_t wmin[kW], wcnt[kW];
   for (int64_t b0 = lo; b0 < hi; b0 += step) {  // uniform trip count: barriers below
+    const int64_t i = b0 + threadIdx.x;
+    const uint64_t key = keys[min(i, hi - 1)];
+    const uint8_t out = skip ? skip[min(i, hi - 1)] : 0;
     for (uint32_t j = threadIdx.x; j < kW; j += kBlock) {
       wk[j] = kEmpty;
       wmin[j] = kNone;
       wcnt[j] = 0;
     }
     __syncthreads();
-    const int64_t i = b0 + threadIdx.x;
-    const bool valid = i < hi && !(skip && skip[i]);
-    const uint64_t key = valid ? keys[i] : kEmpty;
+    const bool valid = i < hi && !out;
     const bool normal = valid && key < kTomb;
     if (valid && !normal) amin32(&t.hdr->spec_first[key - kTomb], (uint32_t)i);
     const uint64_t mix = dedup_mix(key);
     uint32_t s = (uint32_t)(mix >> 32) & (kW - 1);
+    uint32_t h = (uint32_t)mix & dmask;
+    uint64_t e = normal ? t.dd[h] : 0;
     if (normal) {
       for (;;) {  // at most kBlock keys in kW slots: a free or matching slot exists
         const unsigned long long old = atomicCAS(&wk[s], (unsigned long long)kEmpty,
@@ -240,9 +245,7 @@ __device__ __forceinline__ void dedup_range(const TableView& t, const uint64_t* 
       if (wmin[s] == (uint32_t)i) {  // the window's representative of this key
         const uint64_t tag = mix & 0xFFFFFFFF00000000ull;
         const uint64_t mine = tag | (uint64_t)i;
-        uint32_t h = (uint32_t)mix & dmask;
         for (uint32_t probe = 0; probe <= dmask; ++probe) {
-          uint64_t e = t.dd[h];
           if (e == kEmpty) {
             uint64_t expected = kEmpty;
             if (cas64(&t.dd[h], expected, mine)) break;
@@ -257,6 +260,7 @@ __device__ __forceinline__ void dedup_range(const TableView& t, const uint64_t* 
             break;
           }
           h = (h + 1) & dmask;
+          e = t.dd[h];
         }
       }
     }
@@ -693,8 +697,9 @@ __device__ __forceinline__ int64_t insert_range(const TableView& t, WaveLds* w,
     // the value is loaded with the key (coalesced) so that its latency hides behind the probe
     const uint64_t val = (!ALLOC && valid) ? load_val<VK>(vals, i) : 0;
     const uint32_t mark = t.dmark[min(i, hi - 1)];
-    asm volatile("" ::"v"(mark));  // keep the load here, issued with the key's
-    const bool active = valid && !(skip && skip[i]);
+    const uint32_t out = skip ? skip[min(i, hi - 1)] : 0;
+    asm volatile("" ::"v"(mark), "v"(out));  // keep the loads here, issued with the key's
+    const bool active = valid && !out;
     const uint32_t first = active ? first_copy(t, keys, key, i, dmask, mark) : 0u;
     const bool actor = active && first == (uint32_t)i;
     const bool dup = active && !actor;
@@ -1165,57 +1170,82 @@ __device__ __forceinline__ uint32_t dd_find(const TableView& t, const uint64_t* 
   return kNone;
 }
 
-// Build: the keys that enter dd.  Listed direction: windows of 256 elements first resolve their
+// Build: the keys that enter dd.  Listed direction: windows of 1024 elements first resolve their
 // listed keys in LDS, so a key listed many times costs one CAS or atomic min per window (skipped
 // when the held index is already lower).  Claimer direction: every claimer's key is distinct, so
 // each takes an empty entry with one CAS.  Out-of-band listed copies take an atomic min on their
-// header word in both directions.
+// header word in both directions.  Windows that list nothing, most of those of a batch of mostly
+// new keys, cost their flags alone.
 __device__ __forceinline__ void spec_build_range(const TableView& t, const uint64_t* __restrict__ keys,
                                                  int64_t q, int64_t blk, int64_t nblk) {
   const uint32_t nd = t.hdr->ndup;  // written by spec_settle
   if (nd == 0) return;
   const SpecPlan p = spec_plan(nd, q);
   const uint32_t dmask = p.slots - 1;
-  constexpr uint32_t kW = 2 * kBlock;
+  constexpr int kPer = 4;
+  constexpr uint32_t kW = 2 * kPer * kBlock;
   __shared__ unsigned long long wk[kW];
   __shared__ uint32_t wmin[kW];
-  for (int64_t b0 = blk * kBlock; b0 < q; b0 += nblk * kBlock) {
-    const int64_t i = b0 + threadIdx.x;
-    const uint8_t f = i < q ? t.flag[i] : kFlagNone;
-    const uint64_t key = f != kFlagNone ? keys[i] : kEmpty;
-    if (f == kFlagListed && key >= kTomb) amin32(&t.hdr->spec_first[key - kTomb], (uint32_t)i);
-    const uint64_t mix = dedup_mix(key);
-    const uint64_t tag = mix & 0xFFFFFFFF00000000ull;
-    if (p.by_claimers) {
-      if (f == kFlagClaimed) {
+  for (int64_t b0 = blk * kBlock * kPer; b0 < q; b0 += nblk * kBlock * kPer) {
+    uint8_t f[kPer];
+    uint64_t key[kPer];
+    bool any = false;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      const int64_t i = b0 + k * kBlock + threadIdx.x;
+      f[k] = i < q ? t.flag[i] : kFlagNone;
+      any |= f[k] == kFlagListed;
+    }
+    if (!p.by_claimers && !__syncthreads_or(any)) continue;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      const int64_t i = b0 + k * kBlock + threadIdx.x;
+      key[k] = f[k] == kFlagListed || (p.by_claimers && f[k] == kFlagClaimed) ? keys[i] : 0;
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      const int64_t i = b0 + k * kBlock + threadIdx.x;
+      if (f[k] == kFlagListed && key[k] >= kTomb) amin32(&t.hdr->spec_first[key[k] - kTomb], (uint32_t)i);
+      if (p.by_claimers && f[k] == kFlagClaimed) {
+        const uint64_t mix = dedup_mix(key[k]);
         uint32_t h = (uint32_t)mix & dmask;
         for (uint32_t probe = 0; probe <= dmask; ++probe) {
           uint64_t expected = kEmpty;
-          if (cas64(&t.dd[h], expected, tag | (uint64_t)i)) break;
+          if (cas64(&t.dd[h], expected, (mix & 0xFFFFFFFF00000000ull) | (uint64_t)i)) break;
           h = (h + 1) & dmask;
         }
       }
-      continue;
     }
     // listed direction (uniform per block: p depends only on nd and q)
+    if (p.by_claimers) continue;
     for (uint32_t j = threadIdx.x; j < kW; j += kBlock) {
       wk[j] = kEmpty;
       wmin[j] = kNone;
     }
     __syncthreads();
-    const bool normal = f == kFlagListed && key < kTomb;
-    uint32_t s = (uint32_t)(mix >> 32) & (kW - 1);
-    if (normal) {
-      for (;;) {  // at most kBlock keys in kW slots: a free or matching slot exists
-        const unsigned long long old = atomicCAS(&wk[s], (unsigned long long)kEmpty,
-                                                 (unsigned long long)key);
-        if (old == kEmpty || old == key) break;
-        s = (s + 1) & (kW - 1);
+    uint32_t s[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      const int64_t i = b0 + k * kBlock + threadIdx.x;
+      s[k] = kNone;
+      if (f[k] != kFlagListed || key[k] >= kTomb) continue;
+      uint32_t at = (uint32_t)(dedup_mix(key[k]) >> 32) & (kW - 1);
+      for (;;) {  // at most kW / 2 keys in kW slots: a free or matching slot exists
+        const unsigned long long old = atomicCAS(&wk[at], (unsigned long long)kEmpty,
+                                                 (unsigned long long)key[k]);
+        if (old == kEmpty || old == key[k]) break;
+        at = (at + 1) & (kW - 1);
       }
-      atomicMin(&wmin[s], (uint32_t)i);
+      atomicMin(&wmin[at], (uint32_t)i);
+      s[k] = at;
     }
     __syncthreads();
-    if (normal && wmin[s] == (uint32_t)i) {
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      const int64_t i = b0 + k * kBlock + threadIdx.x;
+      if (s[k] == kNone || wmin[s[k]] != (uint32_t)i) continue;
+      const uint64_t mix = dedup_mix(key[k]);
+      const uint64_t tag = mix & 0xFFFFFFFF00000000ull;
       const uint64_t mine = tag | (uint64_t)i;
       uint32_t h = (uint32_t)mix & dmask;
       for (uint32_t probe = 0; probe <= dmask; ++probe) {
@@ -1225,7 +1255,7 @@ __device__ __forceinline__ void spec_build_range(const TableView& t, const uint6
           if (cas64(&t.dd[h], expected, mine)) break;
           e = expected;
         }
-        if ((e & 0xFFFFFFFF00000000ull) == tag && keys[(uint32_t)e] == key) {
+        if ((e & 0xFFFFFFFF00000000ull) == tag && keys[(uint32_t)e] == key[k]) {
           if ((uint32_t)i < (uint32_t)e) amin64(&t.dd[h], mine);
           break;
         }
@@ -1296,18 +1326,45 @@ __device__ __forceinline__ void spec_probe_range(const TableView& t, const uint6
   uint32_t* low = spec_low(t, p);
   constexpr uint32_t kW = 2 * kBlock;
   __shared__ uint32_t wh[kW], wmin[kW];
+  if (!p.by_claimers) {  // four look-ups per thread in flight: flag, key and entry depend on each other
+    constexpr int kPer = 4;
+    for (int64_t b0 = blk * kBlock * kPer; b0 < q; b0 += nblk * kBlock * kPer) {
+      uint8_t f[kPer];
+      uint64_t key[kPer], e[kPer];
+      uint32_t h[kPer];
+#pragma unroll
+      for (int k = 0; k < kPer; ++k) {
+        const int64_t i = b0 + k * kBlock + threadIdx.x;
+        f[k] = i < q ? t.flag[i] : kFlagNone;
+      }
+#pragma unroll
+      for (int k = 0; k < kPer; ++k)
+        key[k] = f[k] == kFlagClaimed ? keys[b0 + k * kBlock + threadIdx.x] : 0;
+#pragma unroll
+      for (int k = 0; k < kPer; ++k) {
+        h[k] = (uint32_t)dedup_mix(key[k]) & dmask;
+        e[k] = f[k] == kFlagClaimed ? t.dd[h[k]] : kEmpty;
+      }
+#pragma unroll
+      for (int k = 0; k < kPer; ++k) {
+        const uint64_t i = (uint64_t)(b0 + k * kBlock + threadIdx.x);
+        const uint64_t tag = dedup_mix(key[k]) & 0xFFFFFFFF00000000ull;
+        for (uint32_t probe = 0; probe <= dmask && e[k] != kEmpty; ++probe) {
+          if ((e[k] & 0xFFFFFFFF00000000ull) == tag && keys[(uint32_t)e[k]] == key[k]) {
+            if ((uint32_t)e[k] < (uint32_t)i)
+              hand_over<VK, ERASE>(t, vals, status, key[k], (uint32_t)i, (uint32_t)e[k]);
+            break;
+          }
+          h[k] = (h[k] + 1) & dmask;
+          e[k] = t.dd[h[k]];
+        }
+      }
+    }
+    return;
+  }
   for (int64_t b0 = blk * kBlock; b0 < q; b0 += nblk * kBlock) {
     const int64_t i = b0 + threadIdx.x;
     const uint8_t f = i < q ? t.flag[i] : kFlagNone;
-    if (!p.by_claimers) {
-      if (f == kFlagClaimed) {
-        const uint64_t key = keys[i];
-        uint32_t m = 0;
-        if (dd_find(t, keys, key, dmask, &m) != kNone && m < (uint32_t)i)
-          hand_over<VK, ERASE>(t, vals, status, key, (uint32_t)i, m);
-      }
-      continue;
-    }
     for (uint32_t j = threadIdx.x; j < kW; j += kBlock) {
       wh[j] = kNone;
       wmin[j] = kNone;
@@ -3002,8 +3059,40 @@ __device__ __forceinline__ GLoc g_locate(const GEntry* __restrict__ e, int32_t n
   return g_locate_at(e, n, (int32_t)blockIdx.x, (int32_t)gridDim.x);
 }
 
+// A pointer read from memory may point anywhere for all the compiler knows, and an access through
+// it goes by the unit that also serves LDS, whose answers the probe rounds wait for.  These point
+// to global memory, and are read as what they are.
+template <typename T>
+__device__ __forceinline__ T* in_global(T* const& field) {
+  typedef __attribute__((address_space(1))) T* Global;
+  return (T*)*reinterpret_cast<Global const*>(&field);
+}
+
+// The step of block L.
+__device__ __forceinline__ GStep g_step(const GStep* __restrict__ st, const GLoc& L) {
+  const GStep& m = st[L.step];
+  GStep g = m;
+  g.v.bk = in_global(m.v.bk);
+  g.v.hdr = in_global(m.v.hdr);
+  g.v.dd = in_global(m.v.dd);
+  g.v.dmark = in_global(m.v.dmark);
+  g.v.dup = in_global(m.v.dup);
+  g.v.flag = in_global(m.v.flag);
+  g.v.ref = in_global(m.v.ref);
+  g.v.tsum = in_global(m.v.tsum);
+  g.v.bcnt = in_global(m.v.bcnt);
+  g.v.stripes = in_global(m.v.stripes);
+  g.v.dfirst = in_global(m.v.dfirst);
+  g.v.fb = in_global(m.v.fb);
+  g.keys = in_global(m.keys);
+  g.vals = in_global(m.vals);
+  g.vout = in_global(m.vout);
+  g.flags = in_global(m.flags);
+  return g;
+}
+
 __device__ __forceinline__ void g_reset_body(const GStep* __restrict__ st, const GLoc L) {
-  const TableView t = st[L.step].v;
+  const TableView t = g_step(st, L).v;
   reset_range(t, (int64_t)L.lb * kBlock, (int64_t)t.nb * kSlots, (int64_t)L.nblk * kBlock,
               L.lb == 0, 0);
 }
@@ -3023,7 +3112,7 @@ __device__ __forceinline__ bool g_speculates(const GStep& g) {
 // entries are cleared after the claims, and only when something is listed); otherwise the
 // dedup scratch is cleared and the header decides as for a single-table chunk.
 __device__ __forceinline__ void g_prologue_body(const GStep* __restrict__ st, const GLoc L) {
-  const GStep& g = st[L.step];
+  const GStep g = g_step(st, L);
   const TableView t = g.v;
   if (g_speculates(g)) {
     if (L.lb == 0 && threadIdx.x == 0) {
@@ -3038,7 +3127,7 @@ __device__ __forceinline__ void g_prologue_body(const GStep* __restrict__ st, co
 }
 
 __device__ __forceinline__ void g_dedup_body(const GStep* __restrict__ st, const GLoc L) {
-  const GStep& g = st[L.step];
+  const GStep g = g_step(st, L);
   const TableView t = g.v;
   if (t.hdr->spec) return;
   dedup_range(t, g.keys, nullptr, g.db - 1, (int64_t)L.lb * kBlock, g.q, (int64_t)L.nblk * kBlock);
@@ -3048,7 +3137,7 @@ __device__ __forceinline__ void g_dedup_body(const GStep* __restrict__ st, const
 // the range code strides by the step's blocks times BS, 8 lanes per key group as always.
 template <int BS>
 __device__ __forceinline__ void g_insert_body(const GStep* __restrict__ st, const GLoc L) {
-  const GStep& g = st[L.step];
+  const GStep g = g_step(st, L);
   const TableView t = g.v;
   const int64_t lo = (int64_t)L.lb * BS, step = (int64_t)L.nblk * BS;
   WaveLds* w = wave_lds<BS>();
@@ -3074,7 +3163,7 @@ __device__ __forceinline__ void g_insert_body(const GStep* __restrict__ st, cons
 
 template <int BS>
 __device__ __forceinline__ void g_erase_body(const GStep* __restrict__ st, const GLoc L) {
-  const GStep& g = st[L.step];
+  const GStep g = g_step(st, L);
   const TableView t = g.v;
   if (t.hdr->spec) {
     const uint2 c = erase_spec_range<false>(t, wave_lds<BS>(), g.keys, g.flags, (int64_t)L.lb * BS, g.q,
@@ -3091,7 +3180,7 @@ __device__ __forceinline__ void g_erase_body(const GStep* __restrict__ st, const
 
 template <int BS>
 __device__ __forceinline__ void g_find_body(const GStep* __restrict__ st, const GLoc L) {
-  const GStep& g = st[L.step];
+  const GStep g = g_step(st, L);
   const TableView t = g.v;
   const int64_t lo = (int64_t)L.lb * BS, step = (int64_t)L.nblk * BS;
   WaveLds* w = wave_lds<BS>();
@@ -3103,7 +3192,7 @@ __device__ __forceinline__ void g_find_body(const GStep* __restrict__ st, const 
 // The count change into the live count and the feedback words; for a speculative step also the
 // listed total, which the resolution stages read.
 __device__ __forceinline__ void g_apply_body(const GStep* __restrict__ st, const GLoc L) {
-  const GStep& g = st[L.step];
+  const GStep g = g_step(st, L);
   const TableView t = g.v;
   const bool erase = g.type == kOpErase;
   if (t.hdr->spec) {
@@ -3120,20 +3209,20 @@ __device__ __forceinline__ void g_apply_body(const GStep* __restrict__ st, const
 
 // Resolution of a speculative step (the single-table kernels' range code, per step).
 __device__ __forceinline__ void g_sclear_body(const GStep* __restrict__ st, const GLoc L) {
-  const GStep& g = st[L.step];
+  const GStep g = g_step(st, L);
   if (!g.v.hdr->spec) return;
   spec_clear_range(g.v, g.q, g.v.hdr->ndup, L.lb, L.nblk);
 }
 
 __device__ __forceinline__ void g_sbuild_body(const GStep* __restrict__ st, const GLoc L) {
-  const GStep& g = st[L.step];
+  const GStep g = g_step(st, L);
   if (!g.v.hdr->spec) return;
   spec_build_range(g.v, g.keys, g.q, L.lb, L.nblk);
 }
 
 template <bool SWAP>
 __device__ __forceinline__ void g_sfix_body(const GStep* __restrict__ st, const GLoc L) {
-  const GStep& g = st[L.step];
+  const GStep g = g_step(st, L);
   const TableView t = g.v;
   if (!t.hdr->spec) return;
   if (g.type == kOpErase) {
@@ -3152,7 +3241,7 @@ __device__ __forceinline__ void g_sfix_body(const GStep* __restrict__ st, const 
 }
 
 __device__ __forceinline__ void g_tile_count_body(const GStep* __restrict__ st, const GLoc L) {
-  const GStep& g = st[L.step];
+  const GStep g = g_step(st, L);
   const TableView t = g.v;
   if (t.hdr->fast) return;
   __shared__ uint32_t part[kBlock / 64];
@@ -3174,13 +3263,13 @@ __device__ __forceinline__ void g_tile_count_body(const GStep* __restrict__ st, 
 
 template <int NT>
 __device__ __forceinline__ void g_tile_scan_body(const GStep* __restrict__ st, const GLoc L) {
-  const TableView t = st[L.step].v;
+  const TableView t = g_step(st, L).v;
   if (t.hdr->fast) return;
   scan_tiles_block<NT>(t, nullptr, st[L.step].ntiles, 0);
 }
 
 __device__ __forceinline__ void g_final_body(const GStep* __restrict__ st, const GLoc L) {
-  const GStep& g = st[L.step];
+  const GStep g = g_step(st, L);
   const TableView t = g.v;
   if (t.hdr->fast) return;   // nothing to rank: leave before any of the tile code
   if (g.vk == 1)
@@ -3198,30 +3287,39 @@ struct GCopy {
   int64_t bytes;
 };
 
-// Segment of this block's entry, copied by the entry's blocks in the widest aligned unit.
+// Segment of this block's entry, copied by the entry's blocks: single bytes up to the destination's
+// first 16-byte boundary and past its last one, 16-byte stores between, four loads per thread in
+// flight.  Operations of odd sizes leave sources and destinations (of one-byte flags above all) at
+// any alignment to each other, and a load may have any.  70 million operations' arrays of 256 tables
+// (0.9 GB in 5000 segments) take 0.38 ms, 0.55 with one unit of the widest common alignment at a time.
+typedef uint32_t Unaligned16 __attribute__((ext_vector_type(4), aligned(1)));
+
 __device__ __forceinline__ void g_copy_body(const GCopy* __restrict__ segs, const GLoc L) {
-  const GCopy g = segs[L.step];
-  const uintptr_t a = reinterpret_cast<uintptr_t>(g.src) | reinterpret_cast<uintptr_t>(g.dst) |
-                      (uintptr_t)g.bytes;
+  const GCopy& g = segs[L.step];
+  const uint8_t* s = static_cast<const uint8_t*>(in_global(g.src));
+  uint8_t* d = static_cast<uint8_t*>(in_global(g.dst));
+  const int64_t bytes = g.bytes;
   const int64_t first = (int64_t)L.lb * kBlock + threadIdx.x;
   const int64_t stride = (int64_t)L.nblk * kBlock;
-  if ((a & 15) == 0) {
-    const uint4* s = static_cast<const uint4*>(g.src);
-    uint4* d = static_cast<uint4*>(g.dst);
-    for (int64_t i = first; i < g.bytes / 16; i += stride) d[i] = s[i];
-  } else if ((a & 7) == 0) {
-    const uint64_t* s = static_cast<const uint64_t*>(g.src);
-    uint64_t* d = static_cast<uint64_t*>(g.dst);
-    for (int64_t i = first; i < g.bytes / 8; i += stride) d[i] = s[i];
-  } else {
-    const uint8_t* s = static_cast<const uint8_t*>(g.src);
-    uint8_t* d = static_cast<uint8_t*>(g.dst);
-    for (int64_t i = first; i < g.bytes; i += stride) d[i] = s[i];
+  const int64_t head = min((int64_t)(-reinterpret_cast<uintptr_t>(d) & 15u), bytes);
+  const int64_t units = (bytes - head) / 16, tail = head + units * 16;
+  if (first < head) d[first] = s[first];
+  if (tail + first < bytes) d[tail + first] = s[tail + first];
+  s += head;
+  uint4* d16 = reinterpret_cast<uint4*>(d + head);
+  for (int64_t i = first; i < units; i += 4 * stride) {
+    Unaligned16 x[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      x[k] = *reinterpret_cast<const Unaligned16*>(s + 16 * min(i + k * stride, units - 1));
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (i + k * stride < units) d16[i + k * stride] = make_uint4(x[k].x, x[k].y, x[k].z, x[k].w);
   }
 }
 
 __device__ __forceinline__ void g_fix_body(const GStep* __restrict__ st, const GLoc L) {
-  const GStep& g = st[L.step];
+  const GStep g = g_step(st, L);
   const TableView t = g.v;
   if (t.hdr->spec) return;   // resolved already
   fix_range(t, g.q, g.flags, nullptr, (int64_t)L.lb * kBlock, (int64_t)L.nblk * kBlock);
@@ -3240,8 +3338,9 @@ __global__ __launch_bounds__(kBlock) void k_g_dedup(const GStep* __restrict__ st
                                                     const GEntry* __restrict__ e, int32_t n) {
   g_dedup_body(st, g_locate(e, n));
 }
+// (5 waves per SIMD as in k_insert: the large multi-table schedule 5.85 ms without, 5.80 with)
 template <int BS>
-__global__ __launch_bounds__(BS) void k_g_insert(const GStep* __restrict__ st,
+__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(5))) void k_g_insert(const GStep* __restrict__ st,
                                                  const GEntry* __restrict__ e, int32_t n) {
   g_insert_body<BS>(st, g_locate(e, n));
 }
