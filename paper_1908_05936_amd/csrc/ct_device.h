@@ -53,6 +53,8 @@ constexpr int kMaxGroupBlocks = 16384;  // blocks of one insert/erase launch: it
 constexpr int kCountStripes = 32;       // count words of a speculative chunk, behind the partials
 constexpr int kCountStride = 16;        // u64 words between them: one 128-byte line each
 constexpr int kStripeRegion = kCountStripes * kCountStride * 8;
+constexpr int kSettleWord = 1;          // beside the first count word: a small grid's count and blocks
+constexpr int kSettleBlocks = 256;      // (65,536 keys) grids that settle through it
 
 enum : uint8_t { kPresent = 0, kInserted = 1, kFull = 2, kNoStatus = 0xFF };
 enum : uint32_t { kErrFull = 1u, kErrPool = 2u, kErrInternal = 0x80000000u };

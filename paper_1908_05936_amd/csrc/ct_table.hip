@@ -107,6 +107,7 @@ __device__ __forceinline__ void reset_range(const TableView& t, int64_t lo, int6
       h->err = 0;
       h->inject = 0;
       for (int j = 0; j < kCountStripes; ++j) t.stripes[j * kCountStride] = 0;
+      t.stripes[kSettleWord] = 0;
     }
     // an empty table starts a fresh history: its next insert and erase chunks speculate
     h->fbd[0] = h->fbd[1] = 0;
@@ -178,7 +179,8 @@ __device__ __forceinline__ void prologue_range(const TableView& t, PoolHeader* p
   if (header && threadIdx.x == 0) chunk_header(t, pool, q, 0u);
 }
 
-// A chunk with a pool ranks its elements: its insert or erase kernel adds to the tile sums.
+// A chunk with a pool, or a small one that may meet FULL: its insert or erase kernel adds to the tile
+// sums.
 __device__ __forceinline__ void zero_tile_sums(const TableView& t, int64_t q) {
   for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < (q + kTile - 1) / kTile;
        j += (int64_t)gridDim.x * kBlock)
@@ -186,8 +188,8 @@ __device__ __forceinline__ void zero_tile_sums(const TableView& t, int64_t q) {
 }
 
 __global__ __launch_bounds__(kBlock) void k_prologue(TableView t, PoolHeader* pool,
-                                                     uint32_t dslots, int64_t q) {
-  if (pool) zero_tile_sums(t, q);
+                                                     uint32_t dslots, int64_t q, int ranked) {
+  if (ranked) zero_tile_sums(t, q);
   prologue_range(t, pool, dslots, q, (int64_t)blockIdx.x * blockDim.x, prologue_units(dslots, q),
                  (int64_t)gridDim.x * blockDim.x, blockIdx.x == 0);
 }
@@ -337,9 +339,9 @@ __device__ __forceinline__ int64_t bin_prologue_units(const TableView& t, int64_
 // The kernels of the path that resolves repeated keys first leave at once when the chunk went the
 // speculative way (decided on the device, k_spec_decide); `decided`: the flag is this chunk's.
 __global__ __launch_bounds__(kBlock) void k_bin_prologue(TableView t, PoolHeader* pool, int64_t q,
-                                                         int decided) {
+                                                         int ranked, int decided) {
   if (decided && t.hdr->spec) return;
-  if (pool) zero_tile_sums(t, q);
+  if (ranked) zero_tile_sums(t, q);
   const int64_t nm = (q + 15) / 16;
   const int64_t hi = bin_prologue_units(t, q);
   const uint4 zero = make_uint4(0, 0, 0, 0);
@@ -703,11 +705,12 @@ __device__ __forceinline__ int64_t insert_range(const TableView& t, WaveLds* w,
     const uint32_t first = active ? first_copy(t, keys, key, i, dmask, mark) : 0u;
     const bool actor = active && first == (uint32_t)i;
     const bool dup = active && !actor;
-    // what k_fix reads: the mark says that the key is repeated, dup[i] names its first copy
-    if (active && (mark || dup)) t.dup[i] = first;
-    if (dup && !mark) t.dmark[i] = 1;  // a later copy of an out-of-band key
+    // what k_fix reads: the mark says that the key is repeated, dup[i] names its first copy.  A later
+    // copy whose first copy can neither meet FULL nor draw a value has its outcome here.
+    if (flags && active && (mark || dup)) t.dup[i] = first;
+    if (flags && dup && !mark) t.dmark[i] = 1;  // a later copy of an out-of-band key
 
-    uint8_t st = kNoStatus;
+    uint8_t st = dup && !flags ? kPresent : kNoStatus;
     uint8_t newf = 0;
     uint64_t ref = 0;
     if (actor && key >= kTomb) {  // out-of-band key: this lane alone
@@ -757,6 +760,36 @@ __device__ __forceinline__ int64_t insert_range(const TableView& t, WaveLds* w,
   return ins;
 }
 
+// The host's view of how an insert chunk of q keys went: q and the keys it stored, one 64-bit
+// store to host-mapped memory (read without synchronising; a stale or torn read only changes
+// which path the next chunk takes, never a result).
+// Word 0 reports insert chunks (keys stored), word 1 erase chunks (keys removed).
+__device__ __forceinline__ void chunk_feedback(const TableView& t, int word, int64_t q,
+                                               int64_t changed) {
+  if (q <= 0) return;
+  const uint64_t w = ((uint64_t)q << 32) | (uint64_t)(uint32_t)(changed < 0 ? 0 : changed);
+  t.hdr->fbd[word] = w;
+  if (t.fb) __hip_atomic_store(t.fb + word, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// The last block of a small grid settles the live count: every block adds (change << 20 | 1) to one
+// word of the table, and the one that completes the grid's number has the total in its answer and
+// puts the word back to zero.  Saves the launch of k_apply_count (4 us of the host, which bounds
+// batches of this size: 96 requests through the server, a third of them updates, went from 2.45 to
+// 2.2 ms with this, the counts and the outcomes below taken into the insert and erase kernels).
+// One same-address atomic takes 12.6 ns, so grids of more than kSettleBlocks leave partials instead.
+__device__ __forceinline__ void settle_count(const TableView& t, int64_t tot, int64_t q, int word) {
+  const uint64_t old = __hip_atomic_fetch_add(&t.stripes[kSettleWord], ((uint64_t)tot << 20) | 1u,
+                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if ((old & 0xFFFFFu) + 1u != gridDim.x) return;
+  Header* h = t.hdr;
+  const int64_t sum = (int64_t)(old >> 20) + tot;
+  t.stripes[kSettleWord] = 0;
+  h->size = word ? h->size - (uint64_t)sum : h->size + (uint64_t)sum;
+  // (an insert chunk that may meet capacity stores more keys in its ranked pass: no report)
+  if (word || h->fast) chunk_feedback(t, word, q, sum);
+}
+
 // The rank flags per tile, by the kernel that wrote them: each pass of the block covers 256
 // consecutive elements, all in one tile, and each thread re-reads the flag it wrote itself; the
 // tile sums were zeroed by the chunk's prologue.
@@ -778,15 +811,19 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(AHEAD ? 
                                                    const void* __restrict__ vals, int64_t q,
                                                    uint32_t dmask, uint8_t* __restrict__ status,
                                                    int32_t* __restrict__ vout,
-                                                   const uint8_t* __restrict__ skip) {
+                                                   const uint8_t* __restrict__ skip, int settle) {
   if (t.hdr->spec) return;
   const int64_t ins = insert_range<VK, ALLOC, AHEAD>(t, wave_lds<kBlock>(), keys, skip, vals, dmask, status, vout,
                                               (int64_t)blockIdx.x * kBlock, q,
                                               (int64_t)gridDim.x * kBlock);
-  // one partial per block, summed by k_apply_count: no same-address atomics across the grid
-  const int64_t tot = block_sum(ins);
-  if (threadIdx.x == 0) t.bcnt[blockIdx.x] = tot;
-  if (ALLOC) count_flags(t, q);
+  if (!ALLOC) {
+    const int64_t tot = block_sum(ins);
+    if (threadIdx.x == 0) {
+      if (settle) settle_count(t, tot, q, 0);
+      else t.bcnt[blockIdx.x] = tot;  // summed by k_apply_count
+    }
+  }
+  if (ALLOC || (settle && !t.hdr->fast)) count_flags(t, q);
 }
 
 // Host-side resizing (a table's capacity is fixed when it is created, Section 4; it grows by a
@@ -876,7 +913,7 @@ __device__ __forceinline__ int64_t erase_range(const TableView& t, WaveLds* w,
 template <bool RELEASE, bool AHEAD>
 __global__ __launch_bounds__(kBlock) void k_erase(TableView t, const uint64_t* __restrict__ keys,
                                                   int64_t q, uint32_t dmask,
-                                                  uint8_t* __restrict__ erased) {
+                                                  uint8_t* __restrict__ erased, int settle) {
   const int64_t del = erase_range<RELEASE, AHEAD>(t, wave_lds<kBlock>(), keys, dmask, erased, (int64_t)blockIdx.x * kBlock, q,
                                            (int64_t)gridDim.x * kBlock);
   if (RELEASE) {  // the removals are the rank flags: their total settles the live count
@@ -884,7 +921,10 @@ __global__ __launch_bounds__(kBlock) void k_erase(TableView t, const uint64_t* _
     return;
   }
   const int64_t tot = block_sum(del);
-  if (threadIdx.x == 0) t.bcnt[blockIdx.x] = -tot;
+  if (threadIdx.x == 0) {
+    if (settle) settle_count(t, tot, q, 1);
+    else t.bcnt[blockIdx.x] = -tot;
+  }
 }
 
 // Add the per-block partials of the preceding insert/erase kernel to the live count.
@@ -903,18 +943,6 @@ __device__ __forceinline__ int64_t apply_count_block(const TableView& t, int npa
   }
   __syncthreads();
   return s;
-}
-
-// The host's view of how an insert chunk of q keys went: q and the keys it stored, one 64-bit
-// store to host-mapped memory (read without synchronising; a stale or torn read only changes
-// which path the next chunk takes, never a result).
-// Word 0 reports insert chunks (keys stored), word 1 erase chunks (keys removed).
-__device__ __forceinline__ void chunk_feedback(const TableView& t, int word, int64_t q,
-                                               int64_t changed) {
-  if (q <= 0) return;
-  const uint64_t w = ((uint64_t)q << 32) | (uint64_t)(uint32_t)(changed < 0 ? 0 : changed);
-  t.hdr->fbd[word] = w;
-  if (t.fb) __hip_atomic_store(t.fb + word, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // fb_q > 0: the partials are the count changes of an insert (fb_word 0) or erase (fb_word 1)
@@ -1857,7 +1885,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
   if (threadIdx.x == 0) spec_count(t, blockIdx.x, tot);
 }
 
-// Flagged count per tile of kTile elements.
+// Flagged count per tile of kTile elements, for grids that do not settle (a launch costs these less than
+// counting in the insert kernel: 4 M repeated keys into a set, 380 us against 386).
 __global__ __launch_bounds__(kBlock) void k_tile_count(TableView t, int64_t q) {
   if (t.hdr->fast) return;
   __shared__ uint32_t part[kBlock / 64];
@@ -1876,7 +1905,6 @@ __global__ __launch_bounds__(kBlock) void k_tile_count(TableView t, int64_t q) {
     t.tsum[blockIdx.x] = s;
   }
 }
-
 
 // One block of NT threads: exclusive scan of the tile counts, then the counter updates the ranks
 // imply.  mode 0: insert near capacity; 1: insert with pool values; 2: erase releasing to the pool.
@@ -2107,8 +2135,9 @@ __device__ __forceinline__ void fix_range(const TableView& t, int64_t q, uint8_t
 }
 
 __global__ __launch_bounds__(kBlock) void k_fix(TableView t, int64_t q, uint8_t* __restrict__ status,
-                                                int32_t* __restrict__ vout) {
+                                                int32_t* __restrict__ vout, int alloc) {
   if (t.hdr->spec) return;
+  if (!alloc && t.hdr->fast) return;  // the insert kernel knew their outcome
   fix_range(t, q, status, vout, (int64_t)blockIdx.x * kBlock, (int64_t)gridDim.x * kBlock);
 }
 
@@ -3065,7 +3094,7 @@ __device__ __forceinline__ GLoc g_locate(const GEntry* __restrict__ e, int32_t n
 template <typename T>
 __device__ __forceinline__ T* in_global(T* const& field) {
   typedef __attribute__((address_space(1))) T* Global;
-  return (T*)*reinterpret_cast<Global const*>(&field);
+  return (T*)*static_cast<Global const*>(static_cast<const void*>(&field));
 }
 
 // The step of block L.
@@ -3321,7 +3350,7 @@ __device__ __forceinline__ void g_copy_body(const GCopy* __restrict__ segs, cons
 __device__ __forceinline__ void g_fix_body(const GStep* __restrict__ st, const GLoc L) {
   const GStep g = g_step(st, L);
   const TableView t = g.v;
-  if (t.hdr->spec) return;   // resolved already
+  if (t.hdr->spec || t.hdr->fast) return;   // the outcomes are known already
   fix_range(t, g.q, g.flags, nullptr, (int64_t)L.lb * kBlock, (int64_t)L.nblk * kBlock);
 }
 
@@ -3665,9 +3694,9 @@ int group_blocks(int64_t n, int bs = kBlock) {
 }
 
 // Chunks of at most this many rank tiles skip the one-block rank scan: each ranked-completion
-// block sums the tile counts before its own tile (at most 256 loads), and the first settles the
-// chunk's totals.
-constexpr int kInlineRankTiles = 256;
+// block sums the tile counts before its own tile (at most four loads a thread), and the first settles the
+// chunk's totals.  (2^21 samples into blocks, 1024 tiles twice: 252.4 us with two scans, 250.5 without.)
+constexpr int kInlineRankTiles = 1024;
 
 int flat_blocks(int64_t n) {
   const int64_t b = (n + kBlock - 1) / kBlock;
@@ -3722,22 +3751,23 @@ BatchScratch batch_scratch(const ct_table* t, int64_t n, void* ws, int64_t ws_by
   return b;
 }
 
-// Resolve the repeated keys of one chunk: binned for large chunks, dd otherwise.
+// Resolve the repeated keys of one chunk: binned for large chunks, dd otherwise.  ranked: the kernel
+// that follows adds to the tile sums.
 void dedup_chunk(ct_table* t, const TableView& v, PoolHeader* pool, const uint64_t* kc, int64_t q,
-                 hipStream_t s, int decided = 0) {
+                 hipStream_t s, int ranked, int decided = 0) {
   const uint32_t db = dedup_slots_for(q);
   if (v.r1k && q >= kBinMinChunk) {
     // blocks per coarse segment: enough for its expected fill (about c1 / 2) in one tile each
     const int blocks_per_seg = (int)std::max<int64_t>(1, (v.c1 / 2 + kBinTile - 1) / kBinTile);
     const int nfine = 1 << v.lp;
-    launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_bin_prologue<<<flat_blocks(bin_prologue_units_host(v, q)), kBlock, 0, s>>>(v, pool, q, decided); });
+    launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_bin_prologue<<<flat_blocks(bin_prologue_units_host(v, q)), kBlock, 0, s>>>(v, pool, q, ranked, decided); });
     launch(t, CT_KERNEL_DEDUP, s, [&] { k_bin_scatter1<<<(int)((q + kBinTile - 1) / kBinTile), kBlock, 0, s>>>(v, kc, q); });
     launch(t, CT_KERNEL_DEDUP, s, [&] { k_bin_scatter2<<<kBinCoarse * kBinSub * blocks_per_seg, kBlock, 0, s>>>(v, blocks_per_seg); });
     launch(t, CT_KERNEL_DEDUP, s, [&] { k_bin_dedup<<<nfine, kBlock, 0, s>>>(v); });
     launch(t, CT_KERNEL_DEDUP, s, [&] { k_bin_fallback_clear<<<flat_blocks(db / 2), kBlock, 0, s>>>(v, db); });
     launch(t, CT_KERNEL_DEDUP, s, [&] { k_bin_fallback_dedup<<<flat_blocks(q), kBlock, 0, s>>>(v, kc, q, db - 1); });
   } else {
-    launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_prologue<<<flat_blocks(db / 2), kBlock, 0, s>>>(v, pool, db, q); });
+    launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_prologue<<<flat_blocks(db / 2), kBlock, 0, s>>>(v, pool, db, q, ranked); });
     launch(t, CT_KERNEL_DEDUP, s, [&] { k_dedup<<<flat_blocks(q), kBlock, 0, s>>>(v, kc, nullptr, q, db - 1); });
   }
 }
@@ -3943,6 +3973,7 @@ ct_status insert_chunks(ct_table* t, const BatchScratch& B, const uint64_t* keys
       if (r != CT_OK) return r;
       continue;
     }
+    const int settle = gb <= kSettleBlocks;
     const int decided = !surely_fast && t->insert_path != CT_INSERT_RESOLVE_FIRST &&
                         v.r1k && q >= kDeviceDecides;
     if (decided) {  // the speculative kernels first; whichever path is not taken leaves at once
@@ -3951,16 +3982,16 @@ ct_status insert_chunks(ct_table* t, const BatchScratch& B, const uint64_t* keys
       launch(t, CT_KERNEL_INSERT, s, [&] { k_insert_spec<VK, false><<<gb, kBlock, 0, s>>>(v, kc, vc, q, sc, 1); });
       spec_resolve<VK, false>(t, v, kc, vc, q, sc, db, s, 1);
     }
-    dedup_chunk(t, v, nullptr, kc, q, s, decided);
-    launch(t, CT_KERNEL_INSERT, s, [&] { (q <= kAheadMax ? k_insert<VK, false, true> : k_insert<VK, false, false>)<<<gb, kBlock, 0, s>>>(v, kc, vc, q, db - 1, sc, nullptr, nullptr); });
-    launch(t, CT_KERNEL_APPLY, s, [&] { k_apply_count<<<1, 1024, 0, s>>>(v, gb, q, 0, decided); });
+    dedup_chunk(t, v, nullptr, kc, q, s, settle && !surely_fast, decided);
+    launch(t, CT_KERNEL_INSERT, s, [&] { (q <= kAheadMax ? k_insert<VK, false, true> : k_insert<VK, false, false>)<<<gb, kBlock, 0, s>>>(v, kc, vc, q, db - 1, sc, nullptr, nullptr, settle); });
+    if (!settle) launch(t, CT_KERNEL_APPLY, s, [&] { k_apply_count<<<1, 1024, 0, s>>>(v, gb, q, 0, decided); });
     if (!surely_fast) {
-      launch(t, CT_KERNEL_RANK, s, [&] { k_tile_count<<<ntiles, kBlock, 0, s>>>(v, q); });
+      if (!settle) launch(t, CT_KERNEL_RANK, s, [&] { k_tile_count<<<ntiles, kBlock, 0, s>>>(v, q); });
       const int inl = ntiles <= kInlineRankTiles ? ntiles : 0;
       if (!inl) launch(t, CT_KERNEL_RANK, s, [&] { k_tile_scan<<<1, 1024, 0, s>>>(v, nullptr, ntiles, 0); });
       launch(t, CT_KERNEL_FINAL, s, [&] { k_final<VK, 0><<<ntiles, kBlock, 0, s>>>(v, nullptr, nullptr, kc, vc, q, sc, nullptr, inl); });
     }
-    if (sc) launch(t, CT_KERNEL_FIX, s, [&] { k_fix<<<flat_blocks((q + 3) / 4), kBlock, 0, s>>>(v, q, sc, nullptr); });
+    if (sc && !surely_fast) launch(t, CT_KERNEL_FIX, s, [&] { k_fix<<<flat_blocks((q + 3) / 4), kBlock, 0, s>>>(v, q, sc, nullptr, 0); });
     ct_status r = launched();
     if (r != CT_OK) return r;
   }
@@ -4000,10 +4031,11 @@ ct_status erase_chunks(ct_table* t, const BatchScratch& B, ct_pool* p, const uin
       if (r != CT_OK) return r;
       continue;
     }
-    dedup_chunk(t, v, RELEASE ? p->hdr : nullptr, kc, q, s);
-    launch(t, CT_KERNEL_ERASE, s, [&] { (q <= kAheadMax ? k_erase<RELEASE, true> : k_erase<RELEASE, false>)<<<gb, kBlock, 0, s>>>(v, kc, q, db - 1, ec); });
+    const int settle = gb <= kSettleBlocks;
+    dedup_chunk(t, v, RELEASE ? p->hdr : nullptr, kc, q, s, RELEASE);
+    launch(t, CT_KERNEL_ERASE, s, [&] { (q <= kAheadMax ? k_erase<RELEASE, true> : k_erase<RELEASE, false>)<<<gb, kBlock, 0, s>>>(v, kc, q, db - 1, ec, settle); });
     if (!RELEASE) {
-      launch(t, CT_KERNEL_APPLY, s, [&] { k_apply_count<<<1, 1024, 0, s>>>(v, gb, q, 1, 0); });
+      if (!settle) launch(t, CT_KERNEL_APPLY, s, [&] { k_apply_count<<<1, 1024, 0, s>>>(v, gb, q, 1, 0); });
     } else {
       const int inl = ntiles <= kInlineRankTiles ? ntiles : 0;
       if (!inl) launch(t, CT_KERNEL_RANK, s, [&] { k_tile_scan<<<1, 1024, 0, s>>>(v, p->hdr, ntiles, 2); });
@@ -4642,16 +4674,16 @@ ct_status insert_alloc_chunks(ct_table* t, const BatchScratch& B, ct_pool* p, co
     const int gb = group_blocks((q + kSlots - 1) / kSlots);
     const int ntiles = (int)((q + kTile - 1) / kTile);
     if (mc) {
-      launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_prologue<<<flat_blocks(db / 2), kBlock, 0, s>>>(v, p->hdr, db, q); });
+      launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_prologue<<<flat_blocks(db / 2), kBlock, 0, s>>>(v, p->hdr, db, q, 1); });
       launch(t, CT_KERNEL_DEDUP, s, [&] { k_dedup<<<flat_blocks(q), kBlock, 0, s>>>(v, kc, mc, q, db - 1); });
     } else {
-      dedup_chunk(t, v, p->hdr, kc, q, s);
+      dedup_chunk(t, v, p->hdr, kc, q, s, 1);
     }
-    launch(t, CT_KERNEL_INSERT, s, [&] { (q <= kAheadMax ? k_insert<1, true, true> : k_insert<1, true, false>)<<<gb, kBlock, 0, s>>>(v, kc, nullptr, q, db - 1, sc, vc, mc); });
+    launch(t, CT_KERNEL_INSERT, s, [&] { (q <= kAheadMax ? k_insert<1, true, true> : k_insert<1, true, false>)<<<gb, kBlock, 0, s>>>(v, kc, nullptr, q, db - 1, sc, vc, mc, 0); });
     const int inl = ntiles <= kInlineRankTiles ? ntiles : 0;
     if (!inl) launch(t, CT_KERNEL_RANK, s, [&] { k_tile_scan<<<1, 1024, 0, s>>>(v, p->hdr, ntiles, 1); });
     launch(t, CT_KERNEL_FINAL, s, [&] { k_final<1, 1><<<ntiles, kBlock, 0, s>>>(v, p->hdr, p->stack, kc, nullptr, q, sc, vc, inl); });
-    if (sc || vc) launch(t, CT_KERNEL_FIX, s, [&] { k_fix<<<flat_blocks((q + 3) / 4), kBlock, 0, s>>>(v, q, sc, vc); });
+    if (sc || vc) launch(t, CT_KERNEL_FIX, s, [&] { k_fix<<<flat_blocks((q + 3) / 4), kBlock, 0, s>>>(v, q, sc, vc, 1); });
     r = launched();
     if (r != CT_OK) return r;
   }
