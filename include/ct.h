@@ -427,10 +427,10 @@ ct_status ct_erase_release_batch(ct_table *t, ct_pool *p, const uint64_t *keys, 
    work enqueued by it has run) the batch runs in larger chunks, and a large insert of several keys
    per bucket brings the keys to the buckets.  Results are the same.
 
-   *bytes: what a batch of n keys can use now, for an insert (CT_OP_INSERT; also insert_alloc) or an
-   erase (CT_OP_ERASE); 0 when the table's own scratch serves it (a batch of one chunk, a chunk that
+   *bytes: what a batch of n keys can use now, for an insert (CT_OP_INSERT) or an erase
+   (CT_OP_ERASE), with pool != 0 for insert_alloc and erase_release; 0 when the table's own scratch serves it (a batch of one chunk, a chunk that
    the caller chose, or the large chunks of the largest tables).  Host only. */
-ct_status ct_workspace_bytes(const ct_table *t, int32_t op, int64_t n, int64_t *bytes);
+ct_status ct_workspace_bytes(const ct_table *t, int32_t op, int32_t pool, int64_t n, int64_t *bytes);
 
 /* ct_insert_batch, ct_erase_batch, ct_insert_alloc_batch (skip NULL) or ct_insert_alloc_batch_masked,
    and ct_erase_release_batch.  ws may be NULL, and a workspace smaller than ct_workspace_bytes is

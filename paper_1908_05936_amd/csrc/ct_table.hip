@@ -3722,6 +3722,7 @@ ct_status read_back(const T* dev, T* host, hipStream_t s) {
 struct BatchScratch {
   TableView v;
   int64_t chunk;
+  bool spec;  // it holds what speculative chunks need, and no more
 };
 
 // Chunk of a batch of n keys given a workspace: the whole batch up to 2^21 keys (228 MB), when that
@@ -3737,18 +3738,6 @@ int64_t workspace_chunk(const ct_table* t, int64_t n) {
   if (t->chunk_chosen || n <= t->chunk) return 0;
   const int64_t q = std::min<int64_t>(pow2ceil(n), kWorkspaceChunk);
   return q > t->chunk ? q : 0;
-}
-
-// The table's own scratch, or `ws` when it holds the chunk that the batch would like.
-BatchScratch batch_scratch(const ct_table* t, int64_t n, void* ws, int64_t ws_bytes) {
-  BatchScratch b = {t->v, t->chunk};
-  const int64_t q = ws ? workspace_chunk(t, n) : 0;
-  Layout L;
-  if (q && layout_scratch(&L, q, 0) && ws_bytes >= L.total) {
-    scratch_view(&b.v, static_cast<uint8_t*>(ws), L);
-    b.chunk = q;
-  }
-  return b;
 }
 
 // Resolve the repeated keys of one chunk: binned for large chunks, dd otherwise.  ranked: the kernel
@@ -3782,6 +3771,66 @@ bool use_speculation(const ct_table* t, int word) {
   const uint64_t f = __atomic_load_n(t->fb_host + word, __ATOMIC_RELAXED);
   const uint64_t fq = f >> 32, changed = f & 0xFFFFFFFFull;
   return fq == 0 || 2 * changed >= fq;
+}
+
+// The scratch of speculative chunks of q elements: the resolution's entries and the flags.
+int64_t spec_bytes(int64_t q) { return align_up(12 * q) + align_up(q); }
+
+// Whether a whole batch can and should run speculatively: it cannot reach capacity (an erase never
+// does), and the table's last chunk changed most of its keys.
+bool spec_wanted(const ct_table* t, bool erase, int64_t n) {
+  return (erase || t->size_ub + (uint64_t)n <= (uint64_t)t->desc.capacity) &&
+         use_speculation(t, erase ? 1 : 0);
+}
+
+// Chunk of a speculative batch given a workspace.  13 bytes a key instead of 109 make chunks of 2^23
+// keys affordable (109 MB): 6,000,000 keys into an empty map took 500 us in chunks of 2^21, 475 in
+// one; 2^22 keys erased and inserted again in a table of 2^24 800, now 779.
+constexpr int64_t kSpecChunk = (int64_t)1 << 23;
+
+int64_t spec_chunk(const ct_table* t, int64_t n) {
+  if (t->chunk_chosen || n <= t->chunk) return 0;
+  const int64_t q = std::min<int64_t>(pow2ceil(n), kSpecChunk);
+  return q > t->chunk ? q : 0;
+}
+
+enum BatchKind : int { bInsert, bErase, bPool };  // bPool: insert_alloc and erase_release
+
+// What a batch of n keys can use.
+int64_t batch_bytes(const ct_table* t, BatchKind kind, int64_t n) {
+  if (kind != bPool && spec_wanted(t, kind == bErase, n)) {
+    const int64_t q = spec_chunk(t, n);
+    return q ? spec_bytes(q) : 0;
+  }
+  Layout L;
+  const int64_t q = workspace_chunk(t, n);
+  return q && layout_scratch(&L, q, 0) ? L.total : 0;
+}
+
+// The table's own scratch, or `ws` when it holds the chunk that the batch would like.  (A workspace
+// that was sized for a speculative batch makes the batch one, whatever the table's last chunk has
+// reported since.)
+BatchScratch batch_scratch(const ct_table* t, BatchKind kind, int64_t n, void* ws, int64_t ws_bytes) {
+  BatchScratch b = {t->v, t->chunk, false};
+  if (!ws) return b;
+  uint8_t* base = static_cast<uint8_t*>(ws);
+  const int64_t q = workspace_chunk(t, n);
+  Layout L;
+  const bool full = q && layout_scratch(&L, q, 0) && ws_bytes >= L.total;
+  const int64_t sq = kind == bPool ? 0 : spec_chunk(t, n);
+  const bool can = kind == bErase ||
+                   (kind == bInsert && t->size_ub + (uint64_t)n <= (uint64_t)t->desc.capacity);
+  if (sq && can && t->insert_path != CT_INSERT_RESOLVE_FIRST && ws_bytes >= spec_bytes(sq) &&
+      (!full || use_speculation(t, kind == bErase ? 1 : 0))) {
+    b.v.dd = reinterpret_cast<uint64_t*>(base);
+    b.v.flag = base + align_up(12 * sq);
+    b.chunk = sq;
+    b.spec = true;
+  } else if (full) {
+    scratch_view(&b.v, base, L);
+    b.chunk = q;
+  }
+  return b;
 }
 
 // A chunk of at least this many keys that the host cannot prove to stay below capacity enqueues both
@@ -3965,7 +4014,7 @@ ct_status insert_chunks(ct_table* t, const BatchScratch& B, const uint64_t* keys
       if (r != CT_OK) return r;
       continue;
     }
-    if (surely_fast && use_speculation(t, 0)) {
+    if (surely_fast && (B.spec || use_speculation(t, 0))) {
       // speculative: insert first, then resolve the copies of keys listed as ambiguous
       launch(t, CT_KERNEL_INSERT, s, [&] { (q <= kAheadMax ? k_insert_spec<VK, true> : k_insert_spec<VK, false>)<<<gb, kBlock, 0, s>>>(v, kc, vc, q, sc, 0); });
       spec_resolve<VK, false>(t, v, kc, vc, q, sc, db, s);
@@ -4023,7 +4072,7 @@ ct_status erase_chunks(ct_table* t, const BatchScratch& B, ct_pool* p, const uin
       if (r != CT_OK) return r;
       continue;
     }
-    if (!RELEASE && use_speculation(t, 1)) {
+    if (!RELEASE && (B.spec || use_speculation(t, 1))) {
       // speculative: remove first, then move each removal to the lowest copy of its key
       launch(t, CT_KERNEL_ERASE, s, [&] { (q <= kAheadMax ? k_erase_spec<true> : k_erase_spec<false>)<<<gb, kBlock, 0, s>>>(v, kc, q, ec); });
       spec_resolve<0, true>(t, v, kc, nullptr, q, ec, db, s);
@@ -4223,7 +4272,7 @@ ct_status ct_insert_batch_ws(ct_table* t, const uint64_t* keys, const void* vals
     if (vk == CT_VAL_U64) return part_insert<2>(t, P, w, keys, vals, n, status, S(stream));
     return part_insert<0>(t, P, w, keys, nullptr, n, status, S(stream));
   }
-  return insert_any(t, batch_scratch(t, n, ws, ws_bytes), keys, vals, n, status, S(stream));
+  return insert_any(t, batch_scratch(t, bInsert, n, ws, ws_bytes), keys, vals, n, status, S(stream));
 }
 
 ct_status ct_insert_batch(ct_table* t, const uint64_t* keys, const void* vals, int64_t n,
@@ -4231,16 +4280,12 @@ ct_status ct_insert_batch(ct_table* t, const uint64_t* keys, const void* vals, i
   return ct_insert_batch_ws(t, keys, vals, n, status, nullptr, 0, stream);
 }
 
-ct_status ct_workspace_bytes(const ct_table* t, int32_t op, int64_t n, int64_t* bytes) {
+ct_status ct_workspace_bytes(const ct_table* t, int32_t op, int32_t pool, int64_t n, int64_t* bytes) {
   if (!t || n < 0 || !bytes || (op != CT_OP_INSERT && op != CT_OP_ERASE)) return CT_E_INVALID;
   PartLayout P;
-  if (op == CT_OP_INSERT && part_wanted(t, n, &P)) {
-    *bytes = P.total;
-    return CT_OK;
-  }
-  Layout L;
-  const int64_t q = workspace_chunk(t, n);
-  *bytes = q && layout_scratch(&L, q, 0) ? L.total : 0;
+  *bytes = op == CT_OP_INSERT && !pool && part_wanted(t, n, &P)
+               ? P.total
+               : batch_bytes(t, pool ? bPool : op == CT_OP_ERASE ? bErase : bInsert, n);
   return CT_OK;
 }
 
@@ -4260,7 +4305,7 @@ ct_status ct_erase_batch_ws(ct_table* t, const uint64_t* keys, int64_t n, uint8_
   ct_status r = check_batch(t, keys, n, ws, ws_bytes);
   if (r != CT_OK) return r;
   if (n == 0) return CT_OK;
-  return erase_chunks<false>(t, batch_scratch(t, n, ws, ws_bytes), nullptr, keys, n, erased,
+  return erase_chunks<false>(t, batch_scratch(t, bErase, n, ws, ws_bytes), nullptr, keys, n, erased,
                              S(stream));
 }
 
@@ -4701,7 +4746,7 @@ ct_status ct_insert_alloc_batch_ws(ct_table* t, ct_pool* p, const uint64_t* keys
   if (r != CT_OK || !p) return CT_E_INVALID;
   if (t->desc.val_kind != CT_VAL_U32) return CT_E_INVALID;
   if (n == 0) return CT_OK;
-  return insert_alloc_chunks(t, batch_scratch(t, n, ws, ws_bytes), p, keys, skip, n, vals_out,
+  return insert_alloc_chunks(t, batch_scratch(t, bPool, n, ws, ws_bytes), p, keys, skip, n, vals_out,
                              status, S(stream));
 }
 
@@ -4723,7 +4768,7 @@ ct_status ct_erase_release_batch_ws(ct_table* t, ct_pool* p, const uint64_t* key
   if (r != CT_OK || !p) return CT_E_INVALID;
   if (t->desc.val_kind != CT_VAL_U32) return CT_E_INVALID;
   if (n == 0) return CT_OK;
-  return erase_chunks<true>(t, batch_scratch(t, n, ws, ws_bytes), p, keys, n, erased, S(stream));
+  return erase_chunks<true>(t, batch_scratch(t, bPool, n, ws, ws_bytes), p, keys, n, erased, S(stream));
 }
 
 ct_status ct_erase_release_batch(ct_table* t, ct_pool* p, const uint64_t* keys, int64_t n,
@@ -4798,9 +4843,9 @@ ct_status run_op(const PlanOp& o, hipStream_t s) {
       launch(t, CT_KERNEL_CLEAR, s, [&] { k_table_reset<<<flat_blocks((int64_t)t->v.nb * kSlots), kBlock, 0, s>>>(t->v, 0); });
       return launched();
     case kOpInsert:
-      return insert_any(t, BatchScratch{t->v, t->chunk}, o.keys, o.vals, o.n, o.flags, s);
+      return insert_any(t, BatchScratch{t->v, t->chunk, false}, o.keys, o.vals, o.n, o.flags, s);
     case kOpErase:
-      return erase_chunks<false>(t, BatchScratch{t->v, t->chunk}, nullptr, o.keys, o.n, o.flags, s);
+      return erase_chunks<false>(t, BatchScratch{t->v, t->chunk, false}, nullptr, o.keys, o.n, o.flags, s);
     default: {
       launch(t, CT_KERNEL_FIND, s, [&] { find_kernel(vk, s, t->v, o.keys, o.n, o.vout, o.flags); });
       return launched();
@@ -5444,7 +5489,7 @@ ct_status ct_insert_batch_noalloc(ct_table* t, const uint64_t* keys, const void*
   w.bcur = nullptr;
   w.dfirst = nullptr;
   const int64_t chunk = std::min<int64_t>(t->chunk, kStaticChunk);
-  return insert_any(t, BatchScratch{w, chunk}, keys, vals, n, status, s);
+  return insert_any(t, BatchScratch{w, chunk, false}, keys, vals, n, status, s);
 }
 
 }  // extern "C"

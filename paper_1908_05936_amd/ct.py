@@ -103,7 +103,7 @@ SIGNATURES = {
     "ct_insert_alloc_batch": (C.c_int, [_P, _P, _P, _I64, _P, _P, _P]),
     "ct_insert_alloc_batch_masked": (C.c_int, [_P, _P, _P, _P, _I64, _P, _P, _P]),
     "ct_erase_release_batch": (C.c_int, [_P, _P, _P, _I64, _P, _P]),
-    "ct_workspace_bytes": (C.c_int, [_P, _I32, _I64, _PI64]),
+    "ct_workspace_bytes": (C.c_int, [_P, _I32, _I32, _I64, _PI64]),
     "ct_insert_batch_ws": (C.c_int, [_P, _P, _P, _I64, _P, _P, _I64, _P]),
     "ct_erase_batch_ws": (C.c_int, [_P, _P, _I64, _P, _P, _I64, _P]),
     "ct_insert_alloc_batch_ws": (C.c_int, [_P, _P, _P, _P, _I64, _P, _P, _P, _I64, _P]),
@@ -312,7 +312,7 @@ class Table:
     def value_dtype(self):
         return _VAL_DTYPE.get(self.value_kind)
 
-    def _workspace(self, n: int, op: int):
+    def _workspace(self, n: int, op: int, pool: bool = False):
         """(workspace tensor or None, its bytes) for a batch of n keys.  It comes from torch's
         allocator on the current stream, so a later tensor takes its memory only after this call's
         kernels.  Without the memory, and while the stream is captured into a graph (which would
@@ -320,7 +320,7 @@ class Table:
         if n <= self.chunk or torch.cuda.is_current_stream_capturing():
             return None, 0
         nb = C.c_int64(0)
-        _check(lib().ct_workspace_bytes(self._h, op, n, C.byref(nb)), "ct_workspace_bytes")
+        _check(lib().ct_workspace_bytes(self._h, op, pool, n, C.byref(nb)), "ct_workspace_bytes")
         if nb.value == 0:
             return None, 0
         try:
@@ -376,7 +376,7 @@ class Table:
         _need(keys, torch.int64, None, "keys", self.device)
         out = torch.empty(n, dtype=torch.int32, device=self.device)
         st = torch.empty(n, dtype=torch.uint8, device=self.device)
-        ws, nb = self._workspace(n, OP_INSERT)
+        ws, nb = self._workspace(n, OP_INSERT, True)
         _check(lib().ct_insert_alloc_batch_ws(self._h, pool._h, _ptr(keys), None, n, _ptr(out),
                                               _ptr(st), _ptr(ws), nb, _stream(self.device)),
                "ct_insert_alloc_batch")
@@ -393,7 +393,7 @@ class Table:
             out = torch.full((n,), -1, dtype=torch.int32, device=self.device)
         if status is None:
             status = torch.full((n,), 0xFF, dtype=torch.uint8, device=self.device)
-        ws, nb = self._workspace(n, OP_INSERT)
+        ws, nb = self._workspace(n, OP_INSERT, True)
         _check(lib().ct_insert_alloc_batch_ws(self._h, pool._h, _ptr(keys), _ptr(skip), n, _ptr(out),
                                               _ptr(status), _ptr(ws), nb, _stream(self.device)),
                "ct_insert_alloc_batch_masked")
@@ -403,7 +403,7 @@ class Table:
         n = keys.numel()
         _need(keys, torch.int64, None, "keys", self.device)
         er = torch.empty(n, dtype=torch.uint8, device=self.device)
-        ws, nb = self._workspace(n, OP_ERASE)
+        ws, nb = self._workspace(n, OP_ERASE, True)
         _check(lib().ct_erase_release_batch_ws(self._h, pool._h, _ptr(keys), n, _ptr(er), _ptr(ws),
                                                nb, _stream(self.device)), "ct_erase_release_batch")
         return er

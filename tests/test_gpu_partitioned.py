@@ -16,14 +16,16 @@ pytestmark = pytest.mark.gpu
 N = 1 << 23   # the smallest batch that takes the path
 
 
-def workspace(t, op, n):
+def workspace(t, op, pool, n):
     nb = C.c_int64(0)
-    assert ct.lib().ct_workspace_bytes(t._h, op, n, C.byref(nb)) == ct.CT_OK
+    assert ct.lib().ct_workspace_bytes(t._h, op, pool, n, C.byref(nb)) == ct.CT_OK
     return nb.value
 
 
 def partitioned(t, n):
-    return workspace(t, ct.OP_INSERT, n) != workspace(t, ct.OP_ERASE, n)
+    """Its workspace is neither that of speculative chunks (as an erase's) nor the general one."""
+    return workspace(t, ct.OP_INSERT, 0, n) not in (workspace(t, ct.OP_ERASE, 0, n),
+                                                    workspace(t, ct.OP_ERASE, 1, n))
 
 
 def values(rng, bits, n):

@@ -45,13 +45,26 @@ def test_batch_beyond_the_workspace_chunk(dev):  # noqa: F811
     p.same_state()
 
 
+def test_speculative_batch_beyond_its_chunk(dev):  # noqa: F811
+    """2^23 keys is the largest speculative chunk: copies of a key on both sides of its end."""
+    rng = rng_for(7303)
+    n = (1 << 23) + 77
+    p = Pair(dev, n + 1000, 32, bucket_count=n // 2, path=ct.INSERT_SPECULATIVE)
+    keys = np.concatenate([distinct_u64(rng, n - 2), RESERVED])
+    k = keys[rng.permutation(n)]
+    k[-70:] = k[:70]
+    p.insert(k, np.arange(n, dtype=np.uint32))
+    p.erase(k[::-1])
+    p.same_state()
+
+
 def test_workspace_arguments(dev):  # noqa: F811
     t = ct.Table(5000, ct.VAL_NONE, device=dev)
     nb = C.c_int64(0)
     L = ct.lib()
-    assert L.ct_workspace_bytes(t._h, ct.OP_INSERT, t.chunk, C.byref(nb)) == ct.CT_OK and nb.value == 0
-    assert L.ct_workspace_bytes(t._h, ct.OP_INSERT, t.chunk + 1, C.byref(nb)) == ct.CT_OK and nb.value > 0
-    assert L.ct_workspace_bytes(t._h, ct.OP_INSERT, -1, C.byref(nb)) == ct.CT_E_INVALID
+    assert L.ct_workspace_bytes(t._h, ct.OP_INSERT, 0, t.chunk, C.byref(nb)) == ct.CT_OK and nb.value == 0
+    assert L.ct_workspace_bytes(t._h, ct.OP_INSERT, 0, t.chunk + 1, C.byref(nb)) == ct.CT_OK and nb.value > 0
+    assert L.ct_workspace_bytes(t._h, ct.OP_INSERT, 0, -1, C.byref(nb)) == ct.CT_E_INVALID
     keys = g64(distinct_u64(rng_for(7302), 3000), dev)
     ws = torch.empty(nb.value, dtype=torch.uint8, device=dev)
     args = (t._h, ct._ptr(keys), None, 3000, None)
@@ -60,4 +73,4 @@ def test_workspace_arguments(dev):  # noqa: F811
     assert L.ct_insert_batch_ws(*args, ws.data_ptr(), 256, s) == ct.CT_OK       # too small: unused
     assert t.size() == 3000 and t.check() == 0
     own = ct.Table(5000, ct.VAL_NONE, chunk=1024, device=dev)                   # a chosen chunk stays
-    assert L.ct_workspace_bytes(own._h, ct.OP_INSERT, 4096, C.byref(nb)) == ct.CT_OK and nb.value == 0
+    assert L.ct_workspace_bytes(own._h, ct.OP_INSERT, 0, 4096, C.byref(nb)) == ct.CT_OK and nb.value == 0
