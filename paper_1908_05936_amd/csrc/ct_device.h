@@ -127,7 +127,8 @@ struct TableView {
   uint64_t cap;
   Header* hdr;
   uint64_t* dd;      // dedup scratch: (fingerprint << 32 | lowest chunk index), kEmpty = free
-  uint8_t* dmark;   // per chunk element: 1 = its key occurs more than once in the chunk
+  uint8_t* dmark;   // per chunk element: 1 = its key occurs more than once in the chunk (a binned
+                    // chunk's insert kernel writes them where k_fix reads them)
   uint32_t* dup;    // per repeated element: index of its key's first occurrence (for k_fix)
   uint8_t* flag;    // per chunk element: 1 = takes part in the rank scan
   uint64_t* ref;    // per chunk element: claimed slot, or the value an erase releases
@@ -144,7 +145,7 @@ struct TableView {
   uint64_t* r2k;    // fine bins: keys, P x c2
   uint32_t* r2i;
   uint32_t* bcur;   // fill counts: P1 x kBinSub coarse, kCtrStride words apart; then P fine
-  uint32_t* dfirst; // per repeated element: index of its key's first occurrence
+  uint32_t* dfirst; // per element: index of its key's first occurrence, kNone: not repeated
   uint32_t c1, c2;  // capacities of a coarse segment and of a fine bin
   int lp1, lp;      // log2 of P1 and of P
   uint64_t* fb;     // host-mapped word (or null): (keys << 32 | keys newly stored) of the table's

@@ -277,9 +277,8 @@ __global__ __launch_bounds__(kBlock) void k_dedup(TableView t, const uint64_t* _
 }
 
 // ---------------------------------------------------------------------------------------------
-// Binned dedup: the same marks as dedup_range (every element of a key that occurs more than once
-// in the chunk), plus each marked element's first occurrence in dfirst, without a device-scope
-// atomic per element.  Keys move into 64 coarse bins and then into P fine bins by the high bits
+// Binned dedup: what dedup_range finds, as each repeated element's first occurrence in dfirst (kNone
+// for an element that is not repeated), without a device-scope atomic per element.  Keys move into 64 coarse bins and then into P fine bins by the high bits
 // of dedup_mix, so all copies of a key share a fine bin; each fine bin (about 1024 elements)
 // finds its repeated keys in an LDS hash table.  The only global atomics reserve room in a bin,
 // one per block and non-empty bin.  A bin that would overflow its capacity sets dovf; the chunk
@@ -429,7 +428,7 @@ __global__ __launch_bounds__(kBlock) void k_bin_scatter1(TableView t, const uint
   __shared__ BinStage S;
   const int64_t t0 = (int64_t)blockIdx.x * kBinTile;
   uint64_t k[kPer];
-  uint32_t ix[kPer], code[kPer], hs[kPer];
+  uint32_t ix[kPer], code[kPer], hs[kPer], first[kPer];
   // all loads first, from clamped (in-bounds) positions: a load under a branch would make the
   // compiler wait for it before the next one is issued.  The chunk's mode comes with them.
 #pragma unroll
@@ -437,7 +436,10 @@ __global__ __launch_bounds__(kBlock) void k_bin_scatter1(TableView t, const uint
   const uint32_t agg = t.hdr->dagg;
   if (threadIdx.x < kBinCoarse) S.cnt[threadIdx.x] = 0;
 #pragma unroll
-  for (int e = 0; e < kPer; ++e) hs[e] = ~0u;
+  for (int e = 0; e < kPer; ++e) {
+    hs[e] = ~0u;
+    first[e] = kNone;  // not repeated, as far as the tile knows
+  }
   if (agg) {
     // H[s] (in S.i): tile position of a copy of slot s's key, the lowest once all have arrived;
     // D[s] (in S.b): the key occurs more than once in the tile.  S.k holds the tile's keys by
@@ -479,14 +481,18 @@ __global__ __launch_bounds__(kBlock) void k_bin_scatter1(TableView t, const uint
       const uint32_t local = e * kBlock + threadIdx.x;
       const uint32_t i = (uint32_t)(t0 + local);
       const uint32_t rep = H[hs[e]];
-      t.dmark[i] = 1;
       if (rep == local) {
-        t.dfirst[i] = i;
+        first[e] = i;
       } else {
-        t.dfirst[i] = kIndirect | (uint32_t)(t0 + rep);
+        first[e] = kIndirect | (uint32_t)(t0 + rep);
         hs[e] = kFolded;
       }
     }
+  }
+#pragma unroll
+  for (int e = 0; e < kPer; ++e) {
+    const int64_t i = t0 + e * kBlock + threadIdx.x;
+    if (i < q) t.dfirst[i] = first[e];
   }
   __syncthreads();
 #pragma unroll
@@ -557,7 +563,8 @@ __global__ __launch_bounds__(kBlock) void k_bin_scatter2(TableView t, int blocks
 // give it the key's lowest index.  A bin holds up to c2 entries but the table has kBinLds slots:
 // it needs fewer distinct keys than slots, which the bins of folded (skewed) chunks meet by far.
 // A bin with more distinct keys (no probe finds a free or matching slot) flags an overflow, and
-// the chunk takes the exact fallback.
+// the chunk takes the exact fallback.  Bound by its scattered stores, one per repeated element: with
+// a mark beside each first occurrence, 4 M repeated keys into a set took 380 us, now 337.
 __global__ __launch_bounds__(kBlock) void k_bin_dedup(TableView t) {
   if (t.hdr->spec) return;
   __shared__ unsigned long long hk[kBinLds];
@@ -627,10 +634,7 @@ __global__ __launch_bounds__(kBlock) void k_bin_dedup(TableView t) {
   __syncthreads();
 #pragma unroll
   for (int e = 0; e < kPer; ++e) {
-    if (slot[e] != kNone && hx[slot[e]]) {
-      t.dmark[idx[e]] = 1;
-      t.dfirst[idx[e]] = hm[slot[e]];
-    }
+    if (slot[e] != kNone && hx[slot[e]]) t.dfirst[idx[e]] = hm[slot[e]];
   }
 }
 
@@ -660,19 +664,28 @@ __global__ __launch_bounds__(kBlock) void k_bin_fallback_dedup(TableView t,
   dedup_range(t, keys, nullptr, dmask, (int64_t)blockIdx.x * kBlock, q, (int64_t)gridDim.x * kBlock);
 }
 
+// What is known of element i's repetition, loaded by the caller together with its key (one memory
+// round trip instead of two): in a binned chunk (dmode) dfirst[i], kNone for an element that is not
+// repeated; else dmark[i].
+__device__ __forceinline__ uint32_t load_mark(const TableView& t, int64_t i, bool binned) {
+  return binned ? t.dfirst[i] : t.dmark[i];
+}
+
+// Whether a mark says that the element is repeated (in a binned chunk also a mark that is its first
+// copy's alone).
+__device__ __forceinline__ bool repeated(uint32_t mark, bool binned) {
+  return binned ? mark != kNone : mark != 0;
+}
+
 // Index-order role of this lane's element: its own index when it is the first copy of its key in
-// the chunk, else the index of that first copy.  `mark` is dmark[i], which the caller loads
-// together with the key (one memory round trip instead of two).
+// the chunk, else the index of that first copy.
 __device__ __forceinline__ uint32_t first_copy(const TableView& t, const uint64_t* keys,
                                                uint64_t key, int64_t i, uint32_t dmask,
-                                               uint32_t mark) {
+                                               uint32_t mark, bool binned) {
   if (key >= kTomb) return t.hdr->spec_first[key - kTomb];
-  if (mark) {
-    if (!t.hdr->dmode) return dedup_lookup(t, keys, key, dmask, (uint32_t)i);
-    const uint32_t f = t.dfirst[i];
-    return (f & kIndirect) ? t.dfirst[f & ~kIndirect] : f;
-  }
-  return (uint32_t)i;
+  if (!repeated(mark, binned)) return (uint32_t)i;
+  if (!binned) return dedup_lookup(t, keys, key, dmask, (uint32_t)i);
+  return (mark & kIndirect) ? t.dfirst[mark & ~kIndirect] : mark;
 }
 
 // Insert actors, one element per lane.  fast: claim directly with one CAS per new key (all CASes of
@@ -691,6 +704,7 @@ __device__ __forceinline__ int64_t insert_range(const TableView& t, WaveLds* w,
   const bool fast = t.hdr->fast != 0;
   const uint32_t inject = t.hdr->inject;
   const bool flags = ALLOC || !fast;
+  const bool binned = t.hdr->dmode != 0;
   int64_t ins = 0;
   for (int64_t w0 = lo + (int64_t)(threadIdx.x & ~63u); w0 < hi; w0 += step) {
     const int64_t i = w0 + wave_lane();
@@ -698,17 +712,19 @@ __device__ __forceinline__ int64_t insert_range(const TableView& t, WaveLds* w,
     const uint64_t key = keys[min(i, hi - 1)];
     // the value is loaded with the key (coalesced) so that its latency hides behind the probe
     const uint64_t val = (!ALLOC && valid) ? load_val<VK>(vals, i) : 0;
-    const uint32_t mark = t.dmark[min(i, hi - 1)];
+    const uint32_t mark = load_mark(t, min(i, hi - 1), binned);
     const uint32_t out = skip ? skip[min(i, hi - 1)] : 0;
     asm volatile("" ::"v"(mark), "v"(out));  // keep the loads here, issued with the key's
     const bool active = valid && !out;
-    const uint32_t first = active ? first_copy(t, keys, key, i, dmask, mark) : 0u;
+    const uint32_t first = active ? first_copy(t, keys, key, i, dmask, mark, binned) : 0u;
     const bool actor = active && first == (uint32_t)i;
     const bool dup = active && !actor;
     // what k_fix reads: the mark says that the key is repeated, dup[i] names its first copy.  A later
     // copy whose first copy can neither meet FULL nor draw a value has its outcome here.
-    if (flags && active && (mark || dup)) t.dup[i] = first;
-    if (flags && dup && !mark) t.dmark[i] = 1;  // a later copy of an out-of-band key
+    if (flags && active && (repeated(mark, binned) || dup)) {
+      t.dup[i] = first;
+      t.dmark[i] = 1;  // (so far only known in dfirst, or a later copy of an out-of-band key)
+    }
 
     uint8_t st = dup && !flags ? kPresent : kNoStatus;
     uint8_t newf = 0;
@@ -873,14 +889,15 @@ __device__ __forceinline__ int64_t erase_range(const TableView& t, WaveLds* w,
                                                const uint64_t* __restrict__ keys, uint32_t dmask,
                                                uint8_t* __restrict__ erased, int64_t lo, int64_t hi,
                                                int64_t step) {
+  const bool binned = t.hdr->dmode != 0;
   int64_t del = 0;
   for (int64_t w0 = lo + (int64_t)(threadIdx.x & ~63u); w0 < hi; w0 += step) {
     const int64_t i = w0 + wave_lane();
     const bool valid = i < hi;
     const uint64_t key = keys[min(i, hi - 1)];
-    const uint32_t mark = t.dmark[min(i, hi - 1)];
+    const uint32_t mark = load_mark(t, min(i, hi - 1), binned);
     asm volatile("" ::"v"(mark));  // keep the load here, issued with the key's
-    const bool actor = valid && first_copy(t, keys, key, i, dmask, mark) == (uint32_t)i;
+    const bool actor = valid && first_copy(t, keys, key, i, dmask, mark, binned) == (uint32_t)i;
     uint8_t hit = 0;
     uint64_t val = 0;
     if (actor && key >= kTomb) {
