@@ -2,7 +2,7 @@
 //
 // Layout of a table buffer (one caller-owned device allocation):
 //   [Header, 256 B][buckets: nb x 128 B][dedup scratch, or the bins of the binned dedup with the
-//   dedup scratch aliasing the coarse bins][marks][dup list][flags][refs][tile sums][block sums]
+//   dedup scratch aliasing the coarse bins][marks][first copies][flags][refs][tile sums][block sums]
 //
 // Buckets.  A bucket is one 128-byte line of 8 slots {u64 key, u64 value}.  A key's probe
 // sequence starts at its home bucket and steps by a key-dependent stride (double hashing) that
@@ -18,10 +18,9 @@
 // when its bucket already holds a kEmpty slot (no probe sequence passes such a bucket) and kTomb
 // otherwise.
 //
-// Cooperation.  Eight lanes of a wave64 probe one key: lane j loads slot j of the bucket (one
-// 16-byte load per lane, one 128-byte line per group), a ballot answers "which slot matches /
-// is empty", and a shuffle broadcasts the matching value.  A wave therefore has eight keys in
-// flight per step.
+// Cooperation.  A wave64 takes 64 keys, one per lane, and probes them in packed rounds (ct_probe.h):
+// eight lanes read one 128-byte bucket line together, 16 bytes each, and every lane gets the answer
+// of its own key's bucket.
 #pragma once
 
 #include <hip/hip_runtime.h>

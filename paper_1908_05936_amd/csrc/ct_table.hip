@@ -1,22 +1,30 @@
 // ct_table.hip -- gfx950 kernels and the C ABI of the batch hash containers and index pool.
 //
 // Operation pipelines (every kernel on the caller's stream, in this order):
-//   find           : k_find                                    one launch, read-only, lock-free
-//   insert (chunk) : k_prologue -> k_dedup -> k_insert [-> k_tile_count -> k_tile_scan -> k_final]
-//                    -> k_fix
-//   insert_alloc   : k_prologue -> k_dedup -> k_insert -> k_tile_count -> k_tile_scan -> k_final
-//                    -> k_fix
-//   erase          : k_prologue -> k_dedup -> k_erase
-//   erase_release  : k_prologue -> k_dedup -> k_erase -> k_tile_count -> k_tile_scan -> k_final
+//   find             : k_find                                  one launch, read-only, lock-free
+//   2048 keys or less: k_small                                 the whole insert or erase in one launch
+//   speculative      : k_insert_spec or k_erase_spec -> k_spec_clear -> k_spec_build ->
+//   insert, erase      k_spec_probe -> k_spec_swap
+//   large insert of  : k_part_coarse -> (k_part_fine -> k_part_insert) per group -> k_part_left ->
+//   several keys per   k_part_over -> the resolution as above
+//   bucket
+//   resolve-first    : k_prologue -> k_dedup -> k_insert [-> k_final -> k_fix where FULL can be met]
+//   insert
+//   insert_alloc     : k_prologue -> k_dedup -> k_insert -> k_final -> k_fix
+//   erase            : k_prologue -> k_dedup -> k_erase
+//   erase_release    : k_prologue -> k_dedup -> k_erase -> k_final
+// Chunks of 2^16 keys or more resolve repeated keys with k_bin_* in the place of k_dedup; grids that do
+// not settle their counters themselves are followed by k_apply_count, and large ranked chunks by
+// k_tile_count and k_tile_scan.
 //
-// Index-order semantics.  k_dedup records, per distinct key of the chunk, the lowest chunk index
-// holding it (an atomic min in a cache-resident scratch table).  Only that element (the "actor")
-// touches the table; later copies are resolved afterwards from its outcome (k_fix), which gives
-// exactly the results of a sequential replay.  Distinct actors never race on one key, so a claim
-// CAS can only fail because another key took the slot.  When a chunk might reach capacity or
-// empty the pool, or when values come from a pool, the new actors are ranked by an exclusive scan
-// in index order (k_tile_count / k_tile_scan) and k_final hands out capacity and pool entries by
-// rank, so the k-th new key of the chunk is the k-th to be stored, as in the sequential replay.
+// Index-order semantics, resolve-first.  k_dedup records, per distinct key of the chunk, the lowest
+// chunk index holding it (an atomic min in a cache-resident scratch table).  Only that element (the
+// "actor") touches the table; later copies are resolved from its outcome, which gives exactly the
+// results of a sequential replay.  Distinct actors never race on one key, so a claim CAS can only
+// fail because another key took the slot.  When a chunk might reach capacity or empty the pool, or
+// when values come from a pool, the new actors are ranked by an exclusive scan in index order and
+// k_final hands out capacity and pool entries by rank, so the k-th new key of the chunk is the k-th
+// to be stored, as in the sequential replay.
 #include <hip/hip_cooperative_groups.h>
 #include <hip/hip_runtime.h>
 
@@ -3180,7 +3188,7 @@ __device__ __forceinline__ void g_dedup_body(const GStep* __restrict__ st, const
 }
 
 // The grouped find / insert / erase stages run with BS threads per block (the plan's block size):
-// the range code strides by the step's blocks times BS, 8 lanes per key group as always.
+// the range code strides by the step's blocks times BS.
 template <int BS>
 __device__ __forceinline__ void g_insert_body(const GStep* __restrict__ st, const GLoc L) {
   const GStep g = g_step(st, L);
@@ -3703,7 +3711,7 @@ int64_t bin_prologue_units_host(const TableView& v, int64_t q) {
   return (q + 15) / 16 + ((int64_t)kCoarseCtrWords + ((int64_t)1 << v.lp)) / 4;
 }
 
-// Blocks of `bs` threads for n key groups of 8 lanes (at most kMaxGroupBlocks: the count
+// Blocks of `bs` threads for n groups of eight keys (at most kMaxGroupBlocks: the count
 // partials of one launch).
 int group_blocks(int64_t n, int bs = kBlock) {
   const int64_t b = (n + (bs / 8) - 1) / (bs / 8);
@@ -3996,10 +4004,10 @@ ct_status part_insert(ct_table* t, const PartLayout& L, uint8_t* ws, const uint6
   v.dd = P.r1k;
   t->size_ub = std::min<uint64_t>(t->size_ub + (uint64_t)n, (uint64_t)t->desc.capacity);
   launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_purge_clear<<<flat_blocks(L.ctr_words), kBlock, 0, s>>>(P.cur1, L.ctr_words); });
-  launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_part_coarse<VK><<<(int)((n + kBinTile - 1) / kBinTile), kBlock, 0, s>>>(v, P, keys, vals, n, (int)L.ncoarse, status); });
+  launch(t, CT_KERNEL_INSERT, s, [&] { k_part_coarse<VK><<<(int)((n + kBinTile - 1) / kBinTile), kBlock, 0, s>>>(v, P, keys, vals, n, (int)L.ncoarse, status); });
   for (int64_t c0 = 0; c0 < L.ncoarse; c0 += L.group) {
     const int64_t nc = (std::min(L.group, L.ncoarse - c0) + kPartXcds - 1) / kPartXcds * kPartXcds;
-    launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_part_fine<VK><<<(int)(nc * kBinSub * L.blocks_per_seg), kBlock, 0, s>>>(v, P, (int)c0, (int)L.ncoarse, (int)L.blocks_per_seg); });
+    launch(t, CT_KERNEL_INSERT, s, [&] { k_part_fine<VK><<<(int)(nc * kBinSub * L.blocks_per_seg), kBlock, 0, s>>>(v, P, (int)c0, (int)L.ncoarse, (int)L.blocks_per_seg); });
     launch(t, CT_KERNEL_INSERT, s, [&] { k_part_insert<VK><<<(int)(nc << L.lp2), kPartThreads, 0, s>>>(v, P, (int)c0, status); });
   }
   const int lb = (int)std::max<int64_t>(1, 2048 / L.ncoarse);
