@@ -316,12 +316,14 @@ ct_status ct_dev_pool_apply(ct_pool *p, int32_t op, const int32_t *in, int64_t n
 /* Read and clear the sticky error word (CT_ERR_* bits).  Synchronises. */
 ct_status ct_get_error(ct_table *t, uint32_t *h_err, void *stream);
 
-/* Test hook, not for production use: from now on (clear keeps it, 0 switches it off), the first
-   claim attempt of every insert element whose index within its chunk is a multiple of `every` is
-   treated as lost to another key, as when a concurrent insert took the slot first (the rare
-   failed attempt of Section 4 that further attempts resolve).  The slot stays free, so the
-   element's retry path claims it; results are unchanged.  Also applies to ct_table_rehash into
-   this table (by source slot).  Enqueued on `stream`. */
+/* Test hook, not for production use: from now on (clear keeps it, 0 switches it off), about one key
+   in `every`, chosen by its hash, loses its claim of the first slot in its order in each bucket where
+   it claims and that slot is free, as when a concurrent insert took the slot first (the rare failed attempt
+   of Section 4 that further attempts resolve).  The key asks for the bucket's other free slots, and
+   for that one again when they are gone; results are unchanged, keys may lie in other slots.
+   Applies to the batch inserts, except where a batch ranks its new keys before they claim (it may
+   reach capacity, or empty the pool, in a chunk of more than 2048 keys), and to ct_table_rehash
+   into this table.  Enqueued on `stream`. */
 ct_status ct_table_debug_inject_claim_losses(ct_table *t, uint32_t every, void *stream);
 
 /* Diagnostic: *h_skewed = 1 when a recent chunk of this table overflowed its dedup bins (keys

@@ -90,8 +90,8 @@ struct alignas(256) Header {
   uint64_t pool_bad;
   int64_t pool_count;
   uint64_t pool_h1, pool_h2;
-  uint32_t inject;         // test hook: when nonzero, the first claim of every chunk element whose
-                           // index is a multiple of it is treated as lost to another key
+  uint32_t inject;         // test hook: when nonzero, one key in that many (by its hash) loses its
+                           // first claim in a bucket (ct_probe.h, injected_loss)
   uint64_t closed_count;   // health scan: buckets without an empty slot
   uint64_t tomb_count;     //              tombstone slots
   uint64_t fbd[2];         // the last insert (0) and erase (1) chunk: keys << 32 | keys stored

@@ -29,7 +29,7 @@ typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
 
 constexpr uint32_t kBitsMatch = 0xFFu;      // bits of an answer: slots holding the key
 constexpr int kEmptyShift = 8;              //   slots holding kEmpty
-constexpr int kTombShift = 16;              //   slots holding kTomb (FREE rounds only)
+constexpr int kTombShift = kEmptyShift + 8; //   slots holding kTomb (FREE rounds only)
 
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp(uint32_t v) {
@@ -173,6 +173,17 @@ __device__ __forceinline__ WaveLds* wave_lds() {
 // view asks for and loses.  So a copy either claims, sees the key, or loses its CAS to the key, and
 // a key is stored once.  Every bucket is asked at most once per slot, so each lane ends.
 // (Probing the bucket again after each lost claim: 2^16 keys into an empty map of 2^17 took 23 us.)
+//
+// The test hook (`inject`, 0 = off) makes keys chosen by their hash lose their claim of one slot per
+// bucket, the first in their order (their compare-and-swap expects the other kind of free slot there),
+// and ask for it again once the bucket's other free slots are gone.  Key and slot alone decide, not
+// what a copy saw, so all copies still ask in the same order.  The slot, or kSlots for none:
+__device__ __forceinline__ uint32_t injected_loss(uint64_t key, uint32_t inject, uint32_t first) {
+  return inject && (uint32_t)(dedup_mix(key) >> 32) % inject == 0 ? first : (uint32_t)kSlots;
+}
+
+constexpr uint32_t kFreeSlot = 0x101u;  // slot 0 of a bucket's free slots: bits 0-7 empty, 8-15 tombstones
+
 struct Place {
   bool found;      // the key is there (with CLAIM: or another copy of it got the slot)
   bool had_empty;  // its bucket holds an empty slot
@@ -182,19 +193,17 @@ struct Place {
 
 template <bool CLAIM, bool VAL, bool AHEAD>
 __device__ __forceinline__ Place place_keys(const TableView& t, WaveLds* w, bool look, uint64_t key,
-                                            bool claim, uint32_t inject, uint64_t id,
-                                            bool home_full = false) {
+                                            bool claim, uint32_t inject, bool home_full = false) {
   Place r = {false, false, kNoPos, 0};
   const Seq q = probe_seq(t, key);
   const uint32_t step = (uint32_t)q.step;
   uint32_t b = (uint32_t)q.home, left = (uint32_t)t.nb;
   uint32_t fb = kNone, fleft = 0;           // first bucket with a free slot on the path
-  uint32_t fe = 0, ft = 0;                  // its empty slots and tombstones
+  uint32_t fs = 0;                          // its free slots: bits 0-7 empty, 8-15 tombstones
   if (home_full) {  // known: begin at the second bucket of the path
     b = next_bucket32(t, b, step);
     look = look && --left != 0;
   }
-  bool forced = CLAIM && inject && id % inject == 0;  // test hook: the first claim counts as lost
   for (uint64_t mask = __ballot(look); mask; mask = __ballot(look)) {
     const ProbeRound<CLAIM, VAL, AHEAD> round(t, w, mask, look, key, b, step);
     bool claiming = false;
@@ -214,12 +223,11 @@ __device__ __forceinline__ Place place_keys(const TableView& t, WaveLds* w, bool
       }
       const uint32_t e = (x >> kEmptyShift) & 0xFFu;
       if constexpr (CLAIM) {
-        const uint32_t tb = (x >> kTombShift) & 0xFFu;
-        if (fb == kNone && (e | tb)) {
+        const uint32_t fr = (x >> kEmptyShift) & 0xFFFFu;
+        if (fb == kNone && fr) {
           fb = b;
           fleft = left;
-          fe = e;
-          ft = tb;
+          fs = fr;
         }
       }
       if (!e && --left != 0) {
@@ -231,22 +239,29 @@ __device__ __forceinline__ Place place_keys(const TableView& t, WaveLds* w, bool
     }
     if constexpr (CLAIM) {
       const uint32_t rot = (step >> 1) & 7u;
+      uint32_t lose = injected_loss(key, inject, rot);
+      uint32_t late = 0;  // the slot of an injected loss, asked for again at the end
       while (claiming) {
-        const uint32_t f = ft ? ft : fe;
+        const uint32_t f = fs >> 8 ? fs >> 8 : fs;
         const uint32_t c = ((uint32_t)__builtin_ctz((f * 0x101u) >> rot) + rot) & 7u;
-        uint64_t expected = ft ? kTomb : kEmpty;
-        if (forced) {
-          forced = false;
-        } else if (cas64(&t.bk[fb].s[c].key, expected, key)) {
+        uint64_t expected = (fs >> 8 != 0) != (c == lose) ? kTomb : kEmpty;
+        if (cas64(&t.bk[fb].s[c].key, expected, key)) {
           r.pos = (uint64_t)fb * kSlots + c;
           claiming = false;
         } else if (expected == key) {
           r.found = true;
           claiming = false;
         } else {  // taken by another key
-          fe &= ~(1u << c);
-          ft &= ~(1u << c);
-          if (!(fe | ft)) {  // the bucket is full now
+          if (c == lose) {
+            late = fs & kFreeSlot << c;
+            lose = kSlots;
+          }
+          fs &= ~(kFreeSlot << c);
+          if (!fs) {
+            fs = late;
+            late = 0;
+          }
+          if (!fs) {  // the bucket is full now
             claiming = false;
             b = next_bucket32(t, fb, step);
             left = fleft - 1;

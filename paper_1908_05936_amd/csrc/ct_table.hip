@@ -710,7 +710,7 @@ __device__ __forceinline__ int64_t insert_range(const TableView& t, WaveLds* w,
                                                 int32_t* __restrict__ vout, int64_t lo, int64_t hi,
                                                 int64_t step) {
   const bool fast = t.hdr->fast != 0;
-  const uint32_t inject = t.hdr->inject;
+  const uint32_t inject = __builtin_amdgcn_readfirstlane(t.hdr->inject);
   const bool flags = ALLOC || !fast;
   const bool binned = t.hdr->dmode != 0;
   int64_t ins = 0;
@@ -756,7 +756,7 @@ __device__ __forceinline__ int64_t insert_range(const TableView& t, WaveLds* w,
       }
     }
     const bool look = actor && key < kTomb;
-    const Place p = place_keys<true, ALLOC, AHEAD>(t, w, look, key, fast, inject, (uint64_t)i);
+    const Place p = place_keys<true, ALLOC, AHEAD>(t, w, look, key, fast, inject);
     if (look) {
       if (p.found) {
         st = kPresent;
@@ -857,7 +857,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(AHEAD ? 
 // Counts per block, summed by k_apply_count.
 __global__ __launch_bounds__(kBlock) void k_rehash(TableView src, TableView dst) {
   const int64_t nslots = (int64_t)src.nb * kSlots;
-  const uint32_t inject = dst.hdr->inject;
+  const uint32_t inject = __builtin_amdgcn_readfirstlane(dst.hdr->inject);
   int64_t ins = 0;
   for (int64_t w0 = (int64_t)blockIdx.x * kBlock + (threadIdx.x & ~63u); w0 < nslots;
        w0 += (int64_t)gridDim.x * kBlock) {
@@ -867,8 +867,7 @@ __global__ __launch_bounds__(kBlock) void k_rehash(TableView src, TableView dst)
     sl.val = 0;
     if (j < nslots) sl = src.bk[j >> 3].s[j & 7];
     const bool live = sl.key < kTomb;
-    const Place p = place_keys<true, false, false>(dst, wave_lds<kBlock>(), live, sl.key, true, inject,
-                                            (uint64_t)j);
+    const Place p = place_keys<true, false, false>(dst, wave_lds<kBlock>(), live, sl.key, true, inject);
     if (live && !p.found) {
       if (p.pos != kNoPos) {
         dst.bk[p.pos >> 3].s[p.pos & 7].val = sl.val;
@@ -916,7 +915,7 @@ __device__ __forceinline__ int64_t erase_range(const TableView& t, WaveLds* w,
         hit = 1;
       }
     }
-    const Place p = place_keys<false, RELEASE, AHEAD>(t, w, actor && key < kTomb, key, false, 0, 0);
+    const Place p = place_keys<false, RELEASE, AHEAD>(t, w, actor && key < kTomb, key, false, 0);
     if (p.found) {
       // kEmpty only where the bucket already holds one: no probe sequence runs through it
       t.bk[p.pos >> 3].s[p.pos & 7].key = p.had_empty ? kEmpty : kTomb;
@@ -1031,7 +1030,7 @@ __device__ __forceinline__ uint2 insert_spec_range(const TableView& t, WaveLds* 
                                                    const void* __restrict__ vals,
                                                    uint8_t* __restrict__ status, int64_t lo,
                                                    int64_t hi, int64_t step) {
-  const uint32_t inject = t.hdr->inject;
+  const uint32_t inject = __builtin_amdgcn_readfirstlane(t.hdr->inject);
   uint32_t ins = 0, listed = 0;
   for (int64_t w0 = lo + (int64_t)(threadIdx.x & ~63u); w0 < hi; w0 += step) {
     const int64_t i = w0 + wave_lane();
@@ -1042,7 +1041,7 @@ __device__ __forceinline__ uint2 insert_spec_range(const TableView& t, WaveLds* 
     uint8_t st = kPresent;
     uint8_t claimed = 0;
     const bool look = valid && key < kTomb;
-    const Place p = place_keys<true, false, AHEAD>(t, w, look, key, true, inject, (uint64_t)i);
+    const Place p = place_keys<true, false, AHEAD>(t, w, look, key, true, inject);
     if (look) {
       if (p.found) {
         amb = true;
@@ -1092,7 +1091,7 @@ __device__ __forceinline__ uint2 erase_spec_range(const TableView& t, WaveLds* w
     const int64_t i = w0 + wave_lane();
     const bool valid = i < hi;
     const uint64_t key = keys[min(i, hi - 1)];
-    const Place p = place_keys<false, false, AHEAD>(t, w, valid && key < kTomb, key, false, 0, 0);
+    const Place p = place_keys<false, false, AHEAD>(t, w, valid && key < kTomb, key, false, 0);
     uint8_t hit = 0;
     if (p.found) {
       uint64_t expected = key;
@@ -1737,6 +1736,7 @@ __global__ __launch_bounds__(kPartThreads) void k_part_insert(TableView t, PartV
   }
   if (threadIdx.x == 0) nleft = 0;
   __syncthreads();
+  const uint32_t inject = __builtin_amdgcn_readfirstlane(t.hdr->inject);
   uint32_t claimed = 0;
   uint64_t val[kPartPer];
   uint32_t idx[kPartPer], slot[kPartPer];  // slot: LDS word of the value; 0: none
@@ -1761,17 +1761,26 @@ __global__ __launch_bounds__(kPartThreads) void k_part_insert(TableView t, PartV
     uint32_t c = m ? (uint32_t)__builtin_ctz(m) : 0u;
     bool met = m != 0, over = !met && !em, full = over && !tb;
     bool won = false;
+    const uint32_t rot = (uint32_t)(key >> 61);
+    uint32_t lose = injected_loss(key, inject, rot), late = 0;  // test hook, as in place_keys
+    uint32_t fs = em | tb << 8;
     while (!met && !over && !won) {  // absent: every pass takes a slot or learns that it is gone
-      const uint32_t fr = tb ? tb : em;
-      const uint32_t rot = (uint32_t)(key >> 61);
+      const uint32_t fr = fs >> 8 ? fs >> 8 : fs;
       c = ((uint32_t)__builtin_ctz((fr * 0x101u) >> rot) + rot) & 7u;
-      const unsigned long long want = tb ? kTomb : kEmpty;
+      const unsigned long long want = (fs >> 8 != 0) != (c == lose) ? kTomb : kEmpty;
       const unsigned long long got = atomicCAS(&w[2 * c], want, (unsigned long long)key);
       won = got == want;
       met = got == key;
-      em &= ~(1u << c);
-      tb &= ~(1u << c);
-      over = full = !met && !won && !(em | tb);
+      if (c == lose) {
+        late = fs & kFreeSlot << c;
+        lose = kSlots;
+      }
+      fs &= ~(kFreeSlot << c);
+      if (!fs) {
+        fs = late;
+        late = 0;
+      }
+      over = full = !met && !won && !fs;
     }
     claimed += won;
     if (over) {
@@ -1830,7 +1839,7 @@ __device__ __forceinline__ uint2 part_place(const TableView& t, const PartView& 
                                             uint64_t val, int64_t i, uint32_t inject, bool home_full,
                                             uint8_t* __restrict__ status) {
   const Place p = place_keys<true, false, false>(t, wave_lds<kBlock>(), mine, key, true, inject,
-                                                 (uint64_t)i, home_full);
+                                                 home_full);
   if (!mine) return make_uint2(0, 0);
   uint8_t f = kFlagClaimed;
   if (p.found) {
@@ -1856,7 +1865,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
   const uint32_t c = blockIdx.x / (uint32_t)blocks;
   const uint32_t m = P.nleft[c * kCtrStride];
   const int64_t src = (int64_t)c * kBinSub * P.c1;
-  const uint32_t inject = t.hdr->inject;
+  const uint32_t inject = __builtin_amdgcn_readfirstlane(t.hdr->inject);
   uint32_t claimed = 0, listed = 0;
   for (uint32_t j0 = blockIdx.x % (uint32_t)blocks * kBlock + (threadIdx.x & ~63u); j0 < m;
        j0 += (uint32_t)blocks * kBlock) {
@@ -1881,7 +1890,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
   if (*P.nover == 0) return;
   __shared__ uint16_t list[kPartWindow];
   __shared__ uint32_t m;
-  const uint32_t inject = t.hdr->inject;
+  const uint32_t inject = __builtin_amdgcn_readfirstlane(t.hdr->inject);
   uint32_t claimed = 0, listed = 0;
   for (int64_t w0 = (int64_t)blockIdx.x * kPartWindow; w0 < n; w0 += (int64_t)gridDim.x * kPartWindow) {
     if (threadIdx.x == 0) m = 0;
@@ -2091,7 +2100,7 @@ __device__ __forceinline__ void final_tile(const TableView& t, WaveLds* w, PoolH
         if (stored) pos = t.ref[i];
       } else {
         const uint64_t key = keys[i];
-        const Place p = place_keys<true, false, false>(t, w, stored && key < kTomb, key, true, 0, 0);
+        const Place p = place_keys<true, false, false>(t, w, stored && key < kTomb, key, true, 0);
         pos = p.pos;
         if (stored && key >= kTomb) {
           pos = kSpecRef + (key - kTomb);
@@ -2208,7 +2217,7 @@ __global__ __launch_bounds__(1024) void k_small(TableView t, PoolHeader* pool,
   const int bd = (int)blockDim.x, tid = (int)threadIdx.x, wave = tid >> 6;
   const uint64_t size0 = hdr->size;
   const uint64_t room = t.cap - size0;
-  const uint32_t inject = kIns ? hdr->inject : 0u;
+  const uint32_t inject = kIns ? __builtin_amdgcn_readfirstlane(hdr->inject) : 0u;
   int64_t top0 = 0, head = 0, pcap = 0;
   if (kPool) {
     top0 = pool->top;
@@ -2274,7 +2283,7 @@ __global__ __launch_bounds__(1024) void k_small(TableView t, PoolHeader* pool,
         }
       }
       const Place p = place_keys<kIns, kPool, true>(t, w, mine && !special, key, kIns && (fast || pass),
-                                                    pass ? 0 : inject, (uint64_t)i);
+                                                    inject);
       bool found = p.found;
       uint64_t val = p.val, pos = p.pos;
       if (mine && special) {

@@ -565,7 +565,7 @@ class Table:
         return e.value
 
     def debug_inject_claim_losses(self, every: int):
-        """Test hook: treat the first claim of every `every`-th chunk element as lost (0 = off)."""
+        """Test hook: one key in `every`, by its hash, loses its first claim in a bucket (0 = off)."""
         _check(lib().ct_table_debug_inject_claim_losses(self._h, int(every), _stream(self.device)),
                "ct_table_debug_inject_claim_losses")
 
