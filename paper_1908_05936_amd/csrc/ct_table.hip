@@ -87,6 +87,14 @@ __device__ __forceinline__ uint32_t dedup_lookup(const TableView& t, const uint6
 // ---------------------------------------------------------------------------------------------
 // kernels
 // ---------------------------------------------------------------------------------------------
+// The words that batches count into (spec_count, settle_count).  Every batch relies on them being zero
+// when it starts and leaves them so; initialisation, clear, and the first batch after one that
+// failed, which may have left its counts, zero them.  One block.
+__device__ __forceinline__ void zero_counts(const TableView& t) {
+  if (threadIdx.x < kCountStripes) t.stripes[threadIdx.x * kCountStride] = 0;
+  if (threadIdx.x == kCountStripes) t.stripes[kSettleWord] = 0;
+}
+
 // Empty every slot in [lo, hi) (thread-strided by `step`); `header` also resets the counters.
 // Slots are written as 16-byte words, U per thread and round (the stores of a round issue
 // back to back; a round that would pass `hi` takes a bounds test per word).
@@ -104,6 +112,7 @@ __device__ __forceinline__ void reset_range(const TableView& t, int64_t lo, int6
   }
   for (int u = 0; u < U; ++u)
     if (j + u * width < hi) slots[j + u * width] = empty;
+  if (header) zero_counts(t);
   if (header && threadIdx.x == 0) {
     Header* h = t.hdr;
     h->size = 0;
@@ -114,8 +123,6 @@ __device__ __forceinline__ void reset_range(const TableView& t, int64_t lo, int6
     if (zero_err) {
       h->err = 0;
       h->inject = 0;
-      for (int j = 0; j < kCountStripes; ++j) t.stripes[j * kCountStride] = 0;
-      t.stripes[kSettleWord] = 0;
     }
     // an empty table starts a fresh history: its next insert and erase chunks speculate
     h->fbd[0] = h->fbd[1] = 0;
@@ -140,6 +147,8 @@ __global__ __launch_bounds__(kBlock) void k_table_reset(TableView t, int zero_he
   reset_range(t, (int64_t)blockIdx.x * blockDim.x, (int64_t)t.nb * kSlots,
               (int64_t)gridDim.x * blockDim.x, blockIdx.x == 0, zero_header);
 }
+
+__global__ __launch_bounds__(64) void k_zero_counts(TableView t) { zero_counts(t); }
 
 // Per chunk: clear the dedup scratch, snapshot the counters, decide whether the chunk can reach
 // capacity (or empty the pool).
@@ -3530,6 +3539,7 @@ struct ct_table {
   int64_t dd_bytes;   // bytes of the dedup scratch region at v.dd (the purge's bitmap)
   int32_t insert_path = CT_INSERT_AUTO;  // how insert chunks resolve repeated keys
   uint64_t* fb_host = nullptr;           // host side of v.fb (pinned, mapped), or null
+  bool counts_stale = false;             // a batch failed: its counts may still be in v.stripes
 };
 
 struct ct_pool {
@@ -3738,6 +3748,22 @@ int flat_blocks(int64_t n) {
 }
 
 ct_status launched() { return hipGetLastError() == hipSuccess ? CT_OK : CT_E_HIP; }
+
+// The same after launches that count into the table's words.
+ct_status counted(ct_table* t) {
+  const ct_status r = launched();
+  if (r != CT_OK) t->counts_stale = true;
+  return r;
+}
+
+// Before launches that count: zero what a failed batch may have left.  (While `s` is captured nothing
+// runs, so the mark stays.)
+void fresh_counts(ct_table* t, hipStream_t s) {
+  if (!t->counts_stale) return;
+  hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+  t->counts_stale = hipStreamIsCapturing(s, &c) != hipSuccess || c != hipStreamCaptureStatusNone;
+  k_zero_counts<<<1, 64, 0, s>>>(t->v);
+}
 
 // dedup entries for a chunk of q elements: a power of two >= 2q (load at most one half)
 uint32_t dedup_slots_for(int64_t q) { return (uint32_t)std::max<int64_t>(2, pow2ceil(2 * q)); }
@@ -4012,6 +4038,7 @@ ct_status part_insert(ct_table* t, const PartLayout& L, uint8_t* ws, const uint6
   v.flag = P.flag;
   v.dd = P.r1k;
   t->size_ub = std::min<uint64_t>(t->size_ub + (uint64_t)n, (uint64_t)t->desc.capacity);
+  fresh_counts(t, s);
   launch(t, CT_KERNEL_PROLOGUE, s, [&] { k_purge_clear<<<flat_blocks(L.ctr_words), kBlock, 0, s>>>(P.cur1, L.ctr_words); });
   launch(t, CT_KERNEL_INSERT, s, [&] { k_part_coarse<VK><<<(int)((n + kBinTile - 1) / kBinTile), kBlock, 0, s>>>(v, P, keys, vals, n, (int)L.ncoarse, status); });
   for (int64_t c0 = 0; c0 < L.ncoarse; c0 += L.group) {
@@ -4023,7 +4050,7 @@ ct_status part_insert(ct_table* t, const PartLayout& L, uint8_t* ws, const uint6
   launch(t, CT_KERNEL_INSERT, s, [&] { k_part_left<VK><<<(int)L.ncoarse * lb, kBlock, 0, s>>>(v, P, lb, status); });
   launch(t, CT_KERNEL_INSERT, s, [&] { k_part_over<VK><<<(int)std::min<int64_t>((n + kPartWindow - 1) / kPartWindow, kSpecGrid), kBlock, 0, s>>>(v, P, keys, vals, n, status); });
   spec_resolve<VK, false>(t, v, keys, vals, n, status, dedup_slots_for(std::min<int64_t>(n, (int64_t)1 << 26)), s);
-  return launched();
+  return counted(t);
 }
 
 // Insert of n keys in the chunks and with the scratch of B.
@@ -4031,6 +4058,7 @@ template <int VK>
 ct_status insert_chunks(ct_table* t, const BatchScratch& B, const uint64_t* keys,
                         const void* vals, int64_t n, uint8_t* status, hipStream_t s) {
   const TableView& v = B.v;
+  fresh_counts(t, s);
   const int vb = VK == 1 ? 4 : 8;
   for (int64_t c0 = 0; c0 < n; c0 += B.chunk) {
     const int64_t q = std::min<int64_t>(B.chunk, n - c0);
@@ -4052,7 +4080,7 @@ ct_status insert_chunks(ct_table* t, const BatchScratch& B, const uint64_t* keys
       // speculative: insert first, then resolve the copies of keys listed as ambiguous
       launch(t, CT_KERNEL_INSERT, s, [&] { (q <= kAheadMax ? k_insert_spec<VK, true> : k_insert_spec<VK, false>)<<<gb, kBlock, 0, s>>>(v, kc, vc, q, sc, 0); });
       spec_resolve<VK, false>(t, v, kc, vc, q, sc, db, s);
-      ct_status r = launched();
+      ct_status r = counted(t);
       if (r != CT_OK) return r;
       continue;
     }
@@ -4075,7 +4103,7 @@ ct_status insert_chunks(ct_table* t, const BatchScratch& B, const uint64_t* keys
       launch(t, CT_KERNEL_FINAL, s, [&] { k_final<VK, 0><<<ntiles, kBlock, 0, s>>>(v, nullptr, nullptr, kc, vc, q, sc, nullptr, inl); });
     }
     if (sc && !surely_fast) launch(t, CT_KERNEL_FIX, s, [&] { k_fix<<<flat_blocks((q + 3) / 4), kBlock, 0, s>>>(v, q, sc, nullptr, 0); });
-    ct_status r = launched();
+    ct_status r = counted(t);
     if (r != CT_OK) return r;
   }
   return CT_OK;
@@ -4093,6 +4121,7 @@ template <bool RELEASE>
 ct_status erase_chunks(ct_table* t, const BatchScratch& B, ct_pool* p, const uint64_t* keys,
                        int64_t n, uint8_t* erased, hipStream_t s) {
   const TableView& v = B.v;
+  fresh_counts(t, s);
   for (int64_t c0 = 0; c0 < n; c0 += B.chunk) {
     const int64_t q = std::min<int64_t>(B.chunk, n - c0);
     const uint32_t db = dedup_slots_for(q);
@@ -4110,7 +4139,7 @@ ct_status erase_chunks(ct_table* t, const BatchScratch& B, ct_pool* p, const uin
       // speculative: remove first, then move each removal to the lowest copy of its key
       launch(t, CT_KERNEL_ERASE, s, [&] { (q <= kAheadMax ? k_erase_spec<true> : k_erase_spec<false>)<<<gb, kBlock, 0, s>>>(v, kc, q, ec); });
       spec_resolve<0, true>(t, v, kc, nullptr, q, ec, db, s);
-      ct_status r = launched();
+      ct_status r = counted(t);
       if (r != CT_OK) return r;
       continue;
     }
@@ -4124,7 +4153,7 @@ ct_status erase_chunks(ct_table* t, const BatchScratch& B, ct_pool* p, const uin
       if (!inl) launch(t, CT_KERNEL_RANK, s, [&] { k_tile_scan<<<1, 1024, 0, s>>>(v, p->hdr, ntiles, 2); });
       launch(t, CT_KERNEL_FINAL, s, [&] { k_final<0, 2><<<ntiles, kBlock, 0, s>>>(v, p->hdr, p->stack, kc, nullptr, q, nullptr, nullptr, inl); });
     }
-    ct_status r = launched();
+    ct_status r = counted(t);
     if (r != CT_OK) return r;
   }
   return CT_OK;
@@ -5223,6 +5252,7 @@ ct_status ct_plan_launch_grouped(ct_plan* p, void* stream) {
   hipStream_t s = S(stream);
   const GStep* st = static_cast<const GStep*>(p->gsteps);
   const GEntry* en = static_cast<const GEntry*>(p->gentries);
+  for (ct_table* t : p->tables) fresh_counts(t, s);
   for (const ct_group::Launch& L : p->glaunch) {
     const GEntry* e = en + L.entry_off;
     switch (L.stage) {
@@ -5251,7 +5281,10 @@ ct_status ct_plan_launch_grouped(ct_plan* p, void* stream) {
         break;
       default: return CT_E_INVALID;
     }
-    if (launched() != CT_OK) return CT_E_HIP;
+    if (launched() != CT_OK) {
+      for (ct_table* t : p->tables) t->counts_stale = true;
+      return CT_E_HIP;
+    }
   }
   return CT_OK;
 }
@@ -5282,6 +5315,7 @@ ct_status ct_plan_launch_single(ct_plan* p, int32_t max_blocks, void* stream) {
   const GStep* st = static_cast<const GStep*>(p->gsteps);
   const GEntry* en = static_cast<const GEntry*>(p->gentries);
   const GCopy* cp = static_cast<const GCopy*>(p->gcopies);
+  for (ct_table* t : p->tables) fresh_counts(t, s);
   void* args[] = {&ls, &nl, &st, &en, &cp};
   if (hipLaunchCooperativeKernel(reinterpret_cast<const void*>(k_g_persistent), dim3((unsigned)grid),
                                  dim3(kBlock), args, 0, s) != hipSuccess) {
