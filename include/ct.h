@@ -430,13 +430,16 @@ ct_status ct_erase_release_batch(ct_table *t, ct_pool *p, const uint64_t *keys, 
    per bucket brings the keys to the buckets.  Results are the same.
 
    *bytes: what a batch of n keys can use now, for an insert (CT_OP_INSERT) or an erase
-   (CT_OP_ERASE), with pool != 0 for insert_alloc and erase_release; 0 when the table's own scratch serves it (a batch of one chunk, a chunk that
-   the caller chose, or the large chunks of the largest tables).  Host only. */
+   (CT_OP_ERASE), with pool != 0 for insert_alloc and erase_release; 0 when the table's own scratch
+   serves it (a batch of one chunk, a chunk that the caller chose, or the large chunks of the largest
+   tables).  It follows what the table's last batches have reported, so it can change when they end.
+   Host only. */
 ct_status ct_workspace_bytes(const ct_table *t, int32_t op, int32_t pool, int64_t n, int64_t *bytes);
 
 /* ct_insert_batch, ct_erase_batch, ct_insert_alloc_batch (skip NULL) or ct_insert_alloc_batch_masked,
-   and ct_erase_release_batch.  ws may be NULL, and a workspace smaller than ct_workspace_bytes is
-   left unused: the batch then runs as without one.  CT_E_INVALID for a misaligned ws. */
+   and ct_erase_release_batch.  ws may be NULL, and a workspace smaller than what ct_workspace_bytes
+   would answer at the time of the call is left unused: the batch then runs as without one.
+   CT_E_INVALID for a misaligned ws. */
 ct_status ct_insert_batch_ws(ct_table *t, const uint64_t *keys, const void *vals, int64_t n,
                              uint8_t *status, void *ws, int64_t ws_bytes, void *stream);
 ct_status ct_erase_batch_ws(ct_table *t, const uint64_t *keys, int64_t n, uint8_t *erased, void *ws,

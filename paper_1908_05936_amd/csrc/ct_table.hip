@@ -3867,26 +3867,22 @@ int64_t batch_bytes(const ct_table* t, BatchKind kind, int64_t n) {
   return q && layout_scratch(&L, q, 0) ? L.total : 0;
 }
 
-// The table's own scratch, or `ws` when it holds the chunk that the batch would like.  (A workspace
-// that was sized for a speculative batch makes the batch one, whatever the table's last chunk has
-// reported since.)
+// The table's own scratch, or `ws` when it holds what the batch can use now (batch_bytes).
 BatchScratch batch_scratch(const ct_table* t, BatchKind kind, int64_t n, void* ws, int64_t ws_bytes) {
   BatchScratch b = {t->v, t->chunk, false};
   if (!ws) return b;
   uint8_t* base = static_cast<uint8_t*>(ws);
-  const int64_t q = workspace_chunk(t, n);
   Layout L;
-  const bool full = q && layout_scratch(&L, q, 0) && ws_bytes >= L.total;
-  const int64_t sq = kind == bPool ? 0 : spec_chunk(t, n);
-  const bool can = kind == bErase ||
-                   (kind == bInsert && t->size_ub + (uint64_t)n <= (uint64_t)t->desc.capacity);
-  if (sq && can && t->insert_path != CT_INSERT_RESOLVE_FIRST && ws_bytes >= spec_bytes(sq) &&
-      (!full || use_speculation(t, kind == bErase ? 1 : 0))) {
-    b.v.dd = reinterpret_cast<uint64_t*>(base);
-    b.v.flag = base + align_up(12 * sq);
-    b.chunk = sq;
-    b.spec = true;
-  } else if (full) {
+  if (kind != bPool && spec_wanted(t, kind == bErase, n)) {
+    const int64_t q = spec_chunk(t, n);
+    if (q && ws_bytes >= spec_bytes(q)) {
+      b.v.dd = reinterpret_cast<uint64_t*>(base);
+      b.v.flag = base + align_up(12 * q);
+      b.chunk = q;
+      b.spec = true;
+    }
+  } else if (const int64_t q = workspace_chunk(t, n);
+             q && layout_scratch(&L, q, 0) && ws_bytes >= L.total) {
     scratch_view(&b.v, base, L);
     b.chunk = q;
   }
@@ -4329,8 +4325,10 @@ ct_status ct_insert_batch_ws(ct_table* t, const uint64_t* keys, const void* vals
   const int vk = t->desc.val_kind;
   if (vk != CT_VAL_NONE && !vals) return CT_E_INVALID;
   PartLayout P;
-  if (ws && part_wanted(t, n, &P) && ws_bytes >= P.total) {
+  if (ws && part_wanted(t, n, &P)) {
     uint8_t* w = static_cast<uint8_t*>(ws);
+    if (ws_bytes < P.total)
+      return insert_any(t, BatchScratch{t->v, t->chunk, false}, keys, vals, n, status, S(stream));
     if (vk == CT_VAL_U32) return part_insert<1>(t, P, w, keys, vals, n, status, S(stream));
     if (vk == CT_VAL_U64) return part_insert<2>(t, P, w, keys, vals, n, status, S(stream));
     return part_insert<0>(t, P, w, keys, nullptr, n, status, S(stream));
