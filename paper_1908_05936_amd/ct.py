@@ -278,7 +278,15 @@ class Pool:
 
 
 class Table:
-    """unordered_map (value_kind VAL_U32 / VAL_U64) or unordered_set (VAL_NONE) on one GPU."""
+    """unordered_map (value_kind VAL_U32 / VAL_U64) or unordered_set (VAL_NONE) on one GPU.
+
+    Batches larger than the table's chunk borrow a workspace from torch's allocator while they run
+    (13 bytes a key, about 109 for repeated keys or near capacity, about 30 for large inserts of
+    several keys per bucket).  ``workspace = False`` makes them run in the table's own chunks
+    instead: same results, slower."""
+
+    workspace = True
+    _WS_REST = 64   # batches without asking again after torch had no memory for a workspace
 
     def __init__(self, capacity: int, value_kind: int = VAL_U64, hash_kind: int = HASH_MIX64,
                  bucket_count: int = 0, chunk: int = 0, device="cuda"):
@@ -302,6 +310,7 @@ class Table:
         self.chunk = c.value
         self.capacity = int(capacity)
         self.value_kind = int(value_kind)
+        self._ws_rest = 0
 
     def __del__(self):
         if getattr(self, "_h", None) and _lib is not None:
@@ -316,8 +325,12 @@ class Table:
         """(workspace tensor or None, its bytes) for a batch of n keys.  It comes from torch's
         allocator on the current stream, so a later tensor takes its memory only after this call's
         kernels.  Without the memory, and while the stream is captured into a graph (which would
-        keep it), the batch runs in the table's own chunks."""
-        if n <= self.chunk or torch.cuda.is_current_stream_capturing():
+        keep it), the batch runs in the table's own chunks.  A request that fails empties torch's
+        cache and waits for the GPU first, so the next batches do not ask."""
+        if n <= self.chunk or not self.workspace or torch.cuda.is_current_stream_capturing():
+            return None, 0
+        if self._ws_rest:
+            self._ws_rest -= 1
             return None, 0
         nb = C.c_int64(0)
         _check(lib().ct_workspace_bytes(self._h, op, pool, n, C.byref(nb)), "ct_workspace_bytes")
@@ -326,6 +339,7 @@ class Table:
         try:
             return torch.empty(nb.value, dtype=torch.uint8, device=self.device), nb.value
         except torch.cuda.OutOfMemoryError:
+            self._ws_rest = self._WS_REST
             return None, 0
 
     def insert(self, keys: torch.Tensor, vals: torch.Tensor | None = None, status: bool = True):
