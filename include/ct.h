@@ -99,8 +99,8 @@ typedef struct ct_table_desc {
     int64_t chunk;        /* keys handled per internal insert/erase chunk; a power of two in
                              [1024, 2^24]; 0 = the largest power of two <= C/8, clamped to
                              [1024, 2^23].  Batches larger than a chunk run as consecutive chunks
-                             (same results).  The table buffer holds about 34 bytes of scratch
-                             per chunk element below 2^16, and 82-109 for larger chunks, which
+                             (same results).  The table buffer holds about 30 bytes of scratch
+                             per chunk element below 2^16, and 78-103 for larger chunks, which
                              resolve repeated keys through bins (ct_table_bytes is exact). */
 } ct_table_desc;
 
@@ -137,7 +137,7 @@ ct_status ct_insert_batch(ct_table *t, const uint64_t *keys, const void *vals, i
 /* ct_insert_batch for callers that cannot allocate device memory, or must not do so while they
    run (code under HIP graph capture, tight serving loops, harnesses that forbid allocation).  Same
    arguments, same results and the same table as ct_insert_batch, but the per-chunk scratch
-   (repeated-key table, marks, lists, rank sums, count partials: about 1.2 MiB) lives in one static
+   (repeated-key table, marks, first copies, rank sums, count partials: about 1.1 MiB) lives in one static
    device array per GPU instead of the table buffer, and no call allocates anything.  The batch
    runs in chunks of at most 2^15 elements, the largest the array holds, so every batch size is
    accepted.  Every call on one GPU shares that GPU's array: calls that overlap on one GPU (other

@@ -128,7 +128,7 @@ struct TableView {
   uint64_t* dd;      // dedup scratch: (fingerprint << 32 | lowest chunk index), kEmpty = free
   uint8_t* dmark;   // per chunk element: 1 = its key occurs more than once in the chunk (a binned
                     // chunk's insert kernel writes them where k_fix reads them)
-  uint32_t* dup;    // per repeated element: index of its key's first occurrence (for k_fix)
+  uint32_t* dup;    // per element that is repeated: index of its key's first occurrence (for k_fix)
   uint8_t* flag;    // per chunk element: 1 = takes part in the rank scan
   uint64_t* ref;    // per chunk element: claimed slot, or the value an erase releases
   uint32_t* tsum;   // per tile: flagged count, then its exclusive prefix

@@ -3578,7 +3578,7 @@ int64_t pow2ceil(int64_t x) {
 
 struct Layout {
   int64_t nb, chunk, dslots, ntiles;
-  int64_t off_bk, off_dd, off_dmark, off_dup, off_flag, off_ref, off_tsum, off_bcnt, total;
+  int64_t off_bk, off_dd, off_dmark, off_dup, off_flag, off_ref, off_tsum, off_bcnt, off_stripes, total;
   // binned dedup (chunk >= kBinMinChunk; otherwise bins == false and the offsets are unused)
   bool bins;
   int64_t nfine, c1, c2;
@@ -3601,7 +3601,7 @@ bool make_layout(const ct_table_desc* d, Layout* L) {
   int64_t q = d->chunk;
   if (q == 0) {
     // one chunk per ~capacity/8 keys: long kernels amortise launch and drain, and the scratch
-    // (about 82 bytes per chunk element at these sizes) stays below two thirds of the buckets'
+    // (about 78 bytes per chunk element at these sizes) stays below two thirds of the buckets'
     // 16 bytes per slot
     int64_t f = 1024;
     while (f * 2 <= d->capacity / 8 && f < ((int64_t)1 << 23)) f *= 2;
@@ -3612,7 +3612,10 @@ bool make_layout(const ct_table_desc* d, Layout* L) {
   int64_t off = align_up((int64_t)sizeof(Header));
   L->off_bk = off;
   off = align_up(off + nb * (int64_t)sizeof(Bucket));
-  return layout_scratch(L, q, off);
+  if (!layout_scratch(L, q, off)) return false;
+  L->off_stripes = L->total;  // the table's own, whatever scratch a batch runs on
+  L->total = align_up(L->total + kStripeRegion);
+  return true;
 }
 
 // The per-chunk scratch of chunks of q elements (a power of two in [1024, 2^24]), from offset `off`.
@@ -3652,7 +3655,7 @@ bool layout_scratch(Layout* L, int64_t q, int64_t off) {
   L->off_dmark = off;
   off = align_up(off + q);
   L->off_dup = off;
-  off = align_up(off + q * (int64_t)sizeof(uint2));
+  off = align_up(off + q * 4);
   L->off_flag = off;
   off = align_up(off + q);
   L->off_ref = off;
@@ -3660,7 +3663,7 @@ bool layout_scratch(Layout* L, int64_t q, int64_t off) {
   L->off_tsum = off;
   off = align_up(off + L->ntiles * 4);
   L->off_bcnt = off;
-  off = align_up(off + kMaxGroupBlocks * 8 + kStripeRegion);
+  off = align_up(off + kMaxGroupBlocks * 8);
   L->total = off;
   return true;
 }
@@ -3785,7 +3788,7 @@ struct BatchScratch {
   bool spec;  // it holds what speculative chunks need, and no more
 };
 
-// Chunk of a batch of n keys given a workspace: the whole batch up to 2^21 keys (228 MB), when that
+// Chunk of a batch of n keys given a workspace: the whole batch up to 2^21 keys (165 MB), when that
 // is more than the table's own chunk and the caller left the chunk to the library; else 0.  A
 // default table cuts a batch that fills it into eight or more chunks of 6 to 12 launches each,
 // which is what small and middle tables spend their time on: 4 M repeated keys into a set of 10^6
@@ -3843,7 +3846,7 @@ bool spec_wanted(const ct_table* t, bool erase, int64_t n) {
          use_speculation(t, erase ? 1 : 0);
 }
 
-// Chunk of a speculative batch given a workspace.  13 bytes a key instead of 109 make chunks of 2^23
+// Chunk of a speculative batch given a workspace.  13 bytes a key instead of 79 make chunks of 2^23
 // keys affordable (109 MB): 6,000,000 keys into an empty map took 500 us in chunks of 2^21, 475 in
 // one; 2^22 keys erased and inserted again in a table of 2^24 800, now 779.
 constexpr int64_t kSpecChunk = (int64_t)1 << 23;
@@ -4233,7 +4236,7 @@ ct_status ct_table_init(void* d_buf, int64_t bytes, const ct_table_desc* d, void
   v.nb = (uint64_t)L.nb;
   v.cap = (uint64_t)d->capacity;
   scratch_view(&v, base, L);
-  v.stripes = reinterpret_cast<uint64_t*>(base + L.off_bcnt + kMaxGroupBlocks * 8);
+  v.stripes = reinterpret_cast<uint64_t*>(base + L.off_stripes);
   v.hash = d->hash_kind;
   v.nb_pow2 = (L.nb & (L.nb - 1)) == 0;
   v.step_mode = v.nb_pow2 ? 1 : (is_prime(L.nb) ? 2 : 0);
@@ -5469,7 +5472,7 @@ constexpr StaticScratch static_scratch_layout() {
   L.dmark = off;
   off += kStaticChunk;
   L.dup = off;
-  off += kStaticChunk * 8;
+  off += kStaticChunk * 4;
   L.flag = off;
   off += kStaticChunk;
   L.ref = off;
@@ -5477,7 +5480,7 @@ constexpr StaticScratch static_scratch_layout() {
   L.tsum = off;
   off += 256;  // kStaticChunk / kTile tile sums, 4 bytes each
   L.bcnt = off;
-  off += (int64_t)kMaxGroupBlocks * 8 + kStripeRegion;
+  off += (int64_t)kMaxGroupBlocks * 8;
   L.total = off;
   return L;
 }

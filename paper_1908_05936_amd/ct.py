@@ -281,7 +281,7 @@ class Table:
     """unordered_map (value_kind VAL_U32 / VAL_U64) or unordered_set (VAL_NONE) on one GPU.
 
     Batches larger than the table's chunk borrow a workspace from torch's allocator while they run
-    (13 bytes a key, about 109 for repeated keys or near capacity, about 30 for large inserts of
+    (13 bytes a key, 30 to 103 for repeated keys or near capacity, about 30 for large inserts of
     several keys per bucket).  ``workspace = False`` makes them run in the table's own chunks
     instead: same results, slower."""
 
