@@ -3180,9 +3180,10 @@ __device__ __forceinline__ bool g_speculates(const GStep& g) {
   return g.spath == 2 || mostly_changed(h, ins ? 0 : 1);
 }
 
-// Prologue: a speculative step needs only its header snapshot and zeroed listed counts (the dd
-// entries are cleared after the claims, and only when something is listed); otherwise the
-// dedup scratch is cleared and the header decides as for a single-table chunk.
+// Prologue: a speculative step needs only its header words (the dd entries are cleared after the
+// claims, and only when something is listed).  Its count words are zero already: g_apply_body zeroes
+// what it has summed, as k_spec_swap does for single-table batches.  Otherwise the dedup scratch is
+// cleared and the header decides as for a single-table chunk.
 __device__ __forceinline__ void g_prologue_body(const GStep* __restrict__ st, const GLoc L) {
   const GStep g = g_step(st, L);
   const TableView t = g.v;
@@ -3742,7 +3743,11 @@ int group_blocks(int64_t n, int bs = kBlock) {
 
 // Chunks of at most this many rank tiles skip the one-block rank scan: each ranked-completion
 // block sums the tile counts before its own tile (at most four loads a thread), and the first settles the
-// chunk's totals.  (2^21 samples into blocks, 1024 tiles twice: 252.4 us with two scans, 250.5 without.)
+// chunk's totals.  Blocks allocated for n new keys and released again (two ranked batches), with
+// the scan and without: 270,000 keys (264 tiles) 105.5 and 101.7 us, 2^19 136.3 and 132.5, 700,000
+// 160.3 and 156.3, 2^20 (1024 tiles) 209.3 and 206.5; a set filled beyond its capacity by 2^20 keys
+// 111.9 and 109.1.  From there to 2048 tiles the gain ends: 217.1 and 214.8 us at 1,100,000 keys
+// allocated, 160.2 and 162.2 at 2^21 keys into the set, where every block sums eight counts a thread.
 constexpr int kInlineRankTiles = 1024;
 
 int flat_blocks(int64_t n) {
@@ -3916,7 +3921,10 @@ void find_kernel(int vk, hipStream_t s, const TableView& v, const uint64_t* keys
 
 // Batches (and last chunks) of at most this many keys run as one workgroup's launch: 2048 keys erased,
 // inserted and partly looked up took 66 us as separate launches and take 50; the limit is what one
-// workgroup holds at two keys per thread.
+// workgroup holds at two keys per thread.  The price is in tables filled to their last slots, where
+// absent keys walk hundreds of buckets or all of them and one compute unit walks them alone: 2000
+// absent keys erased from a full default table of 2^16 took 0.56 ms as separate launches and take
+// 0.75, and 7.6 and 16.5 ms where no bucket at all is open; up to load 0.95 none was slower.
 constexpr int64_t kSmallBatch = kSmallMax;
 
 template <int VK, int OP>
