@@ -3804,7 +3804,7 @@ constexpr int64_t kWorkspaceChunk = (int64_t)1 << 21;
 
 int64_t workspace_chunk(const ct_table* t, int64_t n) {
   if (t->chunk_chosen || n <= t->chunk) return 0;
-  const int64_t q = std::min<int64_t>(pow2ceil(n), kWorkspaceChunk);
+  const int64_t q = pow2ceil(std::min<int64_t>(n, kWorkspaceChunk));
   return q > t->chunk ? q : 0;
 }
 
@@ -3858,7 +3858,7 @@ constexpr int64_t kSpecChunk = (int64_t)1 << 23;
 
 int64_t spec_chunk(const ct_table* t, int64_t n) {
   if (t->chunk_chosen || n <= t->chunk) return 0;
-  const int64_t q = std::min<int64_t>(pow2ceil(n), kSpecChunk);
+  const int64_t q = pow2ceil(std::min<int64_t>(n, kSpecChunk));
   return q > t->chunk ? q : 0;
 }
 

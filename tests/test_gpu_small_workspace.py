@@ -71,3 +71,14 @@ def test_room_below_that_of_a_partitioned_insert(dev):  # noqa: F811
                                                           ws.data_ptr(), need - 256, ct._stream(dev)))
     assert got["insert"] == chunks(N, t.chunk) > 1
     assert t.size() == N and t.check() == 0
+
+
+@pytest.mark.parametrize("op,pool", [(ct.OP_INSERT, 0), (ct.OP_ERASE, 0), (ct.OP_INSERT, 1), (ct.OP_ERASE, 1)])
+def test_sizes_beyond_any_memory(dev, op, pool):  # noqa: F811
+    """The largest chunk is what a batch can use, whatever its size: no power of two is looked for past
+    the range of 64 bits."""
+    t = ct.Table(1 << 18, ct.VAL_U32, device=dev)
+    want = workspace(t, op, pool, 1 << 40)
+    assert want > 0
+    for n in ((1 << 62) - 1, 1 << 62, (1 << 62) + 1, (1 << 63) - 1):
+        assert workspace(t, op, pool, n) == want
